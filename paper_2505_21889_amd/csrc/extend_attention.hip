@@ -10,9 +10,10 @@
 //     (16 bytes per lane, 1 KB per wave instruction, XOR-swizzled 16-byte chunks), one or
 //     two tiles ahead of the one being consumed;
 //   * S^T = K Q^T with 32x32x16 bf16 MFMA: every lane ends up with 32 scores of ONE query
-//     row, so the running max / sum are per-lane scalars plus one cross-half exchange;
+//     row, so its reference and sum are per-lane scalars plus one cross-half exchange;
 //   * P is rounded to bf16 in registers and is directly the B operand of O^T += V^T P^T;
-//     V^T operands come from the row-major V tile through the transposing LDS read.
+//     V^T operands come from the row-major V tile through the transposing LDS read;
+//   * the three run as a pipeline over 32-key halves, each on another half at any time.
 // Accumulation is fp32; partial results of split key ranges are merged by a second kernel or,
 // for the decode step, by the workgroup that finishes last.
 //
@@ -326,8 +327,12 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
   constexpr int kGTileBytes = kKeyTile * kGRowBytes;
   constexpr int kGKeysPerLoad = 1024 / kGRowBytes;      // keys moved by one 1 KB wave load
   constexpr int kGLoadsPerMatrix = kGTileBytes / 1024;  // wave loads per K (or V) tile
-  // stage s: K tile at s * kStageBytes, V tile right behind it
   constexpr int kStageBytes = 2 * kGTileBytes;
+  // Buffer s of the ring: K tile at s * kSlotBytes, V tile kVOff behind it.  The pipelined kernels
+  // keep all K tiles in front of all V tiles, so that each matrix's buffers lie within the 64 KB
+  // that the offset field of an LDS read reaches.
+  constexpr int kSlotBytes = KP ? kStageBytes : kGTileBytes;
+  constexpr int kVOff = KP ? kGTileBytes : STAGES * kGTileBytes;
   // chunk swizzles of code rows.  Keys: the 8-byte operand reads of 32 consecutive keys spread
   // over all banks.  Values: a 16-lane block of the transposing read touches keys
   // {0..3, 8..11} (or {4..7, 12..15}) of a 16-key group at one 16-byte chunk; bits 0, 1 and 3
@@ -464,8 +469,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
   };
   auto issue_tile = [&](int t, int stage, const TilePages& pages) {
     if (issuer < 0) return;
-    const uint32_t kbuf = lds0 + stage * kStageBytes;
-    const uint32_t vbuf = kbuf + kGTileBytes;
+    const uint32_t kbuf = lds0 + stage * kSlotBytes;
+    const uint32_t vbuf = kbuf + kVOff;
     const int key0 = k_begin + t * kKeyTile;
     const bool full_tile = key0 + kKeyTile <= k_end;  // no row of the tile lies past the key range
     const char* kc = reinterpret_cast<const char*>(p.k_cache);
@@ -568,18 +573,20 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
     }
   };
 
-  // per-lane LDS offsets of the MFMA operands
-  const int k_row_off = i32 * G::kRowBytes;
+  // per-lane LDS addresses of the MFMA operands (buffer 0; buffers, key blocks and keys are added
+  // as constants, which go into the offset field of the read)
   const int k_swz = G::kswz(i32);
   const int k8_swz = kswz8(i32);  // same for key i32 + 32
+  uint32_t k_addr[G::kSteps];
+#pragma unroll
+  for (int st = 0; st < G::kSteps; ++st)
+    k_addr[st] = KV8 ? lds0 + i32 * D + ((st ^ k8_swz) << 4) + 8 * hi
+                     : lds0 + i32 * G::kRowBytes + (((2 * st + hi) ^ k_swz) << 4);
   // K operand of key block kb, MFMA step st: 8 consecutive head-dim elements (2 * st + hi) * 8 ..
   // of key kb * 32 + i32 -- 16 bytes of the bf16 tile, or 8 codes that become bf16 in registers
   using KRaw = std::conditional_t<KV8, u32x2, u32x4>;
-  auto read_k = [&](const char* ks, int kb, int st) -> KRaw {
-    if constexpr (KV8)
-      return *reinterpret_cast<const u32x2*>(ks + (kb * 32 + i32) * D + ((st ^ k8_swz) << 4) + 8 * hi);
-    else
-      return *reinterpret_cast<const u32x4*>(ks + k_row_off + kb * 32 * G::kRowBytes + (((2 * st + hi) ^ k_swz) << 4));
+  auto read_k = [&](uint32_t buf, int kb, int st) -> KRaw {
+    return *reinterpret_cast<const LDS_PTR(KRaw)>(k_addr[st] + (buf + kb * 32 * kGRowBytes));
   };
   // (the same conversion serves the value operands)
   auto k_operand = [&](KRaw raw) -> bf16x8 {
@@ -616,138 +623,178 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
   // V^T operand of the 16-key group ks4 and head-dim block d: raw LDS data, then as bf16
   using VRaw = KRaw;
   auto& v_operand = k_operand;
-  auto read_v_raw = [&](const char* vs, int ks4, int d) -> VRaw {
+  uint32_t v_addr[G::kDBlocks];
+#pragma unroll
+  for (int d = 0; d < G::kDBlocks; ++d)
+    v_addr[d] = KV8 ? lds0 + kVOff + v8_key * D + (((d * 2 + v8_chunk) ^ v8_swz) << 4) + v8_sub
+                    : lds0 + kVOff + v_key * G::kRowBytes + v_sub + (((d * 4 + v_chunk) ^ v_swz) << 4);
+  auto read_v_raw = [&](uint32_t buf, int ks4, int d) -> VRaw {
+    const uint32_t at = v_addr[d] + (buf + ks4 * 16 * kGRowBytes);
     if constexpr (KV8) {
-      const char* at = vs + (ks4 * 16 + v8_key) * D + (((d * 2 + v8_chunk) ^ v8_swz) << 4) + v8_sub;
       return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(i32x2))(at)));
     } else {
-      const char* vrow = vs + (ks4 * 16 + v_key) * G::kRowBytes + v_sub;
-      const int off = ((d * 4 + v_chunk) ^ v_swz) << 4;
-      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_PTR(bf16x4))(vrow + off));
-      const bf16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_PTR(bf16x4))(vrow + 8 * G::kRowBytes + off));
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_PTR(bf16x4))(at));
+      const bf16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_PTR(bf16x4))(at + 8 * G::kRowBytes));
       return __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
     }
   };
 
-  // LO: a second pass over a tile that was just processed, adding what the bf16 rounding of the
-  // probabilities dropped: the same scores and exponentials are formed again and the PV
-  // product takes lo = bf16(p - bf16(p)), so that p enters as hi + lo with 16 significant bits.
-  // Run for the first tile of a wave whose first row sees very few keys: there the output is a
-  // weighted mean of a handful of value rows and can reach magnitude 2-4, where its own bf16
-  // rounding is already 7.8e-3, and the 2^-9 relative rounding of single bf16 weights on top of
-  // that would cross the 1e-2 error bound.
-  auto compute_tile = [&](int t, const char* ks, const char* vs, auto lo_c) __attribute__((always_inline)) {
-    constexpr bool LO = decltype(lo_c)::value;
-    const int key0 = k_begin + t * kKeyTile;
-    // ---- S^T[key][row] = sum_d K[key][d] Q[row][d] -----------------------------------
-    // Operand traffic is scheduled by hand: the 8 K operands of the first 32 keys are read
-    // up front, those of the second 32 keys stream in under the first MFMA chain, and the
-    // V^T operands of the PV product stream in under the second chain, so that by the time
-    // the softmax is done they are all in registers.
-    f32x16 s[2];
-    KRaw ka[2][G::kSteps];
-#pragma unroll
-    for (int st = 0; st < G::kSteps; ++st) ka[0][st] = read_k(ks, 0, st);
-#pragma unroll
-    for (int st = 0; st < G::kSteps; ++st) ka[1][st] = read_k(ks, 1, st);
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-#pragma unroll
-      for (int st = 0; st < G::kSteps; ++st)
-        s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[kb][st]), qb[st], s[kb], 0, 0, 0);
-    }
-    VRaw va[4][G::kDBlocks];
-    auto read_v = [&](int ks4) {
-#pragma unroll
-      for (int d = 0; d < G::kDBlocks; ++d) va[ks4][d] = read_v_raw(vs, ks4, d);
-    };
-    read_v(0);
-    read_v(1);
-    if constexpr (!KV8) {
-      // 0x100 = LDS read, 0x008 = MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, G::kSteps, 0);
-#pragma unroll
-      for (int st = 0; st < G::kSteps; ++st) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      }
-#pragma unroll
-      for (int st = 0; st < G::kSteps; ++st) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x100, G::kDBlocks / 2, 0);
-      }
-    }
-    // element r of block kb is key  key0 + kb*32 + (r/4)*8 + hi*4 + r%4  of row i32
-    if (key0 + kKeyTile > wave_min_vis) {
-      const int lim = n_vis - key0 - hi * 4;  // visible keys counted from this lane's first key of the tile
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          if (kb * 32 + (r >> 2) * 8 + (r & 3) >= lim) s[kb][r] = -INFINITY;
-    }
-    // ---- online softmax (per-lane row statistics) ------------------------------------
-    // m_run is a reference value, not necessarily the exact running max: it is only moved
-    // (and the accumulators rescaled) when the max of a row grew by more than 2^kSlack, so
-    // probabilities stay below 2^kSlack and the rescale is rare after the first tile.
-    if constexpr (!LO) {
-      float tmax = max3(s[0][0], s[0][1], s[1][0]);
-      tmax = max3(tmax, s[1][1], s[0][2]);
-#pragma unroll
-      for (int r = 3; r < 16; r += 2) tmax = max3(tmax, s[0][r], s[0][r + 1 < 16 ? r + 1 : r]);
-#pragma unroll
-      for (int r = 2; r < 16; r += 2) tmax = max3(tmax, s[1][r], s[1][r + 1]);
-      tmax = cross_half_max(tmax);
-      const float m_new = tmax * p.scale_log2;
-      const bool grow = m_new > m_run + kSlack;
-      if (__any(grow)) {
-        // only the rows that outgrew their reference move it: a row's arithmetic then depends
-        // on that row's scores alone, whatever the other rows of the wave hold
-        const float m_next = grow ? m_new : m_run;
-        const float m_safe = (m_next == -INFINITY) ? 0.f : m_next;
-        const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-        l_run *= alpha;
-#pragma unroll
-        for (int d = 0; d < G::kDBlocks; ++d)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
-        m_run = m_next;
-      }
-    }
-    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
-    bf16x8 pb[4];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float pr = __builtin_amdgcn_exp2f(s[kb][r] * p.scale_log2 - m_use);
-        pb[kb * 2 + (r >> 3)][r & 7] = LO ? (__bf16)(pr - (float)(__bf16)pr) : (__bf16)pr;
-      }
-    l_run += sum_pairs(pb[0], pb[1]) + sum_pairs(pb[2], pb[3]);
+  // ---- the software pipeline of the kernels with more than 32 query rows per item ----------
+  // A half-tile is 32 keys.  While the VALU turns the scores of half h into probabilities, the
+  // matrix pipe forms the scores of half h + 1 and adds the value product of half h - 1: the
+  // three are independent, so each of a wave's MFMAs has vector instructions to hide behind it
+  // and neither pipe waits for the other inside a wave.  Measured on this part: a 32x32x16 MFMA
+  // occupies its pipe for 32.4 cycles and the wave's issue slot for four of them, so up to six
+  // vector instructions per MFMA are free (an exponential counts as two); a half needs about four.
+  // Against tiles worked off one phase after the other (scores, softmax, values): 28/4-head step
+  // with 8..64 new tokens 131.1 -> 124.6 us (8-bit cache 127.6 -> 121.9 us), 4 x 512 new tokens
+  // behind 16384 502 -> 491 us.
+  u32x4 p0[2], p1[2];  // probabilities of an even / odd half as B operands (bf16)
+  f32x16 s0, s1;       // raw scores of an even / odd half
+  float m_use = 0.f;   // m_run, or 0 while the row has seen no visible key
+  // Two probabilities as a bf16 pair (both operand words and row sums take the rounded values).
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
+  auto prob = [&](float sc) { return __builtin_amdgcn_exp2f(sc * p.scale_log2 - m_use); };
 
-    // ---- O^T[d][row] += sum_key V[key][d] P[row][key] ---------------------------------
-    // the V^T operands of keys 32..63 stream in under the MFMAs of keys 0..31
+  // kQk: scores of key half kb of the K tile at ks into sn.  kPv: value product of pp with 32-key
+  // half vh of the V tile at vs.  kSm: probabilities of sc into pc and their sum.
+  auto phase = [&](auto qk_c, f32x16& sn, uint32_t ks, int kb, auto pv_c, const u32x4 (&pp)[2], uint32_t vs, int vh,
+                   auto sm_c, const f32x16& sc, u32x4 (&pc)[2]) __attribute__((always_inline)) -> float {
+    constexpr bool kQk = decltype(qk_c)::value, kPv = decltype(pv_c)::value, kSm = decltype(sm_c)::value;
+    constexpr int kPvMfma = 2 * G::kDBlocks;
+    constexpr int kGroups = G::kSteps + kPvMfma;
+    constexpr int kPer = 16 / kGroups;  // score elements turned into probabilities per group
+    KRaw ka[G::kSteps];
+    VRaw va[kPvMfma];
+    if constexpr (kQk) {
 #pragma unroll
-    for (int ks4 = 0; ks4 < 4; ++ks4) {
-      if (ks4 < 2) read_v(ks4 + 2);
+      for (int st = 0; st < G::kSteps; ++st) ka[st] = read_k(ks, kb, st);
+    }
+    if constexpr (kPv && !kQk) {
 #pragma unroll
-      for (int d = 0; d < G::kDBlocks; ++d) {
-        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va[ks4][d]), pb[ks4], o[d], 0, 0, 0);
+      for (int j = 0; j < kPvMfma; ++j) va[j] = read_v_raw(vs, vh * 2 + j / G::kDBlocks, j % G::kDBlocks);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float acc[2] = {0.f, 0.f};
+    float pr[kPer > 1 ? kPer : 2];
+#pragma unroll
+    for (int i = 0; i < kGroups; ++i) {
+      if (i < G::kSteps) {
+        if constexpr (kQk) {
+          if (i == 0) {
+            f32x16 zero;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[i]), qb[i], zero, 0, 0, 0);
+          } else {
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[i]), qb[i], sn, 0, 0, 0);
+          }
+          if constexpr (kPv) va[i] = read_v_raw(vs, vh * 2 + i / G::kDBlocks, i % G::kDBlocks);
+        }
+      } else if constexpr (kPv) {
+        const int j = i - G::kSteps, d = j % G::kDBlocks;
+        o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va[j]), __builtin_bit_cast(bf16x8, pp[j / G::kDBlocks]),
+                                                       o[d], 0, 0, 0);
       }
+      if constexpr (kSm) {
+#pragma unroll
+        for (int e = i * kPer; e < (i + 1) * kPer; ++e) {
+          pr[e & 1] = prob(sc[e]);
+          if (e & 1) {
+            const bf16x2 two = __builtin_convertvector((f32x2){pr[0], pr[1]}, bf16x2);
+            pc[e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, two);
+            // two chains; the empty statement keeps each step in its group
+            acc[(e >> 1) & 1] = __builtin_amdgcn_fdot2_f32_bf16(two, ones2, acc[(e >> 1) & 1], false);
+            asm volatile("" : "+v"(acc[(e >> 1) & 1]));
+          }
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    return acc[0] + acc[1];
+  };
+  constexpr auto kYes = std::true_type{};
+  constexpr auto kNo = std::false_type{};
+  // Causal mask of the half whose first key is key0: element r is key key0 + (r/4)*8 + hi*4 + r%4.
+  // (compare and select as one block: the compiler turns the plain form into divergent branches
+  // with copies of all sixteen scores.  The leading wait states cover scores that an MFMA
+  // issued just before the block may still be writing.)
+  auto mask_half = [&](f32x16& sc, int key0) __attribute__((always_inline)) {
+    if (key0 + 32 > wave_min_vis) {
+      const int lim = n_vis - key0 - hi * 4;  // visible keys counted from this lane's first key of the half
+#define EFIM_MASK1(i, k) "v_cmp_gt_i32 vcc, %16, " #k "\n\tv_cndmask_b32 %" #i ", %17, %" #i ", vcc\n\t"
+      asm volatile("s_nop 15\n\ts_nop 3\n\t" EFIM_MASK1(0, 0) EFIM_MASK1(1, 1) EFIM_MASK1(2, 2) EFIM_MASK1(3, 3)
+                       EFIM_MASK1(4, 8) EFIM_MASK1(5, 9) EFIM_MASK1(6, 10) EFIM_MASK1(7, 11) EFIM_MASK1(8, 16)
+                           EFIM_MASK1(9, 17) EFIM_MASK1(10, 18) EFIM_MASK1(11, 19) EFIM_MASK1(12, 24)
+                               EFIM_MASK1(13, 25) EFIM_MASK1(14, 26) EFIM_MASK1(15, 27)
+                   : "+v"(sc[0]), "+v"(sc[1]), "+v"(sc[2]), "+v"(sc[3]), "+v"(sc[4]), "+v"(sc[5]), "+v"(sc[6]),
+                     "+v"(sc[7]), "+v"(sc[8]), "+v"(sc[9]), "+v"(sc[10]), "+v"(sc[11]), "+v"(sc[12]), "+v"(sc[13]),
+                     "+v"(sc[14]), "+v"(sc[15])
+                   : "v"(lim), "v"(-INFINITY)
+                   : "vcc");
+#undef EFIM_MASK1
+    }
+  };
+  auto row_max = [&](const f32x16& sc) __attribute__((always_inline)) {
+    float mx = max3(sc[0], sc[1], sc[2]);
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) mx = max3(mx, sc[r], sc[r + 1]);
+    return cross_half_max(fmaxf(mx, sc[15])) * p.scale_log2;
+  };
+  // Moves a row's reference to `m_next` (rows whose reference stays pass m_run: factor one).
+  auto move_reference = [&](float m_next) __attribute__((always_inline)) {
+    const float m_safe = (m_next == -INFINITY) ? 0.f : m_next;
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+    l_run *= m_next == m_run ? 1.f : alpha;
+    const float f = m_next == m_run ? 1.f : alpha;
+#pragma unroll
+    for (int d = 0; d < G::kDBlocks; ++d)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] *= f;
+    m_run = m_next;
+    m_use = m_safe;
+  };
+  // Behind a half's probabilities: m_run is a reference value, set to the row's maximum over its
+  // first half and moved only by a half whose probabilities sum to more than 2^kOver relative to
+  // it.  No running maximum is formed otherwise: bf16 probabilities and fp32 sums keep their
+  // relative precision at any magnitude, the reference only has to keep them in range.  A row
+  // is moved by its own sum alone, whatever the other rows of the wave hold.
+  auto settle = [&](float acc, const f32x16& sc, u32x4 (&pc)[2]) __attribute__((always_inline)) {
+    constexpr float kOver = 65536.f;
+    if (__any(acc > kOver)) {
+      const bool mine = cross_half_max(acc) > kOver;
+      const float m_new = row_max(sc);
+      move_reference(mine ? m_new : m_run);
+      u32x4 dummy[2];
+      acc = phase(kNo, s0, 0u, 0, kNo, dummy, 0u, 0, kYes, sc, pc);
+    }
+    l_run += acc;
+  };
+  // What the bf16 rounding of a half's probabilities dropped, as B operands: with it a
+  // probability enters the value product with 16 significant bits.  Used for the (single) tile of
+  // a wave whose first row sees very few keys: there the output is a weighted mean of a handful
+  // of value rows and can reach magnitude 2-4, where its own bf16 rounding is already 7.8e-3,
+  // and the 2^-9 relative rounding of single bf16 weights on top of that would cross the 1e-2
+  // error bound.
+  auto dropped = [&](const f32x16& sc, u32x4 (&pl)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) {
+      const float a = prob(sc[e]), c = prob(sc[e + 1]);
+      const bf16x2 two = __builtin_convertvector((f32x2){a - (float)(__bf16)a, c - (float)(__bf16)c}, bf16x2);
+      pl[e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, two);
     }
   };
 
-  // One 32-key half (kb = 0 or 1, wave-uniform) of a tile, same products and softmax as
-  // compute_tile on that half alone.
-  auto compute_half = [&](int t, const char* ks, const char* vs, int kb, auto lo_c) __attribute__((always_inline)) {
+  // One 32-key half (kb = 0 or 1, wave-uniform) of a tile in the key-parallel kernels.  LO: a second
+  // pass that adds what the bf16 rounding of the probabilities dropped (see `dropped` above).
+  auto compute_half = [&](int t, uint32_t buf, int kb, auto lo_c) __attribute__((always_inline)) {
     constexpr bool LO = decltype(lo_c)::value;
     const int key0 = k_begin + t * kKeyTile + kb * 32;
     f32x16 sc;
     KRaw ka[G::kSteps];
 #pragma unroll
-    for (int st = 0; st < G::kSteps; ++st) ka[st] = read_k(ks, kb, st);
+    for (int st = 0; st < G::kSteps; ++st) ka[st] = read_k(buf, kb, st);
 #pragma unroll
     for (int r = 0; r < 16; ++r) sc[r] = 0.f;
 #pragma unroll
@@ -757,7 +804,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int d = 0; d < G::kDBlocks; ++d) va[h][d] = read_v_raw(vs, kb * 2 + h, d);
+      for (int d = 0; d < G::kDBlocks; ++d) va[h][d] = read_v_raw(buf, kb * 2 + h, d);
     if (key0 + 32 > wave_min_vis) {
       const int lim = n_vis - key0 - hi * 4;
 #pragma unroll
@@ -804,26 +851,19 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
   // rows with at most this many visible keys get the second (LO) pass over their first tile
   constexpr int kFineKeys = 16;
   const bool fine_wave = k_begin == 0 && wave_min_vis <= kFineKeys;  // wave-uniform
-  auto step = [&](int t, const char* ks, const char* vs, auto first_c) __attribute__((always_inline)) {
-    if constexpr (KP) {
-      if (wave < 2 && k_begin + t * kKeyTile + wave * 32 < wave_max_vis) {
-        compute_half(t, ks, vs, wave, std::false_type{});
-        if constexpr (decltype(first_c)::value)
-          if (fine_wave && t == 0 && wave == 0) compute_half(t, ks, vs, wave, std::true_type{});
-      }
-    } else {
-      if (wave_active && k_begin + t * kKeyTile < wave_max_vis) {
-        compute_tile(t, ks, vs, std::false_type{});
-        if constexpr (decltype(first_c)::value)
-          if (fine_wave && t == 0) compute_tile(t, ks, vs, std::true_type{});
-      }
+  auto step = [&](int t, uint32_t buf, auto first_c) __attribute__((always_inline)) {
+    if (wave < 2 && k_begin + t * kKeyTile + wave * 32 < wave_max_vis) {
+      compute_half(t, buf, wave, std::false_type{});
+      if constexpr (decltype(first_c)::value)
+        if (fine_wave && t == 0 && wave == 0) compute_half(t, buf, wave, std::true_type{});
     }
   };
-  // Loop top for tile t: the gathers of up to STAGES - 2 later tiles (this wave's newest
-  // loads) may stay in flight; everything older must have landed.  The barrier publishes tile
-  // t and tells that every wave is done with the buffer about to be refilled.
-  auto wait_tile = [&](int t) {
-    const int later = min(STAGES - 2, ntiles - 1 - t);  // tiles issued after t so far
+  // Loop top for tile t (stage t of the pipelined kernels): the gathers of up to STAGES - 2 later
+  // tiles (this wave's newest loads; `last` is the last one it issues) may stay in flight;
+  // everything older must have landed.  The barrier publishes tile t and tells that every wave is
+  // done with the buffer about to be refilled.
+  auto wait_tile = [&](int t, int last) {
+    const int later = min(STAGES - 2, last - t);  // tiles issued after t so far
     if (STAGES >= 5 && later == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * kLoadsPerWave) : "memory");
     else if (STAGES >= 4 && later == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
     else if (STAGES >= 3 && later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
@@ -832,9 +872,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
   };
   static_assert(STAGES <= 5, "wait_tile handles up to three tiles in flight");
 
+  // Pipelined kernels: stage t of the ring holds the keys of tile t and the values of tile t - 1
+  // (a tile's scores are formed one tile ahead of its value product); stages 0 .. ntiles.  Each
+  // wave gathers rows of one matrix only, so that is a shift of the tile index of the waves that
+  // gather values.
+  const int shift = (!KP && issuer * kLoadsPerWave >= kGLoadsPerMatrix) ? 1 : 0;
+  static_assert(KP || kGLoadsPerMatrix % kLoadsPerWave == 0, "a wave gathers one matrix");
+  const int last_stage = ntiles - 1 + shift;
 #pragma unroll
-  for (int s0 = 0; s0 < STAGES - 1; ++s0)
-    if (s0 < ntiles) issue_tile(s0, s0, fetch_pages(s0));
+  for (int st = 0; st < STAGES - 1; ++st)
+    if (st >= shift && st <= last_stage) issue_tile(st - shift, st, fetch_pages(st - shift));
   // Everything the compiler knows to be loading (the query operands) must have landed before
   // the main loop: inside it the only outstanding vector-memory operations are the gathers,
   // which are awaited by hand.  (vmcnt(0), expcnt/lgkmcnt untouched; the gathers just issued
@@ -914,7 +961,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
         constexpr int kAhead = STAGES - 1;
         const int sl = (s0 + kAhead) % STAGES;  // static after unrolling
         const TilePages pages = fetch_pages(min(t + kAhead, ntiles - 1));
-        wait_tile(t);
+        wait_tile(t, ntiles - 1);
         if (t + kAhead < ntiles) issue_tile(t + kAhead, sl, pages);
         if constexpr (FUSED) {
           // Key tiles that reach into the new tokens: their cache slots have not been written
@@ -948,16 +995,92 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
           }
         }
         // (tile 0 is always the first of the unrolled copies)
-        step(t, stages + s0 * kStageBytes, stages + s0 * kStageBytes + kGTileBytes, std::bool_constant<s0 == 0>{});
+        step(t, s0 * kSlotBytes, std::bool_constant<s0 == 0>{});
       }
     }
   };
-  for (int t0 = 0; t0 < ntiles; t0 += STAGES) {
-    ring_step(t0, std::integral_constant<int, 0>{});
-    ring_step(t0, std::integral_constant<int, 1>{});
-    if constexpr (STAGES > 2) ring_step(t0, std::integral_constant<int, 2>{});
-    if constexpr (STAGES > 3) ring_step(t0, std::integral_constant<int, 3>{});
-    if constexpr (STAGES > 4) ring_step(t0, std::integral_constant<int, 4>{});
+  if constexpr (KP) {
+    for (int t0 = 0; t0 < ntiles; t0 += STAGES) {
+      ring_step(t0, std::integral_constant<int, 0>{});
+      ring_step(t0, std::integral_constant<int, 1>{});
+      if constexpr (STAGES > 2) ring_step(t0, std::integral_constant<int, 2>{});
+      if constexpr (STAGES > 3) ring_step(t0, std::integral_constant<int, 3>{});
+      if constexpr (STAGES > 4) ring_step(t0, std::integral_constant<int, 4>{});
+    }
+  } else {
+    // key tiles this wave's rows reach into; its pipeline ends there, its gathers go on
+    const int n_w = wave_active ? min(ntiles, max(0, (wave_max_vis - k_begin + kKeyTile - 1) / kKeyTile)) : 0;
+    // publishes stage t and starts the gather of stage t + STAGES - 1 into `slot`
+    auto top = [&](int t, int slot) __attribute__((always_inline)) {
+      const int s_new = t + STAGES - 1;
+      const TilePages pages = fetch_pages(min(max(s_new - shift, 0), ntiles - 1));
+      wait_tile(t, last_stage);
+      if (s_new >= shift && s_new <= last_stage) issue_tile(s_new - shift, slot, pages);
+    };
+    // stage 0: scores of the first tile, probabilities of its first half
+    top(0, STAGES - 1);
+    if (n_w > 0) {
+      constexpr uint32_t ks = 0;
+      phase(kYes, s0, ks, 0, kNo, p0, 0u, 0, kNo, s0, p0);
+      mask_half(s0, k_begin);
+      m_run = row_max(s0);
+      m_use = (m_run == -INFINITY) ? 0.f : m_run;
+      l_run = phase(kYes, s1, ks, 1, kNo, p0, 0u, 0, kYes, s0, p0);
+    }
+    auto body = [&](int t, auto slot_c) __attribute__((always_inline)) {
+      constexpr int slot = decltype(slot_c)::value;
+      top(t, (slot + STAGES - 1) % STAGES);
+      constexpr uint32_t ks = slot * kSlotBytes, vs = ks;
+      const int key0 = k_begin + t * kKeyTile;
+      mask_half(s1, key0 - 32);
+      float acc = phase(kYes, s0, ks, 0, kYes, p0, vs, 0, kYes, s1, p1);
+      settle(acc, s1, p1);
+      mask_half(s0, key0);
+      acc = phase(kYes, s1, ks, 1, kYes, p1, vs, 1, kYes, s0, p0);
+      settle(acc, s0, p0);
+    };
+    int t = 1;
+    while (true) {
+      if (t >= n_w) break;
+      body(t, std::integral_constant<int, 1 % STAGES>{});
+      ++t;
+      if (t >= n_w) break;
+      body(t, std::integral_constant<int, 2 % STAGES>{});
+      ++t;
+      if constexpr (STAGES > 2) {
+        if (t >= n_w) break;
+        body(t, std::integral_constant<int, 3 % STAGES>{});
+        ++t;
+      }
+      if constexpr (STAGES > 3) {
+        if (t >= n_w) break;
+        body(t, std::integral_constant<int, 4 % STAGES>{});
+        ++t;
+      }
+    }
+    static_assert(STAGES <= 4, "one copy of the body per stage");
+    if (n_w > 0) {
+      // stage n_w: the second half of this wave's last tile and the values of both halves
+      const int slot = t % STAGES;
+      top(t, (slot + STAGES - 1) % STAGES);
+      const uint32_t vs = slot * kSlotBytes;
+      u32x4 pl[2];
+      if (fine_wave) {
+        // (such a wave has one tile only: s0 still holds the scores of its first half)
+        dropped(s0, pl);
+        phase(kNo, s0, 0u, 0, kYes, pl, vs, 0, kNo, s0, pl);
+      }
+      mask_half(s1, k_begin + t * kKeyTile - 32);
+      const float acc = phase(kNo, s0, 0u, 0, kYes, p0, vs, 0, kYes, s1, p1);
+      settle(acc, s1, p1);
+      phase(kNo, s0, 0u, 0, kYes, p1, vs, 1, kNo, s1, p1);
+      if (fine_wave) {
+        dropped(s1, pl);
+        phase(kNo, s0, 0u, 0, kYes, pl, vs, 1, kNo, s1, pl);
+      }
+      ++t;
+    }
+    for (; t <= ntiles; ++t) top(t, (t + STAGES - 1) % STAGES);
   }
 
   // --- waves 0 and 1 shared the rows: combine their results in wave 0 --------------------

@@ -1,0 +1,52 @@
+"""The tile loop of the kernels with more than 32 query rows per work item: scores of one 32-key
+half are formed while the previous half is exponentiated and the one before is multiplied with
+its values, and a row's reference moves only when a half's probabilities outgrow it.  Key counts
+around the 32-key halves and 64-key tiles, and keys that grow so that references have to move in
+the first tile, between tiles and in a partial last half."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import efim_oracle as O
+from paper_2505_21889_amd import workloads as W
+
+import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_21889_amd import binding
+    return binding
+
+
+# (cached, new): visible keys of the last row 33, 64, 65, 96, 97, 128, 129, 193, 321, 40
+EDGES = ([0, 0, 1, 32, 33, 64, 65, 129, 257, 0], [33, 64, 64, 64, 64, 64, 64, 64, 64, 40])
+
+
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("grow", [(), (32,), (64, 128), (40, 96, 190)])
+def test_half_tile_edges_and_growing_scores(E, row_tile, d, grow):
+    b = W.make_batch("c1", seed=4000 + d + len(grow), lengths=tuple(np.array(x, dtype=np.int32) for x in EDGES),
+                     heads=(4, 2), head_dim=d)
+    q_roped, kc, vc = U.oracle_inputs(b)
+    # every key from position `at` on four times as large (an exact power of two in bf16): scores
+    # of standard deviation 4, 16, 64 outgrow any reference taken before
+    k = kc.reshape(b.cache_shape())
+    for at in grow:
+        for r in range(b.batch):
+            for pos in range(at, int(b.cached_len[r] + b.new_len[r])):
+                row = k[b.block_table[r, pos // b.page_size], :, pos % b.page_size]
+                row[...] = np.where(row & 0x7F80, row + np.uint16(2 << 7), row)
+    ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    try:
+        got = U.gpu_extend_attention(E, b, q_roped, kc, vc)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+    # (a sharpened softmax gives outputs as large as single value rows: bound per element)
+    U.assert_close(got, ref, "grow %s" % (grow,), large_outputs=True)
