@@ -777,12 +777,14 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
   // of value rows and can reach magnitude 2-4, where its own bf16 rounding is already 7.8e-3,
   // and the 2^-9 relative rounding of single bf16 weights on top of that would cross the 1e-2
   // error bound.
+  // They go into the row sum as well: the normaliser is the sum of the weights the product uses.
   auto dropped = [&](const f32x16& sc, u32x4 (&pl)[2]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
       const float a = prob(sc[e]), c = prob(sc[e + 1]);
       const bf16x2 two = __builtin_convertvector((f32x2){a - (float)(__bf16)a, c - (float)(__bf16)c}, bf16x2);
       pl[e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, two);
+      l_run = __builtin_amdgcn_fdot2_f32_bf16(two, ones2, l_run, false);
     }
   };
 
