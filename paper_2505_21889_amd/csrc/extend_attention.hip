@@ -488,34 +488,47 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
     // (not in the eight-wave key-parallel kernel over bf16 caches: measured 1.5-2.5 % slower there
     // -- that kernel is bound by HBM alone, and its loads do better spaced out)
     constexpr bool kGroupedIssue = !(KP && WAVES == 8 && !KV8);
+    // The key-parallel kernel of the plain call takes the last tile of a range the same way: through
+    // the general path below it waits for a page lookup in front of each load, one behind the
+    // other (one request of 256 + 32 tokens, 4 heads: 7.7 -> 7.2 us).  The other kernels have
+    // no registers for it (the decode step spilled: 13.3 -> 13.7 us) or longer ranges.
+    constexpr bool kGroupedLast = KP && !FUSED;
     if constexpr (kGroupedIssue && kGKeysPerLoad <= kMinPageSize && kGLoadsPerMatrix % kLoadsPerWave == 0) {
-      if (full_tile && offsets_fit_32) {
-        // Every row lies inside the key range and a load never spans two pages: page, head and
-        // first row make a wave-uniform base (scalar registers), the lane adds its row and
-        // (swizzled) chunk.  This wave's loads are consecutive rows of ONE matrix, so the base
-        // is looked up and multiplied out only where a load starts a new page; inside a page
-        // the next load is 1 KB further on.
+      if ((full_tile || kGroupedLast) && offsets_fit_32) {
+        // A load never spans two pages: page, head and first row make a wave-uniform base (scalar
+        // registers), the lane adds its row and (swizzled) chunk.  This wave's loads are
+        // consecutive rows of ONE matrix, so the base is looked up and multiplied out only where
+        // a load starts a new page; inside a page the next load is 1 KB further on.
         const int load0 = issuer * kLoadsPerWave;
         const bool is_v = load0 >= kGLoadsPerMatrix;  // wave-uniform
         const int idx0 = is_v ? load0 - kGLoadsPerMatrix : load0;
         const char* mat = is_v ? vc : kc;
         const uint32_t buf = (is_v ? vbuf : kbuf) + idx0 * 1024;
         // GS loads (GS KB of consecutive rows inside one page) at a time: one page lookup, one
-        // base, one M0
-        auto grouped = [&](auto gs_c) {
+        // base, one M0.  PART: rows past the key range take the range's last row instead; a group
+        // that lies past it altogether reads the group which holds that row.  (The offset field
+        // moves the global address along with the LDS address, so the lane offsets of such rows
+        // go backwards: the base lies kBias lower to keep them unsigned.)
+        auto grouped = [&](auto gs_c, auto part_c) {
           constexpr int GS = decltype(gs_c)::value;
+          constexpr bool PART = decltype(part_c)::value;
+          constexpr int kBias = PART ? (GS - 1) * 1024 : 0;
+          const int last_row = k_end - 1 - key0;
 #pragma unroll
           for (int j = 0; j < kLoadsPerWave; j += GS) {
-            const int row0 = (idx0 + j) * kGKeysPerLoad;
-            const uint32_t in_page = (uint32_t)(key0 + row0) & (uint32_t)page_mask;
+            int row0 = (idx0 + j) * kGKeysPerLoad;
             const uint32_t page = GS == 4 ? pages.id[j / 4] : page_of(first_off + t * kKeyTile + row0);
-            const uint64_t gbase = (uint64_t)page * (uint32_t)page_bytes + (uint32_t)head_bytes + in_page * kGRowBytes;
+            if constexpr (PART) row0 = min(row0, last_row & ~(GS * kGKeysPerLoad - 1));
+            const uint32_t in_page = (uint32_t)(key0 + row0) & (uint32_t)page_mask;
+            const uint64_t gbase =
+                (uint64_t)page * (uint32_t)page_bytes + (uint32_t)head_bytes + in_page * kGRowBytes - kBias;
             uint32_t off[GS];
 #pragma unroll
             for (int q = 0; q < GS; ++q) {
-              const int tile_row = row0 + q * kGKeysPerLoad + g_key;
+              const int tile_row = (idx0 + j + q) * kGKeysPerLoad + g_key;
               const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? G::vswz(tile_row) : G::kswz(tile_row));
-              off[q] = (uint32_t)(g_key * kGRowBytes + ((g_pc ^ swz) << 4));
+              const int src = PART ? (min(tile_row, last_row) - row0) * kGRowBytes + kBias - q * 1024 : g_key * kGRowBytes;
+              off[q] = (uint32_t)(src + ((g_pc ^ swz) << 4));
             }
             if constexpr (GS == 4) load_to_lds_4x16(mat + gbase, off[0], off[1], off[2], off[3], buf + j * 1024);
             else load_to_lds_2x16(mat + gbase, off[0], off[1], buf + j * 1024);
@@ -523,32 +536,36 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
         };
         if constexpr (kLoadsPerWave % 4 == 0) {
           if (page_loads >= 4) {
-            grouped(std::integral_constant<int, 4>{});
+            if (!kGroupedLast || full_tile) grouped(std::integral_constant<int, 4>{}, std::false_type{});
+            else if constexpr (kGroupedLast) grouped(std::integral_constant<int, 4>{}, std::true_type{});
             return;
           }
         }
         if constexpr (kLoadsPerWave % 2 == 0) {
           if (page_loads >= 2) {
-            grouped(std::integral_constant<int, 2>{});
+            if (!kGroupedLast || full_tile) grouped(std::integral_constant<int, 2>{}, std::false_type{});
+            else if constexpr (kGroupedLast) grouped(std::integral_constant<int, 2>{}, std::true_type{});
             return;
           }
         }
-        uint64_t base = 0;
+        if (!kGroupedLast || full_tile) {
+          uint64_t base = 0;
 #pragma unroll
-        for (int j = 0; j < kLoadsPerWave; ++j) {
-          const int row0 = (idx0 + j) * kGKeysPerLoad;  // first tile row of this load
-          const int tile_row = row0 + g_key;
-          const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? G::vswz(tile_row) : G::kswz(tile_row));
-          const uint32_t in_page = (uint32_t)(key0 + row0) & (uint32_t)page_mask;
-          if (j == 0 || in_page == 0) {
-            const uint32_t page = page_of(first_off + t * kKeyTile + row0);
-            base = (uint64_t)page * (uint32_t)page_bytes + (uint32_t)head_bytes + in_page * kGRowBytes;
-          } else {
-            base += 1024;
+          for (int j = 0; j < kLoadsPerWave; ++j) {
+            const int row0 = (idx0 + j) * kGKeysPerLoad;  // first tile row of this load
+            const int tile_row = row0 + g_key;
+            const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? G::vswz(tile_row) : G::kswz(tile_row));
+            const uint32_t in_page = (uint32_t)(key0 + row0) & (uint32_t)page_mask;
+            if (j == 0 || in_page == 0) {
+              const uint32_t page = page_of(first_off + t * kKeyTile + row0);
+              base = (uint64_t)page * (uint32_t)page_bytes + (uint32_t)head_bytes + in_page * kGRowBytes;
+            } else {
+              base += 1024;
+            }
+            load_to_lds_16(mat + base, (uint32_t)(g_key * kGRowBytes + ((g_pc ^ swz) << 4)), buf + j * 1024);
           }
-          load_to_lds_16(mat + base, (uint32_t)(g_key * kGRowBytes + ((g_pc ^ swz) << 4)), buf + j * 1024);
+          return;
         }
-        return;
       }
     }
     // (rolled: this path serves the last tile of a range and a few rare layouts, and is instantiated

@@ -70,3 +70,19 @@ def test_normaliser_is_the_sum_of_the_weights_used(E, row_tile, heads, d):
     finally:
         E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
     assert np.all(got == 0x4040)
+
+
+@pytest.mark.parametrize("page", [8, 16, 32, 64, 256])
+@pytest.mark.parametrize("d", [64, 128])
+def test_last_tile_of_few_rows_on_every_page_size(E, page, d):
+    """At most 32 query rows: the last key tile of the range is gathered in groups of loads whose
+    rows past the range repeat its last row.  Last tiles of 1 .. 64 keys; cache slots behind a
+    request's end hold NaN patterns."""
+    new = [1, 2, 3, 7, 8, 5, 3, 8, 6, 1, 8, 4, 8]
+    ends = [1, 2, 8, 9, 15, 16, 17, 31, 33, 47, 48, 63, 64]
+    cached = [64 * (i % 3) + e - n if 64 * (i % 3) + e >= n else 0 for i, (e, n) in enumerate(zip(ends, new))]
+    b = W.make_batch("c1", seed=4200 + d + page, heads=(4, 2), head_dim=d, page_size=page,
+                     lengths=(np.array(cached, dtype=np.int32), np.array(new, dtype=np.int32)))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
+    U.assert_close(U.gpu_extend_attention(E, b, q_roped, kc, vc), ref, "page %d" % page, large_outputs=True)
