@@ -227,24 +227,28 @@ __device__ __forceinline__ void load_coherent(const float* at, float* a, float* 
 // Combines the partial results of a split key range: with M = max_s m_s and
 // w_s = 2^(m_s - M):  out = sum_s w_s O_s / sum_s w_s l_s, splits taken in index order
 // (O_s = a_s h_s, h_s the stored binary16 row).
-// nthreads threads (thread index t) share rows [row_lo, row_hi) of the tile, D/4 threads per
-// row.  The splits are taken eight at a time with all their loads issued together (one memory
-// round trip per group instead of one per split); a later group rescales the running sums.
+// nthreads threads (thread index t) share rows [row_lo, row_hi) of the tile, D/8 threads per
+// row with 16 bytes of each part.  The splits are taken GROUP at a time with all their loads issued
+// together (one memory round trip per group instead of one per split); a later group rescales
+// the running sums.  GROUP does not change the bits of a result as long as it holds all splits.
 // COHERENT: the partial results were written by other workgroups of the same launch.
-template <int D, bool COHERENT = false>
+template <int D, int GROUP, bool COHERENT>
 __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem& mi, int t,
                                            int nthreads, int row_lo = 0, int row_hi = 1 << 30) {
-  constexpr int VEC = D / 4;  // float4 columns per row
-  constexpr int GROUP = 8;
-  const int dv = (t % VEC) * 4;
+  typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+  constexpr int E4 = COHERENT ? 1 : 2;  // groups of four elements per thread
+  constexpr int VEC = D / (4 * E4);     // threads per row
+  const int dv = (t % VEC) * 4 * E4;
   const int g = p.group;
   row_hi = min(row_hi, mi.row_count);
   for (int lr = row_lo + t / VEC; lr < row_hi; lr += nthreads / VEC) {
     float mx = -INFINITY, l = 0.f;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4 acc[E4];
+#pragma unroll
+    for (int e = 0; e < E4; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int s0 = 0; s0 < mi.nsplit; s0 += GROUP) {
       float m[GROUP], ls[GROUP], amax[GROUP];
-      uint64_t h[GROUP];
+      uint64_t h[GROUP][E4];
 #pragma unroll
       for (int i = 0; i < GROUP; ++i) {
         // splits past the end re-read the last one and get weight zero
@@ -254,13 +258,15 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
           float unused;
           load_coherent(p.part_ml + prow * 4, &m[i], &ls[i]);
           load_coherent(p.part_ml + prow * 4 + 2, &amax[i], &unused);
-          h[i] = load_coherent_bits(p.part_o + prow * D + dv);
+          h[i][0] = load_coherent_bits(p.part_o + prow * D + dv);
         } else {
           const f32x4 mla = *reinterpret_cast<const f32x4*>(p.part_ml + prow * 4);
           m[i] = mla[0];
           ls[i] = mla[1];
           amax[i] = mla[2];
-          h[i] = *reinterpret_cast<const uint64_t*>(p.part_o + prow * D + dv);
+          const u32x4 both = *reinterpret_cast<const u32x4*>(p.part_o + prow * D + dv);
+          h[i][0] = (uint64_t)both[0] | ((uint64_t)both[1] << 32);
+          h[i][E4 - 1] = (uint64_t)both[2] | ((uint64_t)both[3] << 32);
         }
       }
       float gmx = mx;
@@ -269,17 +275,20 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
       if (s0 > 0) {
         const float back = __builtin_amdgcn_exp2f(mx - gmx);
         l *= back;
-        acc *= back;
+#pragma unroll
+        for (int e = 0; e < E4; ++e) acc[e] *= back;
       }
       mx = gmx;
 #pragma unroll
       for (int i = 0; i < GROUP; ++i) {
         const float w = (s0 + i < mi.nsplit) ? __builtin_amdgcn_exp2f(m[i] - mx) : 0.f;
         l += w * ls[i];
-        typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-        const f16x4 hv = __builtin_bit_cast(f16x4, h[i]);
         const float wa = w * amax[i];
-        acc += f32x4{(float)hv[0], (float)hv[1], (float)hv[2], (float)hv[3]} * wa;
+#pragma unroll
+        for (int e = 0; e < E4; ++e) {
+          const f16x4 hv = __builtin_bit_cast(f16x4, h[i][e]);
+          acc[e] += f32x4{(float)hv[0], (float)hv[1], (float)hv[2], (float)hv[3]} * wa;
+        }
       }
     }
     const float inv = p.out_scale / l;
@@ -287,10 +296,16 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
     const int tok = row / g;
     const int hg = row - tok * g;
     uint16_t* dst = p.out + ((int64_t)(mi.row_start + tok) * p.num_q_heads + mi.kv_head * g + hg) * D + dv;
-    bf16x4 o4;
+    u32x2 words[E4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(acc[e] * inv);
-    *reinterpret_cast<u32x2*>(dst) = __builtin_bit_cast(u32x2, o4);
+    for (int e = 0; e < E4; ++e) {
+      bf16x4 o4;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o4[i] = (__bf16)(acc[e][i] * inv);
+      words[e] = __builtin_bit_cast(u32x2, o4);
+    }
+    if constexpr (E4 == 1) *reinterpret_cast<u32x2*>(dst) = words[0];
+    else *reinterpret_cast<u32x4*>(dst) = u32x4{words[0][0], words[0][1], words[1][0], words[1][1]};
   }
 }
 
@@ -1264,20 +1279,26 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
       *s_last = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == mi.nsplit - 1;
     __syncthreads();
     if (*s_last) {
-      merge_rows<D, true>(p, mi, tid, 64 * WAVES);
+      merge_rows<D, 8, true>(p, mi, tid, 64 * WAVES);
       if (tid == 0) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }
 
+// Bound by the latency of two dependent reads (item, partial results) and by the loads it issues:
+// most ranges are cut into two or three parts, so the group of parts read at once follows their
+// number.
 template <int D>
 __global__ __launch_bounds__(256) void merge_kernel(const AttnParams p, const MergeItem* merges) {
-  constexpr int ROWS = 256 / (D / 4);  // rows per workgroup
-  MergeItem mi = merges[blockIdx.x];
+  constexpr int ROWS = 256 / (D / 8);  // rows per workgroup
+  const MergeItem mi = merges[blockIdx.x];
   // this workgroup's slice of the rows
   const int first = blockIdx.y * ROWS;
   if (first >= mi.row_count) return;
-  merge_rows<D>(p, mi, threadIdx.x, 256, first, min(mi.row_count, first + ROWS));
+  const int last = min(mi.row_count, first + ROWS);
+  if (mi.nsplit <= 2) merge_rows<D, 2, false>(p, mi, threadIdx.x, 256, first, last);
+  else if (mi.nsplit <= 4) merge_rows<D, 4, false>(p, mi, threadIdx.x, 256, first, last);
+  else merge_rows<D, 8, false>(p, mi, threadIdx.x, 256, first, last);
 }
 
 }  // namespace
@@ -1369,7 +1390,7 @@ void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, dim3 grid, 
 }
 
 int launch_merge(const efim_batch_t* b, const Plan& plan, const AttnParams& p, hipStream_t stream) {
-  const dim3 mgrid((unsigned)plan.merges.size(), (unsigned)((plan.partial_rows * (b->head_dim / 4) + 255) / 256));
+  const dim3 mgrid((unsigned)plan.merges.size(), (unsigned)((plan.partial_rows * (b->head_dim / 8) + 255) / 256));
   if (b->head_dim == 128) merge_kernel<128><<<mgrid, 256, 0, stream>>>(p, p.merges);
   else merge_kernel<64><<<mgrid, 256, 0, stream>>>(p, p.merges);
   hipError_t e = hipGetLastError();

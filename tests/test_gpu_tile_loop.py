@@ -86,3 +86,20 @@ def test_last_tile_of_few_rows_on_every_page_size(E, page, d):
     q_roped, kc, vc = U.oracle_inputs(b)
     ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
     U.assert_close(U.gpu_extend_attention(E, b, q_roped, kc, vc), ref, "page %d" % page, large_outputs=True)
+
+
+@pytest.mark.parametrize("parts", [2, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("d", [64, 128])
+def test_merge_kernel_for_every_group_of_parts(E, parts, d):
+    """The merge reads two, four or eight parts at once; 20 tokens of two heads are 40 rows per
+    item, past the in-kernel merge, in row blocks of 16 or 32."""
+    b = W.make_batch("c1", seed=4300 + d, heads=(4, 2), head_dim=d,
+                     lengths=(np.array([64 * parts - 20, 64 * parts - 33], dtype=np.int32), np.array([20, 13], dtype=np.int32)))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, 64)
+    try:
+        got = U.gpu_extend_attention(E, b, q_roped, kc, vc)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+    U.assert_close(got, ref, "%d parts" % parts)
