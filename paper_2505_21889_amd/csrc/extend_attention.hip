@@ -508,8 +508,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
     // other (one request of 256 + 32 tokens, 4 heads: 7.7 -> 7.2 us).  The other kernels have
     // no registers for it (the decode step spilled: 13.3 -> 13.7 us) or longer ranges.
     constexpr bool kGroupedLast = KP && !FUSED;
-    if constexpr (kGroupedIssue && kGKeysPerLoad <= kMinPageSize && kGLoadsPerMatrix % kLoadsPerWave == 0) {
-      if ((full_tile || kGroupedLast) && offsets_fit_32) {
+    if constexpr (kGroupedIssue && kGLoadsPerMatrix % kLoadsPerWave == 0) {
+      if ((full_tile || kGroupedLast) && offsets_fit_32 && page_loads >= 1) {
+        // (page_loads is 0 only for 64-byte code rows on pages of 8; on larger pages the wide form
+        // took such a step, 64 requests of 4000..7000 + 1..8 tokens, 32/8 heads, from 113.9 to 94.5 us)
         // A load never spans two pages: page, head and first row make a wave-uniform base (scalar
         // registers), the lane adds its row and (swizzled) chunk.  This wave's loads are
         // consecutive rows of ONE matrix, so the base is looked up and multiplied out only where
@@ -584,8 +586,11 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
       }
     }
     // (rolled: this path serves the last tile of a range and a few rare layouts, and is instantiated
-    // once per stage; unrolled it was most of the kernel's code)
-#pragma unroll 1
+    // once per stage; unrolled it was most of the kernel's code.  Not where a load can span two
+    // pages -- 64-byte code rows on pages of 8: every tile comes here then, and its page lookups
+    // have to go out together.)
+    constexpr int kUnroll = kGKeysPerLoad <= kMinPageSize ? 1 : kLoadsPerWave;
+#pragma unroll kUnroll
     for (int j = 0; j < kLoadsPerWave; ++j) {
       const int load = issuer * kLoadsPerWave + j;            // 0 .. 2*kGLoadsPerMatrix-1
       const bool is_v = load >= kGLoadsPerMatrix;             // wave-uniform

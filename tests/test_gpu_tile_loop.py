@@ -103,3 +103,24 @@ def test_merge_kernel_for_every_group_of_parts(E, parts, d):
     finally:
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
     U.assert_close(got, ref, "%d parts" % parts)
+
+
+@pytest.mark.parametrize("page", [8, 16, 32, 64, 256])
+@pytest.mark.parametrize("new,row_tile", [([1, 2, 3, 7, 8, 5, 16, 4], 0), ([33, 64, 40, 7, 100, 65, 1, 20], 128),
+                                          ([33, 64, 40, 7, 300, 65, 1, 20], 256)])
+def test_code_rows_of_64_bytes_on_every_page_size(E, page, new, row_tile):
+    """8-bit cache with head dim 64: one load takes sixteen rows, a page or several of them -- or two
+    pages of eight, the one layout whose rows are looked up lane by lane.  Full and partial tiles,
+    with few rows per item (first batch) and many."""
+    from test_gpu_fp8 import gpu_attention8, oracle_cache8, oracle_step8
+    cached = [0, 63, 200, 57, 128, 450, 15, 300]
+    b = W.make_batch("c1", seed=4400 + page, heads=(4, 2), head_dim=64, page_size=page,
+                     lengths=(np.array(cached, dtype=np.int32), np.array(new, dtype=np.int32)))
+    k_scale, v_scale = 0.0123, 0.031
+    q_roped, kc, vc, ref = oracle_step8(b, *oracle_cache8(b, k_scale, v_scale), k_scale, v_scale)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    try:
+        got = gpu_attention8(E, b, q_roped, kc, vc, k_scale, v_scale)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+    U.assert_close(got, ref, "page %d" % page)
