@@ -332,8 +332,16 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // take all the rows and one 32-key half of every key tile each, with their own running max and
 // sums, and their partial results are combined through LDS at the end.  In the four-wave
 // kernel the two waves without rows issue all the gathers.
+//
+// Head dim 64, few rows: a few registers less than the compiler takes by itself let two 8-wave (or
+// four 4-wave) workgroups share a compute unit instead of one (or three), without a spill: 64
+// requests of 4000..7000 + 1..8 tokens, 32/8 heads 153.0 -> 136.2 us, 24 requests of 2000..7000 +
+// 4..8 tokens 55.1 -> 52.3 us.  The kernels for many rows spill at that bound (197 -> 304 us).
+constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp) {
+  return d == 64 && kp && !kv8 && (!fused || waves == 8) ? 4 : 2;
+}
 template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP>
-__global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const AttnParams p) {
+__global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP)) void extend_attention_kernel(const AttnParams p) {
   static_assert(KP || !FUSED, "the decode step has at most 32 rows per tile");
   using G = Geometry<D>;
   // geometry of the gather: rows as they lie in the cache
@@ -588,8 +596,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void extend_attention_kernel(const A
     // (rolled: this path serves the last tile of a range and a few rare layouts, and is instantiated
     // once per stage; unrolled it was most of the kernel's code.  Not where a load can span two
     // pages -- 64-byte code rows on pages of 8: every tile comes here then, and its page lookups
-    // have to go out together.)
-    constexpr int kUnroll = kGKeysPerLoad <= kMinPageSize ? 1 : kLoadsPerWave;
+    // have to go out together.  Nor in the eight-wave kernel that takes this path for all tiles.)
+    constexpr int kUnroll = kGroupedIssue && kGKeysPerLoad <= kMinPageSize ? 1 : kLoadsPerWave;
 #pragma unroll kUnroll
     for (int j = 0; j < kLoadsPerWave; ++j) {
       const int load = issuer * kLoadsPerWave + j;            // 0 .. 2*kGLoadsPerMatrix-1
@@ -1371,13 +1379,16 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 }
 
 // few_rows: no work item has more than 32 query rows (always so for the decode step)
+// Four-wave kernels take two stages over bf16 rows, three where a tile is half as large: 8-bit rows,
+// and the short step with head dim 64 (64 requests of 4000..9000 + 8..16 tokens, 4 heads: 102.4 -> 91.5
+// us; the plain call over the same rows is not faster with three).
 template <bool FUSED>
 void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, dim3 grid, const AttnParams& p,
                    hipStream_t stream) {
 #define EFIM_ATTN_LAUNCH2(DD, F8, KP)                                                              \
   do {                                                                                             \
     if (wide) extend_attention_kernel<DD, 8, 3, FUSED, F8, KP><<<grid, 512, 0, stream>>>(p); \
-    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, FUSED, F8, KP><<<grid, 256, 0, stream>>>(p);   \
+    else extend_attention_kernel<DD, 4, F8 || (FUSED && DD == 64) ? 3 : 2, FUSED, F8, KP><<<grid, 256, 0, stream>>>(p); \
   } while (0)
 #define EFIM_ATTN_LAUNCH(DD, F8)                                               \
   do {                                                                         \
