@@ -709,6 +709,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   u32x4 p0[2], p1[2];  // probabilities of an even / odd half as B operands (bf16)
   f32x16 s0, s1;       // raw scores of an even / odd half
   float m_use = 0.f;   // m_run, or 0 while the row has seen no visible key
+  float l_half = 0.f;  // row sum of the first half of the tile whose second half is next
   // Two probabilities as a bf16 pair (both operand words and row sums take the rounded values).
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
@@ -733,7 +734,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       for (int j = 0; j < kPvMfma; ++j) va[j] = read_v_raw(vs, vh * 2 + j / G::kDBlocks, j % G::kDBlocks);
     }
     __builtin_amdgcn_sched_barrier(0);
-    float acc[2] = {0.f, 0.f};
+    float acc = 0.f;
     float pr[kPer > 1 ? kPer : 2];
 #pragma unroll
     for (int i = 0; i < kGroups; ++i) {
@@ -761,15 +762,15 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
           if (e & 1) {
             const bf16x2 two = __builtin_convertvector((f32x2){pr[0], pr[1]}, bf16x2);
             pc[e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, two);
-            // two chains; the empty statement keeps each step in its group
-            acc[(e >> 1) & 1] = __builtin_amdgcn_fdot2_f32_bf16(two, ones2, acc[(e >> 1) & 1], false);
-            asm volatile("" : "+v"(acc[(e >> 1) & 1]));
+            // the order of `sum_pairs`; the empty statement keeps each step in its group
+            acc = __builtin_amdgcn_fdot2_f32_bf16(two, ones2, acc, false);
+            asm volatile("" : "+v"(acc));
           }
         }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    return acc[0] + acc[1];
+    return acc;
   };
   constexpr auto kYes = std::true_type{};
   constexpr auto kNo = std::false_type{};
@@ -793,18 +794,20 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
 #undef EFIM_MASK1
     }
   };
-  auto row_max = [&](const f32x16& sc) __attribute__((always_inline)) {
+  // maximum of a half's scores of this lane's row, in this lane's half of its elements
+  auto half_max = [&](const f32x16& sc) __attribute__((always_inline)) {
     float mx = max3(sc[0], sc[1], sc[2]);
 #pragma unroll
     for (int r = 3; r < 15; r += 2) mx = max3(mx, sc[r], sc[r + 1]);
-    return cross_half_max(fmaxf(mx, sc[15])) * p.scale_log2;
+    return fmaxf(mx, sc[15]);
   };
   // Moves a row's reference to `m_next` (rows whose reference stays pass m_run: factor one).
   auto move_reference = [&](float m_next) __attribute__((always_inline)) {
     const float m_safe = (m_next == -INFINITY) ? 0.f : m_next;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-    l_run *= m_next == m_run ? 1.f : alpha;
     const float f = m_next == m_run ? 1.f : alpha;
+    l_run *= f;
+    l_half *= f;
 #pragma unroll
     for (int d = 0; d < G::kDBlocks; ++d)
 #pragma unroll
@@ -813,20 +816,22 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     m_use = m_safe;
   };
   // Behind a half's probabilities: m_run is a reference value, set to the row's maximum over its
-  // first half and moved only by a half whose probabilities sum to more than 2^kOver relative to
-  // it.  No running maximum is formed otherwise: bf16 probabilities and fp32 sums keep their
-  // relative precision at any magnitude, the reference only has to keep them in range.  A row
-  // is moved by its own sum alone, whatever the other rows of the wave hold.
-  auto settle = [&](float acc, const f32x16& sc, u32x4 (&pc)[2]) __attribute__((always_inline)) {
-    constexpr float kOver = 65536.f;
-    if (__any(acc > kOver)) {
-      const bool mine = cross_half_max(acc) > kOver;
-      const float m_new = row_max(sc);
-      move_reference(mine ? m_new : m_run);
+  // first tile and moved only by a half whose maximum lies more than 2^kSlack above it, so that
+  // probabilities stay below 2^kSlack.  Such a half shows in its sum: no running maximum is formed
+  // otherwise.  The first reference is the maximum over all 64 keys of the tile because that
+  // makes the largest weight of a short row exactly one: with the maximum over 32 keys the error
+  // against 64-bit arithmetic of a step with full misses was 0.7 % larger (relative L2 2.048e-3
+  // against 2.033e-3).  A row is moved by its own scores alone, whatever the other rows of the
+  // wave hold.
+  auto settle = [&](float acc, const f32x16& sc, u32x4 (&pc)[2]) __attribute__((always_inline)) -> float {
+    constexpr float kOver = 256.f;  // 2^kSlack; a sum of rounded probabilities is never below its largest one
+    if (__any(acc >= kOver)) {
+      const float m_new = cross_half_max(half_max(sc)) * p.scale_log2;
+      move_reference(m_new > m_run + kSlack ? m_new : m_run);
       u32x4 dummy[2];
       acc = phase(kNo, s0, 0u, 0, kNo, dummy, 0u, 0, kYes, sc, pc);
     }
-    l_run += acc;
+    return acc;
   };
   // What the bf16 rounding of a half's probabilities dropped, as B operands: with it a
   // probability enters the value product with 16 significant bits.  Used for the (single) tile of
@@ -834,15 +839,18 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // of value rows and can reach magnitude 2-4, where its own bf16 rounding is already 7.8e-3,
   // and the 2^-9 relative rounding of single bf16 weights on top of that would cross the 1e-2
   // error bound.
-  // They go into the row sum as well: the normaliser is the sum of the weights the product uses.
-  auto dropped = [&](const f32x16& sc, u32x4 (&pl)[2]) __attribute__((always_inline)) {
+  // Returns their sum, which goes into the row sum: the normaliser is the sum of the weights the
+  // product uses.
+  auto dropped = [&](const f32x16& sc, u32x4 (&pl)[2]) __attribute__((always_inline)) -> float {
+    float acc = 0.f;
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
       const float a = prob(sc[e]), c = prob(sc[e + 1]);
       const bf16x2 two = __builtin_convertvector((f32x2){a - (float)(__bf16)a, c - (float)(__bf16)c}, bf16x2);
       pl[e >> 3][(e & 7) >> 1] = __builtin_bit_cast(uint32_t, two);
-      l_run = __builtin_amdgcn_fdot2_f32_bf16(two, ones2, l_run, false);
+      acc = __builtin_amdgcn_fdot2_f32_bf16(two, ones2, acc, false);
     }
+    return acc;
   };
 
   // One 32-key half (kb = 0 or 1, wave-uniform) of a tile in the key-parallel kernels.  LO: a second
@@ -1112,10 +1120,12 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     if (n_w > 0) {
       constexpr uint32_t ks = 0;
       phase(kYes, s0, ks, 0, kNo, p0, 0u, 0, kNo, s0, p0);
+      phase(kYes, s1, ks, 1, kNo, p0, 0u, 0, kNo, s0, p0);
       mask_half(s0, k_begin);
-      m_run = row_max(s0);
+      mask_half(s1, k_begin + 32);
+      m_run = cross_half_max(fmaxf(half_max(s0), half_max(s1))) * p.scale_log2;
       m_use = (m_run == -INFINITY) ? 0.f : m_run;
-      l_run = phase(kYes, s1, ks, 1, kNo, p0, 0u, 0, kYes, s0, p0);
+      l_half = phase(kNo, s0, 0u, 0, kNo, p0, 0u, 0, kYes, s0, p0);
     }
     auto body = [&](int t, auto slot_c) __attribute__((always_inline)) {
       constexpr int slot = decltype(slot_c)::value;
@@ -1124,10 +1134,11 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       const int key0 = k_begin + t * kKeyTile;
       mask_half(s1, key0 - 32);
       float acc = phase(kYes, s0, ks, 0, kYes, p0, vs, 0, kYes, s1, p1);
-      settle(acc, s1, p1);
+      acc = settle(acc, s1, p1);
+      l_run += l_half + acc;
       mask_half(s0, key0);
       acc = phase(kYes, s1, ks, 1, kYes, p1, vs, 1, kYes, s0, p0);
-      settle(acc, s0, p0);
+      l_half = settle(acc, s0, p0);
     };
     int t = 1;
     while (true) {
@@ -1154,19 +1165,17 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       const int slot = t % STAGES;
       top(t, (slot + STAGES - 1) % STAGES);
       const uint32_t vs = slot * kSlotBytes;
-      u32x4 pl[2];
-      if (fine_wave) {
-        // (such a wave has one tile only: s0 still holds the scores of its first half)
-        dropped(s0, pl);
-        phase(kNo, s0, 0u, 0, kYes, pl, vs, 0, kNo, s0, pl);
-      }
       mask_half(s1, k_begin + t * kKeyTile - 32);
-      const float acc = phase(kNo, s0, 0u, 0, kYes, p0, vs, 0, kYes, s1, p1);
-      settle(acc, s1, p1);
+      const float acc = settle(phase(kNo, s0, 0u, 0, kYes, p0, vs, 0, kYes, s1, p1), s1, p1);
+      l_run += l_half + acc;
       phase(kNo, s0, 0u, 0, kYes, p1, vs, 1, kNo, s1, p1);
       if (fine_wave) {
-        dropped(s1, pl);
-        phase(kNo, s0, 0u, 0, kYes, pl, vs, 1, kNo, s1, pl);
+        // (such a wave has one tile only: s0 still holds the scores of its first half)
+        u32x4 pl0[2], pl1[2];
+        const float lo0 = dropped(s0, pl0), lo1 = dropped(s1, pl1);
+        l_run += lo0 + lo1;
+        phase(kNo, s0, 0u, 0, kYes, pl0, vs, 0, kNo, s0, pl0);
+        phase(kNo, s0, 0u, 0, kYes, pl1, vs, 1, kNo, s1, pl1);
       }
       ++t;
     }

@@ -124,3 +124,72 @@ def test_code_rows_of_64_bytes_on_every_page_size(E, page, new, row_tile):
     finally:
         E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
     U.assert_close(got, ref, "page %d" % page)
+
+
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("d", [64, 128])
+def test_weights_are_rounded_relative_to_the_first_tiles_maximum(E, row_tile, d):
+    """A weight is bf16(2^(s - m)), m the row's maximum over the first 64 keys of its range (none of
+    these scores outgrows it by 2^8), and an output is the rounded quotient of the fp32 sums.  In 64
+    bits the same definition gives the same bf16 number unless a sum or an exponential falls
+    within its fp32 error of a rounding boundary: about 1e-6 of an element's 2^-8 spacing for the
+    sums, and one weight in 2000 rounded the other way shifts its row by 2^-8 / 64 at most -- under
+    one element in a hundred.  Another reference rounds every weight elsewhere."""
+    b = W.make_batch("c1", seed=4500 + d, heads=(4, 2), head_dim=d,
+                     lengths=(np.array([20, 64, 150, 257], dtype=np.int32), np.array([50, 64, 64, 64], dtype=np.int32)))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, 0)
+    try:
+        got = O.bf16_to_f64(U.gpu_extend_attention(E, b, q_roped, kc, vc))
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+    scale = np.log2(np.e) / np.sqrt(d)
+    differ, at = 0, 0
+    for r in range(b.batch):
+        c, n = int(b.cached_len[r]), int(b.new_len[r])
+        for h in range(4):
+            q = O.bf16_to_f64(q_roped[at:at + n, h])
+            k, v = (O.gather_kv(x.reshape(b.cache_shape()), b.block_table[r], c + n, b.page_size, h // 2) for x in (kc, vc))
+            k, v = (x if x.dtype == np.float64 else O.bf16_to_f64(x) for x in (k, v))
+            s = q @ k.T * scale
+            s[np.arange(c + n)[None, :] > c + np.arange(n)[:, None]] = -np.inf
+            m = s[:, :64].max(axis=1, keepdims=True)
+            assert (s.max(axis=1, keepdims=True) < m + 8).all()
+            w = O.bf16_to_f64(O.f64_to_bf16(np.exp2(s - m)))
+            out = O.bf16_to_f64(O.f64_to_bf16(w @ v / w.sum(axis=1, keepdims=True)))
+            differ += int((out != got[at:at + n, h]).sum())
+        at += n
+    assert differ <= got.size // 100, "%d of %d elements" % (differ, got.size)
+
+
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("d", [64, 128])
+def test_weights_stay_in_range_of_the_largest_values(E, row_tile, d):
+    """Values of 2^115: with weights of at most 2^8 their products stay far inside fp32.  Keys whose
+    scores lie 2^13 and 2^15 above those of all keys before them move the reference instead of
+    getting such a weight."""
+    b = W.make_batch("c1", seed=4600 + d, heads=(4, 2), head_dim=d,
+                     lengths=(np.array([100, 230], dtype=np.int32), np.array([64, 64], dtype=np.int32)))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    q_roped[...] = 0
+    q_roped[..., 0] = 0x3F80  # 1.0
+    k = kc.reshape(b.cache_shape())
+    for r in range(b.batch):
+        total = int(b.cached_len[r] + b.new_len[r])
+        for pos in range(total):
+            grown = {70: 13.0, 77: 13.0, 200: 28.0, 225: 28.0}.get(pos, 0.0)
+            k[b.block_table[r, pos // b.page_size], :, pos % b.page_size, 0] = O.f64_to_bf16(
+                np.array([grown * np.sqrt(d) / np.log2(np.e)]))[0]
+    v = O.bf16_to_f64(vc)
+    vc[...] = np.where(np.isnan(v), vc, O.f64_to_bf16(np.where(np.isnan(v), 0.0, v) * 2.0 ** 115))
+    ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, 0)
+    try:
+        got = U.gpu_extend_attention(E, b, q_roped, kc, vc)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+    U.assert_close(got, ref, large_outputs=True, value_scale=2.0 ** 115)
