@@ -282,12 +282,15 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 #pragma unroll
       for (int i = 0; i < GROUP; ++i) {
         const float w = (s0 + i < mi.nsplit) ? __builtin_amdgcn_exp2f(m[i] - mx) : 0.f;
-        l += w * ls[i];
+        // (explicit: left to itself the compiler fused the rescale into the addition in one of the
+        // two merges, whose results then differed in the last bit past eight parts)
+        l = fmaf(w, ls[i], l);
         const float wa = w * amax[i];
 #pragma unroll
         for (int e = 0; e < E4; ++e) {
           const f16x4 hv = __builtin_bit_cast(f16x4, h[i][e]);
-          acc[e] += f32x4{(float)hv[0], (float)hv[1], (float)hv[2], (float)hv[3]} * wa;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) acc[e][k] = fmaf((float)hv[k], wa, acc[e][k]);
         }
       }
     }

@@ -193,3 +193,24 @@ def test_weights_stay_in_range_of_the_largest_values(E, row_tile, d):
         E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
     U.assert_close(got, ref, large_outputs=True, value_scale=2.0 ** 115)
+
+
+@pytest.mark.parametrize("parts", [9, 12, 17, 33])
+@pytest.mark.parametrize("d", [64, 128])
+def test_merges_of_more_than_eight_parts_agree_to_the_bit(E, parts, d):
+    """Past eight parts the running sums are rescaled between groups: the merge kernel and the merge
+    inside the attention kernel round that product, then add with one rounding."""
+    b = W.make_batch("c1", seed=4700 + d, heads=(32, 8), head_dim=d,
+                     lengths=(np.array([64 * parts - 8, 64 * parts - 40, 64 * parts - 20], dtype=np.int32),
+                              np.array([8, 5, 7], dtype=np.int32)))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    got = []
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, 64)
+    try:
+        for inside in (0, 1):
+            E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, inside)
+            got.append(U.gpu_extend_attention(E, b, q_roped, kc, vc))
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+        E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, -1)
+    assert np.array_equal(got[0], got[1])
