@@ -711,7 +711,10 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // behind 16384 502 -> 491 us.
   u32x4 p0[2], p1[2];  // probabilities of an even / odd half as B operands (bf16)
   f32x16 s0, s1;       // raw scores of an even / odd half
-  float m_use = 0.f;   // m_run, or 0 while the row has seen no visible key
+  // m_run, or while the row has seen no score above minus infinity a value so low that any finite
+  // score makes an infinite weight: its half then takes the path that sets the reference
+  float m_use = 0.f;
+  constexpr float kNoReference = -3.0e38f;
   float l_half = 0.f;  // row sum of the first half of the tile whose second half is next
   // Two probabilities as a bf16 pair (both operand words and row sums take the rounded values).
   typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -806,7 +809,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   };
   // Moves a row's reference to `m_next` (rows whose reference stays pass m_run: factor one).
   auto move_reference = [&](float m_next) __attribute__((always_inline)) {
-    const float m_safe = (m_next == -INFINITY) ? 0.f : m_next;
+    const float m_safe = (m_next == -INFINITY) ? kNoReference : m_next;
     const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
     const float f = m_next == m_run ? 1.f : alpha;
     l_run *= f;
@@ -1127,7 +1130,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       mask_half(s0, k_begin);
       mask_half(s1, k_begin + 32);
       m_run = cross_half_max(fmaxf(half_max(s0), half_max(s1))) * p.scale_log2;
-      m_use = (m_run == -INFINITY) ? 0.f : m_run;
+      m_use = (m_run == -INFINITY) ? kNoReference : m_run;
       l_half = phase(kNo, s0, 0u, 0, kNo, p0, 0u, 0, kYes, s0, p0);
     }
     auto body = [&](int t, auto slot_c) __attribute__((always_inline)) {

@@ -214,3 +214,35 @@ def test_merges_of_more_than_eight_parts_agree_to_the_bit(E, parts, d):
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
         E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, -1)
     assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("row_tile", [0, 128, 256])
+@pytest.mark.parametrize("split", [0, 64, 128])
+@pytest.mark.parametrize("d", [64, 128])
+def test_minus_infinity_scores_in_front_of_low_ones(E, row_tile, split, d):
+    """Cached keys with minus infinity in an element that every query has at one: their scores are
+    minus infinity, weight zero, over 32 .. 150 keys from the first on.  The scores behind lie 400
+    log2 units below zero: relative to any reference but their own they vanish.  Row tile 0 with few
+    rows takes the key-parallel kernel."""
+    new = [5, 8, 3, 16, 12] if row_tile == 0 else [64, 64, 70, 64, 64]
+    first_finite = [32, 40, 64, 100, 150]
+    b = W.make_batch("c1", seed=4800 + d, heads=(4, 2), head_dim=d,
+                     lengths=(np.array([170, 200, 330, 180, 250], dtype=np.int32), np.array(new, dtype=np.int32)))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    q_roped[..., :2] = 0x3F80  # 1.0
+    k = kc.reshape(b.cache_shape())
+    low = O.f64_to_bf16(np.array([-400.0 * np.sqrt(d) / np.log2(np.e)]))[0]
+    for r in range(b.batch):
+        for pos in range(int(b.cached_len[r] + b.new_len[r])):
+            row = k[b.block_table[r, pos // b.page_size], :, pos % b.page_size]
+            row[:, 0] = 0xFF80 if pos < first_finite[r] else 0
+            row[:, 1] = low
+    ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+    try:
+        got = U.gpu_extend_attention(E, b, q_roped, kc, vc)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+    U.assert_close(got, ref)
