@@ -781,23 +781,21 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   constexpr auto kYes = std::true_type{};
   constexpr auto kNo = std::false_type{};
   // Causal mask of the half whose first key is key0: element r is key key0 + (r/4)*8 + hi*4 + r%4.
-  // (compare and select as one block: the compiler turns the plain form into divergent branches
-  // with copies of all sixteen scores.  The leading wait states cover scores that an MFMA
-  // issued just before the block may still be writing.)
+  // Each lane holds one bit per key of the half, and an element takes minus infinity through a bit
+  // select: two vector instructions each and no condition register.  A compare whose result a
+  // select reads has to stand two wait states in front of it on this target; the compiler keeps
+  // that rule for its own instructions (and would turn a plain select here into divergent
+  // branches with copies of all sixteen scores) but not inside inline assembly.
   auto mask_half = [&](f32x16& sc, int key0) __attribute__((always_inline)) {
     if (key0 + 32 > wave_min_vis) {
       const int lim = n_vis - key0 - hi * 4;  // visible keys counted from this lane's first key of the half
-#define EFIM_MASK1(i, k) "v_cmp_gt_i32 vcc, %16, " #k "\n\tv_cndmask_b32 %" #i ", %17, %" #i ", vcc\n\t"
-      asm volatile("s_nop 15\n\ts_nop 3\n\t" EFIM_MASK1(0, 0) EFIM_MASK1(1, 1) EFIM_MASK1(2, 2) EFIM_MASK1(3, 3)
-                       EFIM_MASK1(4, 8) EFIM_MASK1(5, 9) EFIM_MASK1(6, 10) EFIM_MASK1(7, 11) EFIM_MASK1(8, 16)
-                           EFIM_MASK1(9, 17) EFIM_MASK1(10, 18) EFIM_MASK1(11, 19) EFIM_MASK1(12, 24)
-                               EFIM_MASK1(13, 25) EFIM_MASK1(14, 26) EFIM_MASK1(15, 27)
-                   : "+v"(sc[0]), "+v"(sc[1]), "+v"(sc[2]), "+v"(sc[3]), "+v"(sc[4]), "+v"(sc[5]), "+v"(sc[6]),
-                     "+v"(sc[7]), "+v"(sc[8]), "+v"(sc[9]), "+v"(sc[10]), "+v"(sc[11]), "+v"(sc[12]), "+v"(sc[13]),
-                     "+v"(sc[14]), "+v"(sc[15])
-                   : "v"(lim), "v"(-INFINITY)
-                   : "vcc");
-#undef EFIM_MASK1
+      // (its last key is number 27, so that a limit of 31 hides nothing)
+      const uint32_t hidden = ~0u << min(max(lim, 0), 31);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)hidden, (r >> 2) * 8 + (r & 3), 1);  // 0 or all ones
+        sc[r] = __uint_as_float((m & 0xFF800000u) | (~m & __float_as_uint(sc[r])));
+      }
     }
   };
   // maximum of a half's scores of this lane's row, in this lane's half of its elements
