@@ -339,12 +339,19 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // Head dim 64, few rows: a few registers less than the compiler takes by itself let two 8-wave (or
 // four 4-wave) workgroups share a compute unit instead of one (or three), without a spill: 64
 // requests of 4000..7000 + 1..8 tokens, 32/8 heads 153.0 -> 136.2 us, 24 requests of 2000..7000 +
-// 4..8 tokens 55.1 -> 52.3 us.  The kernels for many rows spill at that bound (197 -> 304 us).
-constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp) {
-  return d == 64 && kp && !kv8 && (!fused || waves == 8) ? 4 : 2;
+// 4..8 tokens 55.1 -> 52.3 us.
+//
+// PACK (head dim 64, bf16 cache, many rows): the same for the pipelined kernel, whose plain form
+// takes 149 registers (four waves: 151).  With the value product in front of the score product in
+// every phase, two key operands in flight instead of four and operand addresses derived from one
+// register each it fits 128 (four waves: with two spilled, outside the loop).  Either form does
+// the same arithmetic; Plan::pack chooses.
+constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bool pack) {
+  return pack || (d == 64 && kp && !kv8 && (!fused || waves == 8)) ? 4 : 2;
 }
-template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP>
-__global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP)) void extend_attention_kernel(const AttnParams p) {
+template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false>
+__global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(const AttnParams p) {
+  static_assert(!PACK || (D == 64 && !KV8 && !KP), "the packed form is for head dim 64, bf16, many rows");
   static_assert(KP || !FUSED, "the decode step has at most 32 rows per tile");
   using G = Geometry<D>;
   // geometry of the gather: rows as they lie in the cache
@@ -646,7 +653,9 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // of key kb * 32 + i32 -- 16 bytes of the bf16 tile, or 8 codes that become bf16 in registers
   using KRaw = std::conditional_t<KV8, u32x2, u32x4>;
   auto read_k = [&](uint32_t buf, int kb, int st) -> KRaw {
-    return *reinterpret_cast<const LDS_PTR(KRaw)>(k_addr[st] + (buf + kb * 32 * kGRowBytes));
+    // (PACK: bits 5 and 6 of the address belong to the step alone)
+    const uint32_t at = PACK ? k_addr[0] ^ (uint32_t)(st << 5) : k_addr[st];
+    return *reinterpret_cast<const LDS_PTR(KRaw)>(at + (buf + kb * 32 * kGRowBytes));
   };
   // (the same conversion serves the value operands)
   auto k_operand = [&](KRaw raw) -> bf16x8 {
@@ -689,7 +698,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     v_addr[d] = KV8 ? lds0 + kVOff + v8_key * D + (((d * 2 + v8_chunk) ^ v8_swz) << 4) + v8_sub
                     : lds0 + kVOff + v_key * G::kRowBytes + v_sub + (((d * 4 + v_chunk) ^ v_swz) << 4);
   auto read_v_raw = [&](uint32_t buf, int ks4, int d) -> VRaw {
-    const uint32_t at = v_addr[d] + (buf + ks4 * 16 * kGRowBytes);
+    const uint32_t at = (PACK ? v_addr[0] ^ (uint32_t)(d << 6) : v_addr[d]) + (buf + ks4 * 16 * kGRowBytes);
     if constexpr (KV8) {
       return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(i32x2))(at)));
     } else {
@@ -705,21 +714,22 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // three are independent, so each of a wave's MFMAs has vector instructions to hide behind it
   // and neither pipe waits for the other inside a wave.  Measured on this part: a 32x32x16 MFMA
   // occupies its pipe for 32.4 cycles and the wave's issue slot for four of them, so up to six
-  // vector instructions per MFMA are free (an exponential counts as two); a half needs about four.
+  // vector instructions per MFMA are free (an exponential counts as two); with head dim 128 a
+  // half needs about four.  With head dim 64 it has half the MFMAs for the same softmax, about
+  // eight each: there the vector pipe is the longer one and the matrix pipe hides behind it.
   // Against tiles worked off one phase after the other (scores, softmax, values): 28/4-head step
   // with 8..64 new tokens 131.1 -> 124.6 us (8-bit cache 127.6 -> 121.9 us), 4 x 512 new tokens
   // behind 16384 502 -> 491 us.
   u32x4 p0[2], p1[2];  // probabilities of an even / odd half as B operands (bf16)
   f32x16 s0, s1;       // raw scores of an even / odd half
-  // m_run, or while the row has seen no score above minus infinity a value so low that any finite
-  // score makes an infinite weight: its half then takes the path that sets the reference
-  float m_use = 0.f;
+  // The reference of a row that has seen no score above minus infinity: so low that any finite
+  // score makes an infinite weight, whose half then takes the path that sets the reference.
   constexpr float kNoReference = -3.0e38f;
   float l_half = 0.f;  // row sum of the first half of the tile whose second half is next
   // Two probabilities as a bf16 pair (both operand words and row sums take the rounded values).
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
-  auto prob = [&](float sc) { return __builtin_amdgcn_exp2f(sc * p.scale_log2 - m_use); };
+  auto prob = [&](float sc) { return __builtin_amdgcn_exp2f(sc * p.scale_log2 - m_run); };
 
   // kQk: scores of key half kb of the K tile at ks into sn.  kPv: value product of pp with 32-key
   // half vh of the V tile at vs.  kSm: probabilities of sc into pc and their sum.
@@ -729,37 +739,50 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     constexpr int kPvMfma = 2 * G::kDBlocks;
     constexpr int kGroups = G::kSteps + kPvMfma;
     constexpr int kPer = 16 / kGroups;  // score elements turned into probabilities per group
+    // Scores first: their K operands are read in front of the phase, the V operands under their
+    // MFMAs.  PACK: values first, then fewer registers are live at any point; the last two of
+    // their MFMAs and the score MFMAs each cover the read of a K operand two steps ahead.
+    constexpr int kAheadK = PACK && kPv ? 2 : G::kSteps;
+    constexpr int kFirst = PACK ? kPvMfma : G::kSteps;  // MFMAs of the product that comes first
     KRaw ka[G::kSteps];
     VRaw va[kPvMfma];
-    if constexpr (kQk) {
+    auto load_k = [&](int st) __attribute__((always_inline)) { ka[st] = read_k(ks, kb, st); };
+    auto load_v = [&](int j) __attribute__((always_inline)) { va[j] = read_v_raw(vs, vh * 2 + j / G::kDBlocks, j % G::kDBlocks); };
+    // (keeps the derived addresses from being formed once and held)
+    if constexpr (PACK) asm volatile("" : "+v"(k_addr[0]), "+v"(v_addr[0]));
+    if constexpr (kQk && !(PACK && kPv)) {
 #pragma unroll
-      for (int st = 0; st < G::kSteps; ++st) ka[st] = read_k(ks, kb, st);
+      for (int st = 0; st < G::kSteps; ++st) load_k(st);
     }
-    if constexpr (kPv && !kQk) {
+    if constexpr (kPv && (PACK || !kQk)) {
 #pragma unroll
-      for (int j = 0; j < kPvMfma; ++j) va[j] = read_v_raw(vs, vh * 2 + j / G::kDBlocks, j % G::kDBlocks);
+      for (int j = 0; j < kPvMfma; ++j) load_v(j);
     }
     __builtin_amdgcn_sched_barrier(0);
     float acc = 0.f;
     float pr[kPer > 1 ? kPer : 2];
 #pragma unroll
     for (int i = 0; i < kGroups; ++i) {
-      if (i < G::kSteps) {
+      const bool scores = (i < kFirst) != PACK;
+      const int j = i < kFirst ? i : i - kFirst;
+      if (scores) {
         if constexpr (kQk) {
-          if (i == 0) {
+          if (j == 0) {
             f32x16 zero;
 #pragma unroll
             for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[i]), qb[i], zero, 0, 0, 0);
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[j]), qb[j], zero, 0, 0, 0);
           } else {
-            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[i]), qb[i], sn, 0, 0, 0);
+            sn = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k_operand(ka[j]), qb[j], sn, 0, 0, 0);
           }
-          if constexpr (kPv) va[i] = read_v_raw(vs, vh * 2 + i / G::kDBlocks, i % G::kDBlocks);
+          if constexpr (kPv && !PACK) load_v(j);
+          if (j + kAheadK < G::kSteps) load_k(j + kAheadK);
         }
       } else if constexpr (kPv) {
-        const int j = i - G::kSteps, d = j % G::kDBlocks;
+        const int d = j % G::kDBlocks;
         o[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v_operand(va[j]), __builtin_bit_cast(bf16x8, pp[j / G::kDBlocks]),
                                                        o[d], 0, 0, 0);
+        if (PACK && kQk && j >= kPvMfma - kAheadK) load_k(j - (kPvMfma - kAheadK));
       }
       if constexpr (kSm) {
 #pragma unroll
@@ -807,9 +830,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   };
   // Moves a row's reference to `m_next` (rows whose reference stays pass m_run: factor one).
   auto move_reference = [&](float m_next) __attribute__((always_inline)) {
-    const float m_safe = (m_next == -INFINITY) ? kNoReference : m_next;
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-    const float f = m_next == m_run ? 1.f : alpha;
+    const float f = m_next == m_run ? 1.f : __builtin_amdgcn_exp2f(m_run - m_next);
     l_run *= f;
     l_half *= f;
 #pragma unroll
@@ -817,7 +838,6 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[d][r] *= f;
     m_run = m_next;
-    m_use = m_safe;
   };
   // Behind a half's probabilities: m_run is a reference value, set to the row's maximum over its
   // first tile and moved only by a half whose maximum lies more than 2^kSlack above it, so that
@@ -1128,7 +1148,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       mask_half(s0, k_begin);
       mask_half(s1, k_begin + 32);
       m_run = cross_half_max(fmaxf(half_max(s0), half_max(s1))) * p.scale_log2;
-      m_use = (m_run == -INFINITY) ? kNoReference : m_run;
+      if (m_run == -INFINITY) m_run = kNoReference;
       l_half = phase(kNo, s0, 0u, 0, kNo, p0, 0u, 0, kYes, s0, p0);
     }
     auto body = [&](int t, auto slot_c) __attribute__((always_inline)) {
@@ -1183,6 +1203,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       }
       ++t;
     }
+    if (m_run == kNoReference) m_run = -INFINITY;
     for (; t <= ntiles; ++t) top(t, (t + STAGES - 1) % STAGES);
   }
 
@@ -1396,7 +1417,7 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 // and the short step with head dim 64 (64 requests of 4000..9000 + 8..16 tokens, 4 heads: 102.4 -> 91.5
 // us; the plain call over the same rows is not faster with three).
 template <bool FUSED>
-void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, dim3 grid, const AttnParams& p,
+void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool pack, dim3 grid, const AttnParams& p,
                    hipStream_t stream) {
 #define EFIM_ATTN_LAUNCH2(DD, F8, KP)                                                              \
   do {                                                                                             \
@@ -1409,6 +1430,13 @@ void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, dim3 grid, 
     else if (few_rows) EFIM_ATTN_LAUNCH2(DD, F8, true);                        \
     else EFIM_ATTN_LAUNCH2(DD, F8, FUSED);                                     \
   } while (0)
+  if constexpr (!FUSED) {
+    if (pack && head_dim == 64 && !fp8 && !few_rows) {
+      if (wide) extend_attention_kernel<64, 8, 3, false, false, false, true><<<grid, 512, 0, stream>>>(p);
+      else extend_attention_kernel<64, 4, 2, false, false, false, true><<<grid, 256, 0, stream>>>(p);
+      return;
+    }
+  }
   if (head_dim == 128) {
     if (fp8) EFIM_ATTN_LAUNCH(128, true); else EFIM_ATTN_LAUNCH(128, false);
   } else {
@@ -1457,7 +1485,7 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, grid, p, stream);
+  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, plan.pack, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
@@ -1491,7 +1519,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<true>(D, wide, fmt.fp8, true, grid, p, stream);
+  launch_kernel<true>(D, wide, fmt.fp8, true, false, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }

@@ -229,6 +229,52 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   }
   plan->num_partial_slots = slot;
 
+  // Head dim 64, bf16 cache, many rows: there are two forms of the kernel, one that leaves room for
+  // another 8-wave workgroup on its compute unit (a fourth 4-wave one) and one that runs 2-4 %
+  // faster where there is none.  Two on a unit do about 1.15 times the work of one, but either
+  // then runs at little more than half speed, and a long one that started late ends late.
+  // Measured (us, plain / packed; 32/8 heads unless given).  Two workgroups per unit, items all
+  // resident at once: their pairs are fixed and are compared with the plain form's packing --
+  // 424 equal items 285 / 259, 512 equal 79.0 / 73.0, 512 of 31..108 tiles 185 / 190, 312 of 40..92
+  // tiles 106 / 118.  More items than that are handed out as units fall free: 616 of up to 102
+  // tiles, longest 1.4 times an even share 193 / 170, 660 (1.6 times; 4 heads, full misses) 108 /
+  // 105, 592 (1.8 times) 98 / 101, 516 (2.0 times) 88 / 97.  Four waves: with up to three items per
+  // unit the fourth place stays empty, 488..572 items 1-7 % slower packed; 950..1050 items 6-11 %
+  // faster, 1280 equal.
+  if (b->head_dim == 64) {
+    const size_t units = (size_t)std::max(1, M == 256 ? num_slots : num_slots / 2), n = pend.size();
+    if (M != 256) {
+      plan->pack = n > 3 * units;
+    } else if (n > units) {
+      constexpr double kTwo = 1.15;
+      std::vector<int64_t> cost;
+      cost.reserve(n);
+      int64_t total = 0;
+      for (const Pending& p : pend) {
+        cost.push_back(p.cost);
+        total += p.cost;
+      }
+      std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
+      if (n > 2 * units) {
+        plan->pack = (double)cost[0] * (double)(2 * units) < 1.7 * (double)total;
+      } else {
+        double paired = 0;
+        std::vector<int64_t> load(cost.begin(), cost.begin() + units);  // ends as a min-heap
+        std::make_heap(load.begin(), load.end(), std::greater<int64_t>());
+        for (size_t i = 0; i < units; ++i) {
+          const double a = (double)cost[i], c = i + units < n ? (double)cost[i + units] : 0.0;
+          paired = std::max(paired, 2.0 * c / kTwo + (a - c));
+        }
+        for (size_t i = units; i < n; ++i) {
+          std::pop_heap(load.begin(), load.end(), std::greater<int64_t>());
+          load.back() += cost[i];
+          std::push_heap(load.begin(), load.end(), std::greater<int64_t>());
+        }
+        plan->pack = paired < (double)*std::max_element(load.begin(), load.end());
+      }
+    }
+  }
+
   // Order: heaviest first.  With XCD grouping, items that read the same K/V (same request and
   // kv head) are given workgroup ids congruent modulo 8, so they run on one XCD and share its
   // L2; the groups are spread over the 8 XCDs by greedy load balancing.

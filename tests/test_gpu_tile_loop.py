@@ -246,3 +246,37 @@ def test_minus_infinity_scores_in_front_of_low_ones(E, row_tile, split, d):
         E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
     U.assert_close(got, ref)
+
+
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("grow", [(), (40, 96, 190)])
+@pytest.mark.parametrize("page", [8, 16, 256])
+def test_packed_kernel_gives_the_plain_kernels_bits(E, row_tile, grow, page):
+    """Head dim 64 over a bf16 cache has a second form of the kernel, taken when there are many work
+    items for the compute units; told that there is one unit, the planner takes it for any batch.
+    Same arithmetic, so the same bits; lengths at the edges of halves and tiles, and keys that move
+    references.  The plain form is compared with the oracle above."""
+    b = W.make_batch("c1", seed=4900 + len(grow), heads=(8, 2), head_dim=64, page_size=page,
+                     lengths=tuple(np.array(x, dtype=np.int32) for x in EDGES))
+    q_roped, kc, vc = U.oracle_inputs(b)
+    k = kc.reshape(b.cache_shape())
+    for at in grow:
+        for r in range(b.batch):
+            for pos in range(at, int(b.cached_len[r] + b.new_len[r])):
+                row = k[b.block_table[r, pos // b.page_size], :, pos % b.page_size]
+                row[...] = np.where(row & 0x7F80, row + np.uint16(2 << 7), row)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    got = []
+    try:
+        for split in (0, 64):
+            E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+            for slots in (0, 2):
+                E.efim_set_tuning(E.EFIM_TUNE_NUM_SLOTS, slots)
+                got.append(U.gpu_extend_attention(E, b, q_roped, kc, vc))
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+        E.efim_set_tuning(E.EFIM_TUNE_NUM_SLOTS, 0)
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[2], got[3])
+    U.assert_close(got[1], O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc),
+                   large_outputs=True)
