@@ -349,9 +349,12 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bool pack) {
   return pack || (d == 64 && kp && !kv8 && (!fused || waves == 8)) ? 4 : 2;
 }
-template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false>
+//
+// P8: 64-byte code rows on pages of 8, the one layout whose 1 KB load spans two pages.
+template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false>
 __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(const AttnParams p) {
   static_assert(!PACK || (D == 64 && !KV8 && !KP), "the packed form is for head dim 64, bf16, many rows");
+  static_assert(!P8 || (D == 64 && KV8), "other rows are longer");
   static_assert(KP || !FUSED, "the decode step has at most 32 rows per tile");
   using G = Geometry<D>;
   // geometry of the gather: rows as they lie in the cache
@@ -526,10 +529,34 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     // other (one request of 256 + 32 tokens, 4 heads: 7.7 -> 7.2 us).  The other kernels have
     // no registers for it (the decode step spilled: 13.3 -> 13.7 us) or longer ranges.
     constexpr bool kGroupedLast = KP && !FUSED;
-    if constexpr (kGroupedIssue && kGLoadsPerMatrix % kLoadsPerWave == 0) {
-      if ((full_tile || kGroupedLast) && offsets_fit_32 && page_loads >= 1) {
-        // (page_loads is 0 only for 64-byte code rows on pages of 8; on larger pages the wide form
-        // took such a step, 64 requests of 4000..7000 + 1..8 tokens, 32/8 heads, from 113.9 to 94.5 us)
+    // P8: both page ids of a load come by scalar loads, all of the wave's together, and a lane picks
+    // its page's; looked up lane by lane the ids wait on the counter of the gathers and drain the
+    // tiles in flight.  64 requests of 4000..7000 + 1..8 tokens, 32/8 heads 116.3 -> 97.5 us.  (A
+    // kernel of its own: as a branch it cost the larger pages 1-3 %.)
+    if constexpr (P8) {
+      static_assert(kGKeysPerLoad == 2 * kMinPageSize && kGLoadsPerMatrix % kLoadsPerWave == 0,
+                    "two pages per load, one matrix per wave");
+      if (full_tile && offsets_fit_32) {
+        const int load0 = issuer * kLoadsPerWave;
+        const bool is_v = load0 >= kGLoadsPerMatrix;  // wave-uniform
+        const int idx0 = is_v ? load0 - kGLoadsPerMatrix : load0;
+        uint32_t id[2 * kLoadsPerWave];
+#pragma unroll
+        for (int j = 0; j < 2 * kLoadsPerWave; ++j) id[j] = page_of(t * kKeyTile + (2 * idx0 + j) * kMinPageSize);
+        const char* mat = (is_v ? vc : kc) + head_bytes + (g_key & (kMinPageSize - 1)) * kGRowBytes;
+#pragma unroll
+        for (int j = 0; j < kLoadsPerWave; ++j) {
+          const int tile_row = (idx0 + j) * kGKeysPerLoad + g_key;
+          const int swz = is_v ? vswz8(tile_row) : kswz8(tile_row);
+          const uint32_t page = g_key < kMinPageSize ? id[2 * j] : id[2 * j + 1];
+          load_to_lds_16(mat + (uint64_t)page * (uint32_t)page_bytes + ((g_pc ^ swz) << 4),
+                         (is_v ? vbuf : kbuf) + (idx0 + j) * 1024);
+        }
+        return;
+      }
+    }
+    if constexpr (!P8 && kGroupedIssue && kGLoadsPerMatrix % kLoadsPerWave == 0) {
+      if ((full_tile || kGroupedLast) && offsets_fit_32) {
         // A load never spans two pages: page, head and first row make a wave-uniform base (scalar
         // registers), the lane adds its row and (swizzled) chunk.  This wave's loads are
         // consecutive rows of ONE matrix, so the base is looked up and multiplied out only where
@@ -604,9 +631,9 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       }
     }
     // (rolled: this path serves the last tile of a range and a few rare layouts, and is instantiated
-    // once per stage; unrolled it was most of the kernel's code.  Not where a load can span two
-    // pages -- 64-byte code rows on pages of 8: every tile comes here then, and its page lookups
-    // have to go out together.  Nor in the eight-wave kernel that takes this path for all tiles.)
+    // once per stage; unrolled it was most of the kernel's code.  Not with 64-byte code rows, whose
+    // four loads per wave have their page lookups go out together, nor in the eight-wave kernel
+    // that takes this path for all tiles.)
     constexpr int kUnroll = kGroupedIssue && kGKeysPerLoad <= kMinPageSize ? 1 : kLoadsPerWave;
 #pragma unroll kUnroll
     for (int j = 0; j < kLoadsPerWave; ++j) {
@@ -629,7 +656,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       // one load never spans two pages, except for the shortest rows on the smallest pages:
       // then every lane looks its own page up
       int64_t page;
-      if constexpr (kGKeysPerLoad <= kMinPageSize)
+      if constexpr (!P8)
         page = page_of(first_off + t * kKeyTile + row0);
       else
         page = bt[min(first_page + ((first_off + t * kKeyTile + tile_row) >> ps), last_page)];  // per lane
@@ -1419,16 +1446,16 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 template <bool FUSED>
 void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool pack, dim3 grid, const AttnParams& p,
                    hipStream_t stream) {
-#define EFIM_ATTN_LAUNCH2(DD, F8, KP)                                                              \
+#define EFIM_ATTN_LAUNCH2(DD, F8, KP, P8)                                                             \
   do {                                                                                             \
-    if (wide) extend_attention_kernel<DD, 8, 3, FUSED, F8, KP><<<grid, 512, 0, stream>>>(p); \
-    else extend_attention_kernel<DD, 4, F8 || (FUSED && DD == 64) ? 3 : 2, FUSED, F8, KP><<<grid, 256, 0, stream>>>(p); \
+    if (wide) extend_attention_kernel<DD, 8, 3, FUSED, F8, KP, false, P8><<<grid, 512, 0, stream>>>(p); \
+    else extend_attention_kernel<DD, 4, F8 || (FUSED && DD == 64) ? 3 : 2, FUSED, F8, KP, false, P8><<<grid, 256, 0, stream>>>(p); \
   } while (0)
-#define EFIM_ATTN_LAUNCH(DD, F8)                                               \
+#define EFIM_ATTN_LAUNCH(DD, F8, P8)                                           \
   do {                                                                         \
-    if constexpr (FUSED) EFIM_ATTN_LAUNCH2(DD, F8, true);                      \
-    else if (few_rows) EFIM_ATTN_LAUNCH2(DD, F8, true);                        \
-    else EFIM_ATTN_LAUNCH2(DD, F8, FUSED);                                     \
+    if constexpr (FUSED) EFIM_ATTN_LAUNCH2(DD, F8, true, P8);                   \
+    else if (few_rows) EFIM_ATTN_LAUNCH2(DD, F8, true, P8);                     \
+    else EFIM_ATTN_LAUNCH2(DD, F8, FUSED, P8);                                   \
   } while (0)
   if constexpr (!FUSED) {
     if (pack && head_dim == 64 && !fp8 && !few_rows) {
@@ -1438,9 +1465,11 @@ void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool pack, 
     }
   }
   if (head_dim == 128) {
-    if (fp8) EFIM_ATTN_LAUNCH(128, true); else EFIM_ATTN_LAUNCH(128, false);
+    if (fp8) EFIM_ATTN_LAUNCH(128, true, false); else EFIM_ATTN_LAUNCH(128, false, false);
+  } else if (fp8) {
+    if (p.page_shift == 3) EFIM_ATTN_LAUNCH(64, true, true); else EFIM_ATTN_LAUNCH(64, true, false);
   } else {
-    if (fp8) EFIM_ATTN_LAUNCH(64, true); else EFIM_ATTN_LAUNCH(64, false);
+    EFIM_ATTN_LAUNCH(64, false, false);
   }
 #undef EFIM_ATTN_LAUNCH
 #undef EFIM_ATTN_LAUNCH2

@@ -280,3 +280,29 @@ def test_packed_kernel_gives_the_plain_kernels_bits(E, row_tile, grow, page):
     assert np.array_equal(got[0], got[1]) and np.array_equal(got[2], got[3])
     U.assert_close(got[1], O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc),
                    large_outputs=True)
+
+
+@pytest.mark.parametrize("page", [8, 16, 256])
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("split", [-1, 64])
+def test_short_step_over_code_rows_of_64_bytes(E, page, row_tile, split):
+    """One launch over an 8-bit cache with head dim 64: full tiles and last tiles of 1 .. 64 keys, on pages
+    of 8 (two pages to a load) and larger ones; codes byte for byte."""
+    from test_gpu_fp8 import oracle_cache8, oracle_step8, run_decode8
+    new = [1, 2, 7, 8, 5, 3, 8, 4]
+    ends = [1, 9, 64, 65, 128, 200, 321, 700]
+    cached = [max(0, e - n) for e, n in zip(ends, new)]
+    b = W.make_batch("c1", seed=4950 + page, heads=(8, 2), head_dim=64, page_size=page,
+                     lengths=(np.array(cached, dtype=np.int32), np.array(new, dtype=np.int32)))
+    k_scale, v_scale = 0.0123, 0.031
+    kc, vc = oracle_cache8(b, k_scale, v_scale)
+    _, kc_ref, vc_ref, ref = oracle_step8(b, kc, vc, k_scale, v_scale)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+    try:
+        got, kc_got, vc_got, _ = run_decode8(E, b, kc, vc, k_scale, v_scale)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+    assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+    U.assert_close(got, ref, large_outputs=True)
