@@ -46,8 +46,8 @@ def scalar_registers(operand):
 
 
 def short_waits(text):
-    """Vector instructions that read a scalar register or VCC less than two wait states behind the
-    vector instruction that wrote it, in program order."""
+    """Vector instructions that read a scalar register or VCC less than two wait states -- memory
+    instructions less than five -- behind the vector instruction that wrote it, in program order."""
     found, written, function = [], {}, ""
     for line in text.splitlines():
         m = re.match(r"[0-9a-f]+ <(.*)>:", line)
@@ -80,6 +80,10 @@ def short_waits(text):
                 for r in scalar_registers(x):
                     written[r] = 0
         else:
+            if op.startswith(("global_", "buffer_", "flat_", "scratch_")):
+                read = set().union(set(), *(scalar_registers(x.split(" ")[0]) for x in operands))
+                if any(written.get(r, 5) < 5 for r in read):
+                    found.append("%s: %s" % (function[:60], line.split("//")[0].strip()))
             written = {r: n + states for r, n in written.items()}
             for x in operands[:1]:  # a scalar instruction that writes the register ends the matter
                 for r in scalar_registers(x) if op.startswith("s_") else ():
@@ -94,6 +98,8 @@ def short_waits(text):
     ("v_cmp_gt_i32_e64 s[2:3], v1, v2\n\tv_mov_b32_e32 v9, v8\n\tv_cndmask_b32_e64 v3, v4, v5, s[2:3]", 1),
     ("v_cmp_gt_i32_e64 s[2:3], v1, v2\n\tv_cmp_gt_i32_e64 s[4:5], v1, v2\n\tv_mov_b32_e32 v9, v8\n\t"
      "v_cndmask_b32_e64 v3, v4, v5, s[2:3]", 0),
+    ("v_readfirstlane_b32 s2, v1\n\ts_mov_b32 m0, s9\n\ts_nop 0\n\tglobal_load_lds_dwordx4 v3, s[2:3] offset:1024", 1),
+    ("v_readfirstlane_b32 s2, v1\n\ts_mov_b32 m0, s9\n\ts_nop 3\n\tglobal_load_lds_dwordx4 v3, s[2:3] offset:1024", 0),
 ])
 def test_the_rule_finds_its_cases(code, count):
     assert len(short_waits("0 <f>:\n\t" + code)) == count

@@ -306,3 +306,43 @@ def test_short_step_over_code_rows_of_64_bytes(E, page, row_tile, split):
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
     assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
     U.assert_close(got, ref, large_outputs=True)
+
+
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("cache", ["bf16", "fp8"])
+@pytest.mark.parametrize("split", [0, 64, 128])
+def test_growing_scores_through_split_ranges_and_codes(E, row_tile, d, cache, split):
+    """Keys four times as large from positions 40, 96 and 190 on, so that references move inside a part and
+    parts with very different references are merged; bf16 rows and codes (all below saturation)."""
+    from test_gpu_fp8 import gpu_attention8, oracle_cache8
+    from oracle import fp8_oracle as F
+    b = W.make_batch("c1", seed=4970 + d, lengths=tuple(np.array(x, dtype=np.int32) for x in EDGES), heads=(4, 2), head_dim=d)
+    scale = 1.0
+    if cache == "bf16":
+        q_roped, kc, vc = U.oracle_inputs(b)
+        low, step = np.uint16(0x7F80), np.uint16(2 << 7)  # exponent field, factor of four
+    else:
+        kc, vc = oracle_cache8(b, scale, scale)
+        q_roped, _ = F.rope_append_fp8(b.cached_len, b.new_len, b.block_table, b.page_size, b.q_new, b.k_new, b.v_new,
+                                       kc, vc, b.rope_base, scale, scale)
+        low, step = np.uint8(0x78), np.uint8(2 << 3)
+    k = kc.reshape(b.cache_shape())
+    for at in (40, 96, 190):
+        for r in range(b.batch):
+            for pos in range(at, int(b.cached_len[r] + b.new_len[r])):
+                row = k[b.block_table[r, pos // b.page_size], :, pos % b.page_size]
+                row[...] = np.where(row & low, row + step, row)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+    try:
+        if cache == "bf16":
+            ref = O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc)
+            got = U.gpu_extend_attention(E, b, q_roped, kc, vc)
+        else:
+            ref = F.extend_attention_fp8(b.cached_len, b.new_len, b.block_table, b.page_size, q_roped, kc, vc, scale, scale)
+            got = gpu_attention8(E, b, q_roped, kc, vc, scale, scale)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+    U.assert_close(got, ref, large_outputs=True)
