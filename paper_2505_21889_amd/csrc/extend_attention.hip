@@ -313,12 +313,14 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 }
 
 // WAVES wavefronts per workgroup, 32 query rows each; STAGES LDS buffers of one 64-key K/V
-// tile each.  Two configurations are launched:
-//   <4 waves, 2 stages>  128 rows, 64 KB LDS, two workgroups per compute unit -- steps bound
-//                        by HBM, where many small independent gathers in flight matter;
-//   <8 waves, 3 stages>  256 rows, 96 KB LDS, one workgroup per compute unit -- compute-heavy
-//                        steps, where each gathered K/V byte is used by twice as many rows and
-//                        the gather runs two tiles ahead.
+// tile each.  Launched are
+//   <4 waves, 2 stages>  128 rows, 64 KB LDS with head dim 128, two workgroups per compute unit --
+//                        steps bound by HBM, where many small independent gathers in flight
+//                        matter; three stages where a tile is half as large (8-bit caches; the
+//                        short step with head dim 64);
+//   <8 waves, 3 stages>  256 rows, 96 KB LDS with head dim 128, one workgroup per compute unit --
+//                        compute-heavy steps, where each gathered K/V byte is used by twice as
+//                        many rows and the gather runs two tiles ahead.
 //
 // FUSED (decode step and other short steps: every request has at most kFusedMaxTokens new
 // tokens and at most 32 query rows per kv head, so all rows of a (request, kv head) pair are
@@ -327,7 +329,7 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // those that fall into its key range into its LDS tiles and stores them, with their values,
 // into the paged cache.
 //
-// KV8: the caches hold E4M3 codes.  The stages then hold code tiles (half the size); both
+// KV8: the caches hold E4M3 codes.  The stages then hold code tiles (half the size); all
 // configurations run with three of them -- more tiles in flight measured slower, not faster.
 //
 // KP ("key parallel"): every work item of the launch has at most 32 query rows (decode steps,
@@ -337,9 +339,9 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // kernel the two waves without rows issue all the gathers.
 //
 // Head dim 64, few rows: a few registers less than the compiler takes by itself let two 8-wave (or
-// four 4-wave) workgroups share a compute unit instead of one (or three), without a spill: 64
-// requests of 4000..7000 + 1..8 tokens, 32/8 heads 153.0 -> 136.2 us, 24 requests of 2000..7000 +
-// 4..8 tokens 55.1 -> 52.3 us.
+// four 4-wave) workgroups share a compute unit instead of one (or three), without a spill.  The
+// same kernel without and with the bound: 64 requests of 4000..7000 + 1..8 tokens, 32/8 heads, one
+// launch 143.7 / 137.1 us, 24 requests of 2000..7000 + 4..8 tokens, two calls 47.1 / 42.5 us.
 //
 // PACK (head dim 64, bf16 cache, many rows): the same for the pipelined kernel, whose plain form
 // takes 149 registers (four waves: 151).  With the value product in front of the score product in
@@ -982,13 +984,11 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // done with the buffer about to be refilled.
   auto wait_tile = [&](int t, int last) {
     const int later = min(STAGES - 2, last - t);  // tiles issued after t so far
-    if (STAGES >= 5 && later == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * kLoadsPerWave) : "memory");
-    else if (STAGES >= 4 && later == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
-    else if (STAGES >= 3 && later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
+    if (STAGES >= 3 && later == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   };
-  static_assert(STAGES <= 5, "wait_tile handles up to three tiles in flight");
+  static_assert(STAGES <= 3, "wait_tile and the loops below handle two tiles in flight");
 
   // Pipelined kernels: stage t of the ring holds the keys of tile t and the values of tile t - 1
   // (a tile's scores are formed one tile ahead of its value product); stages 0 .. ntiles.  Each
@@ -1058,7 +1058,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
         }
     }
     // this wave's raw rows have landed; the gathers issued behind them stay in flight
-    static_assert(STAGES <= 3 && 2 * kLoadsPerWave <= 63, "the wait counts up to two tiles");
+    static_assert(2 * kLoadsPerWave <= 63, "the wait counts up to two tiles");
     if (issuer < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (STAGES >= 3 && ntiles >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
@@ -1153,8 +1153,6 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       ring_step(t0, std::integral_constant<int, 0>{});
       ring_step(t0, std::integral_constant<int, 1>{});
       if constexpr (STAGES > 2) ring_step(t0, std::integral_constant<int, 2>{});
-      if constexpr (STAGES > 3) ring_step(t0, std::integral_constant<int, 3>{});
-      if constexpr (STAGES > 4) ring_step(t0, std::integral_constant<int, 4>{});
     }
   } else {
     // key tiles this wave's rows reach into; its pipeline ends there, its gathers go on
@@ -1204,13 +1202,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
         body(t, std::integral_constant<int, 3 % STAGES>{});
         ++t;
       }
-      if constexpr (STAGES > 3) {
-        if (t >= n_w) break;
-        body(t, std::integral_constant<int, 4 % STAGES>{});
-        ++t;
-      }
     }
-    static_assert(STAGES <= 4, "one copy of the body per stage");
     if (n_w > 0) {
       // stage n_w: the second half of this wave's last tile and the values of both halves
       const int slot = t % STAGES;
@@ -1441,8 +1433,9 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 
 // few_rows: no work item has more than 32 query rows (always so for the decode step)
 // Four-wave kernels take two stages over bf16 rows, three where a tile is half as large: 8-bit rows,
-// and the short step with head dim 64 (64 requests of 4000..9000 + 8..16 tokens, 4 heads: 102.4 -> 91.5
-// us; the plain call over the same rows is not faster with three).
+// and the short step with head dim 64 (64 requests of 4000..9000 + 8..16 tokens, 4 heads, otherwise
+// the same kernel: two stages 102.5 us, three 90.6 us; the plain call over the same rows is not
+// faster with three).
 template <bool FUSED>
 void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool pack, dim3 grid, const AttnParams& p,
                    hipStream_t stream) {
