@@ -71,7 +71,7 @@ struct Plan {
   int rows_per_item = 128;  // query rows per workgroup tile (32 per wave)
   int max_item_rows = 0;    // largest row_count of a work item
   int partial_rows = 128;   // rows per partial-result slot of a split key range
-  bool pack = false;        // head dim 64: the kernel of which more workgroups fit a compute unit
+  bool crowded = false;     // head dim 64: work items crowd the compute units (other forms of the bf16 kernels)
   std::vector<ReqInfo> reqs;
   std::vector<WorkItem> items;
   std::vector<MergeItem> merges;

@@ -317,7 +317,7 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 //   <4 waves, 2 stages>  128 rows, 64 KB LDS with head dim 128, two workgroups per compute unit --
 //                        steps bound by HBM, where many small independent gathers in flight
 //                        matter; three stages where a tile is half as large (8-bit caches; the
-//                        short step with head dim 64);
+//                        short step with head dim 64 and many work items);
 //   <8 waves, 3 stages>  256 rows, 96 KB LDS with head dim 128, one workgroup per compute unit --
 //                        compute-heavy steps, where each gathered K/V byte is used by twice as
 //                        many rows and the gather runs two tiles ahead.
@@ -347,7 +347,7 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // takes 149 registers (four waves: 151).  With the value product in front of the score product in
 // every phase, two key operands in flight instead of four and operand addresses derived from one
 // register each it fits 128 (four waves: with two spilled, outside the loop).  Either form does
-// the same arithmetic; Plan::pack chooses.
+// the same arithmetic; Plan::crowded chooses.
 constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bool pack) {
   return pack || (d == 64 && kp && !kv8 && (!fused || waves == 8)) ? 4 : 2;
 }
@@ -1432,17 +1432,20 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 }
 
 // few_rows: no work item has more than 32 query rows (always so for the decode step)
-// Four-wave kernels take two stages over bf16 rows, three where a tile is half as large: 8-bit rows,
-// and the short step with head dim 64 (64 requests of 4000..9000 + 8..16 tokens, 4 heads, otherwise
-// the same kernel: two stages 102.5 us, three 90.6 us; the plain call over the same rows is not
-// faster with three).
+// Four-wave kernels take two stages over bf16 rows and three over 8-bit rows, where a tile is half
+// as large.  The short step with head dim 64 takes the third stage with more than three work items
+// per compute unit: with two stages three workgroups fit a unit, with three only two, whose
+// deeper look-ahead then wins over a third round that is mostly empty.  Measured (us, two stages /
+// three): 976 items of 14 tiles 45.3 / 42.4, 1012 of 28 tiles 102.5 / 91.4; up to 520 items two
+// are better, 512 of 10 tiles 25.1 / 32.0, 520 of 8 tiles (four layers) 68.7 / 82.8, 320 of 4
+// tiles 15.3 / 16.1.  The plain call over the same rows is not faster with three.
 template <bool FUSED>
-void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool pack, dim3 grid, const AttnParams& p,
+void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool crowded, dim3 grid, const AttnParams& p,
                    hipStream_t stream) {
 #define EFIM_ATTN_LAUNCH2(DD, F8, KP, P8)                                                             \
   do {                                                                                             \
     if (wide) extend_attention_kernel<DD, 8, 3, FUSED, F8, KP, false, P8><<<grid, 512, 0, stream>>>(p); \
-    else extend_attention_kernel<DD, 4, F8 || (FUSED && DD == 64) ? 3 : 2, FUSED, F8, KP, false, P8><<<grid, 256, 0, stream>>>(p); \
+    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, FUSED, F8, KP, false, P8><<<grid, 256, 0, stream>>>(p); \
   } while (0)
 #define EFIM_ATTN_LAUNCH(DD, F8, P8)                                           \
   do {                                                                         \
@@ -1450,8 +1453,13 @@ void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool pack, 
     else if (few_rows) EFIM_ATTN_LAUNCH2(DD, F8, true, P8);                     \
     else EFIM_ATTN_LAUNCH2(DD, F8, FUSED, P8);                                   \
   } while (0)
-  if constexpr (!FUSED) {
-    if (pack && head_dim == 64 && !fp8 && !few_rows) {
+  if constexpr (FUSED) {
+    if (crowded && head_dim == 64 && !fp8 && !wide) {
+      extend_attention_kernel<64, 4, 3, true, false, true><<<grid, 256, 0, stream>>>(p);
+      return;
+    }
+  } else {
+    if (crowded && head_dim == 64 && !fp8 && !few_rows) {
       if (wide) extend_attention_kernel<64, 8, 3, false, false, false, true><<<grid, 512, 0, stream>>>(p);
       else extend_attention_kernel<64, 4, 2, false, false, false, true><<<grid, 256, 0, stream>>>(p);
       return;
@@ -1507,7 +1515,7 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, plan.pack, grid, p, stream);
+  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, plan.crowded, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
@@ -1541,7 +1549,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<true>(D, wide, fmt.fp8, true, false, grid, p, stream);
+  launch_kernel<true>(D, wide, fmt.fp8, true, plan.crowded, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }

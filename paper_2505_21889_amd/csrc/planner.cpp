@@ -229,7 +229,7 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   }
   plan->num_partial_slots = slot;
 
-  // Head dim 64, bf16 cache, many rows: there are two forms of the kernel, one that leaves room for
+  // Head dim 64, bf16 cache.  Many rows: there are two forms of the kernel, one that leaves room for
   // another 8-wave workgroup on its compute unit (a fourth 4-wave one) and one that runs 2-4 %
   // faster where there is none.  Two on a unit do about 1.15 times the work of one, but either
   // then runs at little more than half speed, and a long one that started late ends late.
@@ -240,11 +240,11 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   // tiles, longest 1.4 times an even share 193 / 170, 660 (1.6 times; 4 heads, full misses) 108 /
   // 105, 592 (1.8 times) 98 / 101, 516 (2.0 times) 88 / 97.  Four waves: with up to three items per
   // unit the fourth place stays empty, 488..572 items 1-7 % slower packed; 950..1050 items 6-11 %
-  // faster, 1280 equal.
+  // faster, 1280 equal.  (The short step chooses its number of stages at the same line.)
   if (b->head_dim == 64) {
     const size_t units = (size_t)std::max(1, M == 256 ? num_slots : num_slots / 2), n = pend.size();
     if (M != 256) {
-      plan->pack = n > 3 * units;
+      plan->crowded = n > 3 * units;
     } else if (n > units) {
       constexpr double kTwo = 1.15;
       std::vector<int64_t> cost;
@@ -256,7 +256,7 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
       }
       std::sort(cost.begin(), cost.end(), std::greater<int64_t>());
       if (n > 2 * units) {
-        plan->pack = (double)cost[0] * (double)(2 * units) < 1.7 * (double)total;
+        plan->crowded = (double)cost[0] * (double)(2 * units) < 1.7 * (double)total;
       } else {
         double paired = 0;
         std::vector<int64_t> load(cost.begin(), cost.begin() + units);  // ends as a min-heap
@@ -270,7 +270,7 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
           load.back() += cost[i];
           std::push_heap(load.begin(), load.end(), std::greater<int64_t>());
         }
-        plan->pack = paired < (double)*std::max_element(load.begin(), load.end());
+        plan->crowded = paired < (double)*std::max_element(load.begin(), load.end());
       }
     }
   }

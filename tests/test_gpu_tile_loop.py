@@ -346,3 +346,34 @@ def test_growing_scores_through_split_ranges_and_codes(E, row_tile, d, cache, sp
         E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
     U.assert_close(got, ref, large_outputs=True)
+
+
+@pytest.mark.parametrize("page", [8, 16, 256])
+@pytest.mark.parametrize("split", [0, 64, 128])
+def test_short_step_with_two_and_with_three_stages(E, page, split):
+    """Head dim 64, bf16 cache, 128-row tiles: the short step takes a third stage when there are many work
+    items for the compute units (here: told that there is one unit).  Ranges of 1 .. 11 tiles; the same bits
+    and the same cache, against the oracle too."""
+    from test_gpu_decode import oracle_step, run_decode
+    new = [1, 2, 7, 8, 5, 3, 8, 4]
+    ends = [1, 9, 64, 65, 129, 200, 321, 700]
+    cached = [max(0, e - n) for e, n in zip(ends, new)]
+    b = W.make_batch("c1", seed=4990 + page, heads=(8, 2), head_dim=64, page_size=page,
+                     lengths=(np.array(cached, dtype=np.int32), np.array(new, dtype=np.int32)))
+    kc, vc = U.oracle_cache(b)
+    _, kc_ref, vc_ref, ref = oracle_step(b, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 128)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+    got = []
+    try:
+        for slots in (0, 2):
+            E.efim_set_tuning(E.EFIM_TUNE_NUM_SLOTS, slots)
+            out, kc_got, vc_got, _ = run_decode(E, b, kc, vc)
+            assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+            got.append(out)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+        E.efim_set_tuning(E.EFIM_TUNE_NUM_SLOTS, 0)
+    assert np.array_equal(got[0], got[1])
+    U.assert_close(got[0], ref, large_outputs=True)
