@@ -748,7 +748,8 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // eight each: there the vector pipe is the longer one and the matrix pipe hides behind it.
   // Against tiles worked off one phase after the other (scores, softmax, values): 28/4-head step
   // with 8..64 new tokens 131.1 -> 124.6 us (8-bit cache 127.6 -> 121.9 us), 4 x 512 new tokens
-  // behind 16384 502 -> 491 us.
+  // behind 16384 502 -> 491 us.  Ranges of three to five tiles are too short for it: 28/4 heads, 104
+  // items of 3-4 tiles over four layers 79 -> 82 us.
   u32x4 p0[2], p1[2];  // probabilities of an even / odd half as B operands (bf16)
   f32x16 s0, s1;       // raw scores of an even / odd half
   // The reference of a row that has seen no score above minus infinity: so low that any finite
