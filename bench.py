@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 # on: the digest of extend_attention.hip is recorded with it and checked at run time.
 MEASURED_TRAFFIC = {
     # workload: (bytes per launch, sha256 of csrc/extend_attention.hip when measured)
-    "c5": (2586449093, "670040b0231dcd4819c4ba31518c52aebdefded2f1c99ae12c236741e673c4eb"),
+    "c5": (2592539813, "e4dbfe00f0f2fe60b3623cfb333e51a3cd3566a3f832f3c4825bd3e205303c57"),
 }
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak
@@ -433,9 +433,10 @@ def measure_ceilings(torch, E, reps=7):
         "mfma_TFLOPs": round(flops / t_mfma / 1e12, 1), "mfma_frac_of_peak": round(flops / t_mfma / 1e12 / PEAK_BF16_TFLOPS, 4),
         "read_GBps": round(size / t_read / 1e9, 1), "read_frac_of_peak": round(size / t_read / 1e9 / PEAK_HBM_GBPS, 4),
         "copy_GBps": round(2 * size / t_copy / 1e9, 1), "copy_frac_of_peak": round(2 * size / t_copy / 1e9 / PEAK_HBM_GBPS, 4),
-        # what the tile loop's structure (eight waves of 32 rows, 64-key tiles, a barrier per tile)
-        # reaches as its ingredients are added: MFMAs alone, + K / V^T operands from LDS, + the
-        # softmax arithmetic, + the direct-to-LDS loads of the next tiles
+        # what a tile loop that works one phase after the other (eight waves of 32 rows, 64-key tiles, a
+        # barrier per tile) reaches as its ingredients are added: MFMAs alone, + K / V^T operands from
+        # LDS, + the softmax arithmetic, + the direct-to-LDS loads of the next tiles.  The attention
+        # kernel's loop overlaps these phases: only the first two are upper bounds for it
         "tile_loop": tile_loop,
         "what": "libefim_ceilings.so: v_mfma_f32_32x32x16_bf16 from registers (2 waves per SIMD, %d workgroups, N(0,1) "
                 "operands); streaming read of 2 GiB; streaming copy of 2 GiB (read + written bytes); tile_loop: %d workgroups "
