@@ -7,13 +7,17 @@
 //                           matrix cores draw, and with it the clock, depends on the values)
 //   efim_ceiling_read       streaming read of a buffer, 16 bytes per lane
 //   efim_ceiling_copy       streaming read + write
-//   efim_ceiling_tile_loop  the ingredients of the attention kernel's tile loop added one at a time,
+//   efim_ceiling_tile_loop  the ingredients of an attention tile loop added one at a time,
 //                           on fixed data and with nothing else around them: (0) the 32 MFMAs per
 //                           wave and 64-key tile alone, (1) with their K / V^T operands read from
 //                           LDS as the kernel reads them, (2) plus the softmax arithmetic between
 //                           the two products, (3) plus this wave's four 1 KB direct-to-LDS loads
-//                           per tile.  Eight waves of 32 rows, a workgroup barrier per tile: what
-//                           this loop structure can reach before any paging, masking or planning.
+//                           per tile.  Eight waves of 32 rows, a workgroup barrier per tile, one
+//                           phase after the other (scores, softmax with a running maximum,
+//                           values): what THIS structure can reach before any paging, masking or
+//                           planning.  The attention kernel's own loop overlaps the three phases on
+//                           32-key halves and forms no running maximum, so modes 2 and 3 are no
+//                           upper bound for it.
 #include <hip/hip_runtime.h>
 
 #include <cstddef>
