@@ -346,8 +346,8 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // PACK (head dim 64, bf16 cache, many rows): the same for the pipelined kernel, whose plain form
 // takes 149 registers (four waves: 151).  With the value product in front of the score product in
 // every phase, two key operands in flight instead of four and operand addresses derived from one
-// register each it fits 128 (four waves: with two spilled, outside the loop).  Either form does
-// the same arithmetic; Plan::crowded chooses.
+// register each it fits 128 without a spill.  Either form does the same arithmetic; Plan::crowded
+// chooses.
 constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bool pack) {
   return pack || (d == 64 && kp && !kv8 && (!fused || waves == 8)) ? 4 : 2;
 }
@@ -1283,7 +1283,16 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     if (row_ok) {
       if (it.partial_slot < 0) {
         const float inv = p.out_scale / l_tot;
-        uint16_t* dst = p.out + q_off;
+        int64_t out_off = q_off;
+        if constexpr (PACK) {
+          // formed again (the empty statement hides that it is known): held across the loop it
+          // would be spilled
+          int r = row;
+          asm volatile("" : "+v"(r));
+          const int t = r / g;
+          out_off = ((int64_t)(rq.row_start + t) * p.num_q_heads + it.kv_head * g + (r - t * g)) * D;
+        }
+        uint16_t* dst = p.out + out_off;
 #pragma unroll
         for (int d = 0; d < G::kDBlocks; ++d)
 #pragma unroll
