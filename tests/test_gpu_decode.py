@@ -144,6 +144,36 @@ def test_short_step_in_the_eight_wave_configuration(E, name, cached, new, heads,
         E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
 
 
+@pytest.mark.parametrize("row_tile", [128, 256])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [(4, 4), (8, 4), (6, 1)])
+def test_rows_of_an_item_at_the_edges_of_the_write_out(E, heads, d, row_tile):
+    """1 .. 32 query rows per item (the write-out takes 8, 16 or 32 rows at a time), written directly and as
+    parts, the parts combined in either way."""
+    g = heads[0] // heads[1]
+    n = np.array([t for t in (1, 2, 4, 5, 8, 9, 15, 16) if t * g <= 32], dtype=np.int32)
+    c = np.array([70 + 33 * i for i in range(len(n))], dtype=np.int32)
+    b = W.make_batch("c1", seed=190 + d + g, lengths=(c, n), heads=heads, head_dim=d)
+    kc, vc = U.oracle_cache(b)
+    _, kc_ref, vc_ref, ref = oracle_step(b, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    try:
+        for split in (0, 64):
+            outs = []
+            for fused in (0, 1):
+                E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+                E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, fused)
+                got, kc_got, vc_got, _ = run_decode(E, b, kc, vc)
+                assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+                U.assert_close(got, ref, "split %d merge %d" % (split, fused))
+                outs.append(got)
+            assert np.array_equal(outs[0], outs[1])
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+        E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, -1)
+
+
 @pytest.mark.parametrize("page_size", [8, 256])
 def test_short_step_other_page_sizes(E, page_size):
     c = np.array([0, 7, 8, 60, 64, 250, 256, 1000, 2049], dtype=np.int32)
