@@ -15,6 +15,8 @@ constexpr int kMinPageSize = 8;       // tokens per KV page: a power of two in t
 constexpr int kMaxPageSize = 256;
 constexpr int kKeyTile = 64;          // keys staged in LDS per main-loop iteration
 constexpr int kWavesPerGroup = 4;     // wavefronts per attention workgroup
+// key tiles that the kernel which gathers a whole key range at the start of an item holds (128 KB of bf16 rows)
+constexpr int once_tiles(int head_dim) { return head_dim == 128 ? 4 : 8; }
 constexpr int kMaxRowsPerItem = 256;  // largest query-row tile of one workgroup
 constexpr int kStageSlots = 64;       // launch tokens in turn: a token comes round again after this many calls
 constexpr int kTicketSlots = kStageSlots;
@@ -71,6 +73,7 @@ struct Plan {
   int rows_per_item = 128;  // query rows per workgroup tile (32 per wave)
   int max_item_rows = 0;    // largest row_count of a work item
   int partial_rows = 128;   // rows per partial-result slot of a split key range
+  bool once = false;        // few work items of few rows, each short enough for the kernel that gathers a whole range at once
   bool crowded = false;     // head dim 64: work items crowd the compute units (other forms of the bf16 kernels)
   std::vector<ReqInfo> reqs;
   std::vector<WorkItem> items;

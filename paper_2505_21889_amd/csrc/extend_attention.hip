@@ -370,8 +370,17 @@ constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bo
 }
 //
 // P8: 64-byte code rows on pages of 8, the one layout whose 1 KB load spans two pages.
-template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false>
-__global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(const AttnParams p) {
+//
+// ONCE (key parallel, eight waves): for launches with at most one work item per compute unit, whose
+// ranges fit the tile buffers whole (Plan::once).  Such a launch is bound by latency: with a ring
+// of two or three buffers and two waves at work the tiles of an item pass one behind the other at
+// 0.8 us each.  Here all of them are gathered at the start, each pair of waves takes tiles of its own,
+// and the eight waves' sums are combined at the end.  One request of 1000 keys, 32/8 heads 12.2 -> 10.4
+// us, 16 requests of 250 keys 10.2 -> 8.2 us, four requests of 300 + 32 tokens, 4 heads of 64, two
+// calls 16.8 -> 11.2 us.
+template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false, bool ONCE = false>
+__global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(const AttnParams p) {
+  static_assert(!ONCE || (KP && WAVES == 8 && STAGES == once_tiles(D) && !P8), "the form for few work items");
   static_assert(!PACK || (D == 64 && !KV8 && !KP), "the packed form is for head dim 64, bf16, many rows");
   static_assert(!P8 || (D == 64 && KV8), "other rows are longer");
   static_assert(KP || !FUSED, "the decode step has at most 32 rows per tile");
@@ -406,9 +415,18 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
   // (8-bit caches: the raw bf16 rows of the new tokens have an area of their own behind that)
   constexpr int kFusedRawBytes = FUSED && KV8 ? kFusedMaxTokens * 2 * 2 * D : 0;
   constexpr int kFusedBytes = FUSED ? kFusedRows * D * 2 + kFusedMaxTokens * 2 * kGRowBytes + kFusedRawBytes : 0;
-  static_assert(STAGES >= 2 && kTileBufBytes + kFusedBytes <= 160 * 1024, "stages must fit the 160 KB LDS");
+  // cosines and sines of the new tokens' positions: in the tile buffer that is filled last, or, where
+  // all are filled at the start, behind everything else
+  constexpr int kTableBytes = FUSED && ONCE ? kFusedMaxTokens * (D / 2) * 16 : 0;
+  // key-parallel kernels: where the waves that share the rows leave their sums at the end
+  constexpr int kSharers = ONCE ? WAVES : 2;
+  constexpr int kPitch = D + 4;  // floats from row to row: 16 bytes on, so that 16 rows spread over all banks
+  constexpr int kExchangeBytes = KP ? kSharers * 32 * (kPitch + 3) * 4 : 0;
+  constexpr int kBufBytes = kTileBufBytes + kFusedBytes + kTableBytes;
+  constexpr int kLdsBytes = kBufBytes > kExchangeBytes ? kBufBytes : kExchangeBytes;
+  static_assert(STAGES >= 2 && kLdsBytes <= 160 * 1024, "stages must fit the 160 KB LDS");
   // One array, carved by hand.
-  __shared__ __attribute__((aligned(1024))) char lds[kTileBufBytes + kFusedBytes];
+  __shared__ __attribute__((aligned(1024))) char lds[kLdsBytes];
   char* const stages = lds;
   uint16_t* const s_q = reinterpret_cast<uint16_t*>(lds + kTileBufBytes);
   char* const s_kv = reinterpret_cast<char*>(s_q + kFusedRows * D);  // token j: key row at j * 2 * kGRowBytes, value row behind it
@@ -542,12 +560,12 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     const char* vc = reinterpret_cast<const char*>(p.v_cache);
     // (not in the eight-wave key-parallel kernel over bf16 caches: measured 1.5-2.5 % slower there
     // -- that kernel is bound by HBM alone, and its loads do better spaced out)
-    constexpr bool kGroupedIssue = !(KP && WAVES == 8 && !KV8);
+    constexpr bool kGroupedIssue = !(KP && WAVES == 8 && !KV8) || ONCE;
     // The key-parallel kernel of the plain call takes the last tile of a range the same way: through
     // the general path below it waits for a page lookup in front of each load, one behind the
     // other (one request of 256 + 32 tokens, 4 heads: 7.7 -> 7.2 us).  The other kernels have
     // no registers for it (the decode step spilled: 13.3 -> 13.7 us) or longer ranges.
-    constexpr bool kGroupedLast = KP && !FUSED;
+    constexpr bool kGroupedLast = KP && (!FUSED || ONCE);
     // P8: both page ids of a load come by scalar loads, all of the wave's together, and a lane picks
     // its page's; looked up lane by lane the ids wait on the counter of the gathers and drain the
     // tiles in flight.  64 requests of 4000..7000 + 1..8 tokens, 32/8 heads 116.3 -> 97.5 us.  (A
@@ -1006,7 +1024,7 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
   };
-  static_assert(STAGES <= 3, "wait_tile and the loops below handle two tiles in flight");
+  static_assert(STAGES <= 3 || ONCE, "wait_tile and the loops below handle two tiles in flight");
 
   // Pipelined kernels: stage t of the ring holds the keys of tile t and the values of tile t - 1
   // (a tile's scores are formed one tile ahead of its value product); stages 0 .. ntiles.  Each
@@ -1048,9 +1066,18 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       load_to_lds_16(src, dst);
     }
   }
+  if constexpr (ONCE) {
+    TilePages pages[STAGES];  // of all tiles together: one latency
 #pragma unroll
-  for (int st = 0; st < STAGES - 1; ++st)
-    if (st >= shift && st <= last_stage) issue_tile(st - shift, st, fetch_pages(st - shift));
+    for (int st = 0; st < STAGES; ++st) pages[st] = fetch_pages(min(st, ntiles - 1));
+#pragma unroll
+    for (int st = 0; st < STAGES; ++st)
+      if (st < ntiles) issue_tile(st, st, pages[st]);
+  } else {
+#pragma unroll
+    for (int st = 0; st < STAGES - 1; ++st)
+      if (st >= shift && st <= last_stage) issue_tile(st - shift, st, fetch_pages(st - shift));
+  }
   // Everything the compiler knows to be loading (the query operands) must have landed before
   // the main loop: inside it the only outstanding vector-memory operations are the gathers,
   // which are awaited by hand.  (vmcnt(0), expcnt/lgkmcnt untouched; the gathers just issued
@@ -1063,8 +1090,9 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     // into the tile buffer that no gather has been issued into yet (the last one), while the raw
     // rows are on their way; then one task per (row, pair) over the query rows and the key rows.
     const int rot_half = p.rotary_dim / 2;  // pairs per head row (D/2 when the whole row rotates)
-    double* const s_cs = reinterpret_cast<double*>(stages + (STAGES - 1) * kStageBytes);  // [token][pair] (cos, sin)
-    static_assert(kFusedMaxTokens * (D / 2) * 16 <= kStageBytes, "the cos/sin table must fit one tile buffer");
+    double* const s_cs =  // [token][pair] (cos, sin)
+        reinterpret_cast<double*>(ONCE ? lds + kTileBufBytes + kFusedBytes : stages + (STAGES - 1) * kStageBytes);
+    static_assert(kFusedMaxTokens * (D / 2) * 16 <= (ONCE ? kTableBytes : kStageBytes), "the cos/sin table must fit");
     {
       const int j = tid % (D / 2);
       if (j < rot_half)
@@ -1076,8 +1104,17 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
         }
     }
     // this wave's raw rows have landed; the gathers issued behind them stay in flight
-    static_assert(2 * kLoadsPerWave <= 63, "the wait counts up to two tiles");
-    if (issuer < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    static_assert((ONCE ? STAGES : 2) * kLoadsPerWave <= 63, "the wait counts that many tiles");
+    if constexpr (ONCE) {
+#define EFIM_WAIT_TILES(N) \
+  case N: asm volatile("s_waitcnt vmcnt(%0)" ::"n"((N) <= STAGES ? (N) * kLoadsPerWave : 0) : "memory"); break;
+      switch (ntiles) {
+        EFIM_WAIT_TILES(1) EFIM_WAIT_TILES(2) EFIM_WAIT_TILES(3) EFIM_WAIT_TILES(4)
+        EFIM_WAIT_TILES(5) EFIM_WAIT_TILES(6) EFIM_WAIT_TILES(7) EFIM_WAIT_TILES(8)
+        default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+#undef EFIM_WAIT_TILES
+    } else if (issuer < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     else if (STAGES >= 3 && ntiles >= 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * kLoadsPerWave) : "memory");
     else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLoadsPerWave) : "memory");
     __syncthreads();
@@ -1119,6 +1156,37 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
       qb[s] = __builtin_bit_cast(bf16x8, v);
     }
   }
+  // Fused step.  Key tiles that reach into the new tokens: their cache slots have not been written
+  // yet, so those rows of the landed tile are replaced by the rotated keys / the values
+  // from LDS, and the tokens are appended to the paged cache (each position by the one
+  // workgroup of its kv head whose key range holds it).  Rows behind the key range,
+  // which the gather fetched from the range's last slot, take that token's rows too.
+  // True: the tile in buffer `slot` has been written to.
+  auto patch_tile = [&](int t, int slot) __attribute__((always_inline)) -> bool {
+    const int key0 = k_begin + t * kKeyTile;
+    if (k_end <= rq.cached || key0 + kKeyTile <= rq.cached) return false;
+    const int prow = max(rq.cached - key0, 0);  // first row of the tile that holds a new token
+    constexpr int kPerRow = 2 * kGChunks;  // 16-byte chunks of a key row and a value row
+    for (int u = tid; u < (kKeyTile - prow) * kPerRow; u += 64 * WAVES) {
+      const int row = prow + u / kPerRow;
+      const int w = u % kPerRow;
+      const bool is_v = w >= kGChunks;
+      const int c = is_v ? w - kGChunks : w;
+      const int pos = min(key0 + row, k_end - 1);
+      const u32x4 val = *reinterpret_cast<const u32x4*>(s_kv + (pos - rq.cached) * 2 * kGRowBytes +
+                                                        (is_v ? kGRowBytes : 0) + c * 16);
+      const int swz = KV8 ? (is_v ? vswz8(row) : kswz8(row)) : (is_v ? G::vswz(row) : G::kswz(row));
+      char* tile = stages + slot * kStageBytes + (is_v ? kGTileBytes : 0);
+      *reinterpret_cast<u32x4*>(tile + row * kGRowBytes + ((c ^ swz) << 4)) = val;
+      if (key0 + row < k_end) {
+        const int64_t page = bt[pos >> ps];
+        char* cache = reinterpret_cast<char*>(is_v ? p.v_cache_w : p.k_cache_w);
+        *reinterpret_cast<u32x4*>(
+            cache + (((page * p.num_kv_heads + it.kv_head) << ps) + (pos & page_mask)) * kGRowBytes + c * 16) = val;
+      }
+    }
+    return true;
+  };
   // One tile of the unrolled ring: stage s0 (a compile-time constant) holds tile t0 + s0.
   auto ring_step = [&](int t0, auto s0_c) __attribute__((always_inline)) {
     constexpr int s0 = decltype(s0_c)::value;
@@ -1131,42 +1199,28 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
         wait_tile(t, ntiles - 1);
         if (t + kAhead < ntiles) issue_tile(t + kAhead, sl, pages);
         if constexpr (FUSED) {
-          // Key tiles that reach into the new tokens: their cache slots have not been written
-          // yet, so those rows of the landed tile are replaced by the rotated keys / the values
-          // from LDS, and the tokens are appended to the paged cache (each position by the one
-          // workgroup of its kv head whose key range holds it).  Rows behind the key range,
-          // which the gather fetched from the range's last slot, take that token's rows too.
-          const int key0 = k_begin + t * kKeyTile;
-          if (k_end > rq.cached && key0 + kKeyTile > rq.cached) {
-            const int prow = max(rq.cached - key0, 0);  // first row of the tile that holds a new token
-            constexpr int kPerRow = 2 * kGChunks;  // 16-byte chunks of a key row and a value row
-            for (int u = tid; u < (kKeyTile - prow) * kPerRow; u += 64 * WAVES) {
-              const int row = prow + u / kPerRow;
-              const int w = u % kPerRow;
-              const bool is_v = w >= kGChunks;
-              const int c = is_v ? w - kGChunks : w;
-              const int pos = min(key0 + row, k_end - 1);
-              const u32x4 val = *reinterpret_cast<const u32x4*>(s_kv + (pos - rq.cached) * 2 * kGRowBytes +
-                                                                (is_v ? kGRowBytes : 0) + c * 16);
-              const int swz = KV8 ? (is_v ? vswz8(row) : kswz8(row)) : (is_v ? G::vswz(row) : G::kswz(row));
-              char* tile = stages + s0 * kStageBytes + (is_v ? kGTileBytes : 0);
-              *reinterpret_cast<u32x4*>(tile + row * kGRowBytes + ((c ^ swz) << 4)) = val;
-              if (key0 + row < k_end) {
-                const int64_t page = bt[pos >> ps];
-                char* cache = reinterpret_cast<char*>(is_v ? p.v_cache_w : p.k_cache_w);
-                *reinterpret_cast<u32x4*>(
-                    cache + (((page * p.num_kv_heads + it.kv_head) << ps) + (pos & page_mask)) * kGRowBytes + c * 16) = val;
-              }
-            }
-            __syncthreads();
-          }
+          if (patch_tile(t, s0)) __syncthreads();
         }
         // (tile 0 is always the first of the unrolled copies)
         step(t, s0 * kSlotBytes, std::bool_constant<s0 == 0>{});
       }
     }
   };
-  if constexpr (KP) {
+  if constexpr (ONCE) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if constexpr (FUSED) {
+      bool patched = false;
+      for (int t = max(0, rq.cached - k_begin) / kKeyTile; t < ntiles; ++t) patched |= patch_tile(t, t);
+      if (patched) __syncthreads();
+    }
+    const int half = wave & 1;
+    for (int t = wave >> 1; t < ntiles; t += WAVES / 2)
+      if (k_begin + t * kKeyTile + half * 32 < wave_max_vis) {
+        compute_half(t, t * kSlotBytes, half, std::false_type{});
+        if (fine_wave && t == 0 && half == 0) compute_half(t, 0u, 0, std::true_type{});
+      }
+  } else if constexpr (KP) {
     for (int t0 = 0; t0 < ntiles; t0 += STAGES) {
       ring_step(t0, std::integral_constant<int, 0>{});
       ring_step(t0, std::integral_constant<int, 1>{});
@@ -1256,13 +1310,10 @@ __global__ __launch_bounds__(64 * WAVES, waves_per_simd(D, WAVES, FUSED, KV8, KP
     // depend on how each variant of the kernel is scheduled, and the variants must agree bit
     // for bit)
 #pragma clang fp contract(off)
-    constexpr int kSharers = 2;      // waves with sums of their own
-    constexpr int kPitch = D + 4;    // floats from row to row: 16 bytes on, so that 16 rows spread over all banks
-    constexpr int kVec = D / 4;      // threads per row
+    constexpr int kVec = D / 4;  // threads per row
     float* xo = reinterpret_cast<float*>(lds);    // [sharer][32 rows] x kPitch
     float* xm = xo + kSharers * 32 * kPitch;      // [sharer][32 rows]
     float* xl = xm + kSharers * 32;               // [sharer][32 rows][2 halves of the wave]
-    static_assert((kSharers * 32 * (kPitch + 3)) * 4 <= kTileBufBytes, "the exchange area must fit the tile buffers");
     __syncthreads();  // every wave is done with the tiles
     if (wave < kSharers && row_ok) {
       float* mine = xo + (wave * 32 + i32) * kPitch + hi * 4;
@@ -1530,7 +1581,7 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 // are better, 512 of 10 tiles 25.1 / 32.0, 520 of 8 tiles (four layers) 68.7 / 82.8, 320 of 4
 // tiles 15.3 / 16.1.  The plain call over the same rows is not faster with three.
 template <bool FUSED>
-void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool crowded, dim3 grid, const AttnParams& p,
+void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool crowded, bool once, dim3 grid, const AttnParams& p,
                    hipStream_t stream) {
 #define EFIM_ATTN_LAUNCH2(DD, F8, KP, P8)                                                             \
   do {                                                                                             \
@@ -1543,6 +1594,17 @@ void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool crowde
     else if (few_rows) EFIM_ATTN_LAUNCH2(DD, F8, true, P8);                     \
     else EFIM_ATTN_LAUNCH2(DD, F8, FUSED, P8);                                   \
   } while (0)
+  if (once && !(fp8 && head_dim == 64 && p.page_shift == 3)) {
+#define EFIM_ATTN_ONCE(DD, F8) \
+  extend_attention_kernel<DD, 8, once_tiles(DD), FUSED, F8, true, false, false, true><<<grid, 512, 0, stream>>>(p)
+    if (head_dim == 128) {
+      if (fp8) EFIM_ATTN_ONCE(128, true); else EFIM_ATTN_ONCE(128, false);
+    } else {
+      if (fp8) EFIM_ATTN_ONCE(64, true); else EFIM_ATTN_ONCE(64, false);
+    }
+#undef EFIM_ATTN_ONCE
+    return;
+  }
   if constexpr (FUSED) {
     if (crowded && head_dim == 64 && !fp8 && !wide) {
       extend_attention_kernel<64, 4, 3, true, false, true><<<grid, 256, 0, stream>>>(p);
@@ -1605,7 +1667,7 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, plan.crowded, grid, p, stream);
+  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, plan.crowded, plan.once, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
@@ -1639,7 +1701,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<true>(D, wide, fmt.fp8, true, plan.crowded, grid, p, stream);
+  launch_kernel<true>(D, wide, fmt.fp8, true, plan.crowded, plan.once, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }

@@ -174,6 +174,33 @@ def test_rows_of_an_item_at_the_edges_of_the_write_out(E, heads, d, row_tile):
         E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, -1)
 
 
+@pytest.mark.parametrize("page_size", [8, 16, 256])
+@pytest.mark.parametrize("heads,d", [((8, 2), 128), ((4, 4), 128), ((8, 2), 64)])
+def test_ranges_gathered_at_once(E, heads, d, page_size):
+    """Few items of few rows: key ranges of one tile up to all that the buffers hold, one key more (a split range),
+    ends just in front of, on and behind tile edges, new tokens in one tile, over an edge and over a
+    split; in one call and as two calls, over bf16 rows and codes."""
+    from test_gpu_fp8 import oracle_cache8, oracle_step8, run_decode8
+    most = 64 * (4 if d == 128 else 8)
+    ends = [1, 5, 64, 65, 130, most - 60, most - 1, most, most + 1, 2 * most + 3]
+    n = [1, 5, 3, 4, 8, 2, 7, 8, 4, 8]
+    c = np.array([e - k for e, k in zip(ends, n)], dtype=np.int32)
+    n = np.array(n, dtype=np.int32)
+    b = W.make_batch("c1", seed=210 + d + page_size, lengths=(c, n), heads=heads, head_dim=d, page_size=page_size)
+    kc, vc = U.oracle_cache(b)
+    _, kc_ref, vc_ref, ref = oracle_step(b, kc, vc)
+    got, kc_got, vc_got, _ = run_decode(E, b, kc, vc)
+    assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+    U.assert_close(got, ref, large_outputs=True)
+    assert np.array_equal(got, two_call_path(E, b, kc, vc))
+    k_scale, v_scale = 0.0123, 0.031
+    kc, vc = oracle_cache8(b, k_scale, v_scale)
+    _, kc_ref, vc_ref, ref = oracle_step8(b, kc, vc, k_scale, v_scale)
+    got, kc_got, vc_got, _ = run_decode8(E, b, kc, vc, k_scale, v_scale)
+    assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+    U.assert_close(got, ref, large_outputs=True)
+
+
 @pytest.mark.parametrize("page_size", [8, 256])
 def test_short_step_other_page_sizes(E, page_size):
     c = np.array([0, 7, 8, 60, 64, 250, 256, 1000, 2049], dtype=np.int32)

@@ -320,3 +320,19 @@ def test_plan_objects_on_the_host():
     # an empty batch plans to nothing and uploads nothing
     empty = E.Plan(_desc([5, 6], [0, 0]))
     E.efim_plan_upload(empty, FAKE_DEV + 0 if FAKE_DEV % 256 == 0 else (FAKE_DEV // 256 + 1) * 256, E.efim_plan_workspace_bytes(empty))
+
+
+@pytest.mark.parametrize("d,most", [(128, 4), (64, 8)])
+@pytest.mark.parametrize("lengths", [[1], [64 * 4], [2344], [64 * 9 + 1, 3], [8000], [100] * 16, [64 * 16] * 4])
+def test_short_steps_of_few_tiles_are_cut_into_ranges_that_fit_the_buffers(d, most, lengths):
+    """Few rows and few tiles: one item per compute unit at most (256 without a device), none longer than the
+    kernel that gathers a whole range at once holds; every key in one item."""
+    items = E.efim_extend_plan_items(_desc([x - 1 for x in lengths], [1] * len(lengths), hq=8, hkv=4, d=d))
+    items = items[items["row_count"] > 0]
+    assert len(items) <= 256
+    tiles = -(-(items["key_end"] - items["key_begin"]) // 64)
+    assert tiles.max() <= most and tiles.min() >= 1
+    for r, x in enumerate(lengths):
+        for h in range(4):
+            mine = items[(items["req"] == r) & (items["kv_head"] == h)]
+            assert (mine["key_end"] - mine["key_begin"]).sum() == x
