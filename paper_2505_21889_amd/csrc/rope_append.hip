@@ -108,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void rope_append_kernel(
   const int units_per_tok = rows_per_tok * UNITS_PER_ROW;
   const int ntok = min(kTokens, end_row - tok0);
   for (int u = tid; u < ntok * units_per_tok; u += kThreads) {
-    const int tt = u / units_per_tok;
+    const int tt = kTokens == 1 ? 0 : u / units_per_tok;  // (the division was 2-3 % of a one-token launch)
     const int w = u - tt * units_per_tok;
     const int hr = w / UNITS_PER_ROW;   // 0..Hq-1: q heads, then Hkv k heads, then Hkv v heads
     const int cp = w - hr * UNITS_PER_ROW;
