@@ -119,6 +119,15 @@ __device__ __forceinline__ float cross_half_max(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// the same between neighbouring quarters (16 lanes) of a wave
+__device__ __forceinline__ float cross_quarter_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float cross_quarter_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 __device__ __forceinline__ float cross_half_sum(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
@@ -134,10 +143,7 @@ __device__ __forceinline__ float row_lanes_max(float v) {
   v = fmaxf(v, with(std::integral_constant<int, 0x4E>{}));   // quad_perm [2, 3, 0, 1]
   v = fmaxf(v, with(std::integral_constant<int, 0x141>{}));  // row_half_mirror
   v = fmaxf(v, with(std::integral_constant<int, 0x140>{}));  // row_mirror
-  if constexpr (N == 32) {
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  }
+  if constexpr (N == 32) v = cross_quarter_max(v);
   return v;
 }
 
@@ -378,11 +384,18 @@ constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bo
 // and the eight waves' sums are combined at the end.  One request of 1000 keys, 32/8 heads 12.2 -> 10.4
 // us, 16 requests of 250 keys 10.2 -> 8.2 us, four requests of 300 + 32 tokens, 4 heads of 64, two
 // calls 16.8 -> 11.2 us.
-template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false, bool ONCE = false>
+//
+// R16 (key parallel, no item has more than 16 query rows): products of 16 keys by 16 rows instead of 32 by
+// 32.  A 32 x 32 product over one to seven rows spends most of its time, of the softmax and of the
+// accumulators on columns that are no rows, and a short step is bound by that chain: one request
+// of 2344 keys, 32/8 heads 11.9 -> 11.2 us, 20 requests of 500..3000 keys, 32/32 heads 124.6 -> 118.4 us, 24
+// drawn steps 3.4 % in the mean, none slower.  With 17 to 32 rows it would take two column blocks.
+template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false, bool ONCE = false, bool R16 = false>
 __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(const AttnParams p) {
   static_assert(!ONCE || (KP && WAVES == 8 && STAGES == once_tiles(D) && !P8), "the form for few work items");
   static_assert(!PACK || (D == 64 && !KV8 && !KP), "the packed form is for head dim 64, bf16, many rows");
   static_assert(!P8 || (D == 64 && KV8), "other rows are longer");
+  static_assert(KP || !R16, "16 rows are one tile of the key-parallel kernels");
   static_assert(KP || !FUSED, "the decode step has at most 32 rows per tile");
   using G = Geometry<D>;
   // geometry of the gather: rows as they lie in the cache
@@ -403,9 +416,13 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   // of the key (D = 128; bits 1 and 3 for the 64-byte rows of D = 64, where two rows share a
   // bank cycle) tell those eight rows apart.
   auto kswz8 = [](int row) { return D == 128 ? (row & 7) : ((row >> 1) & 3); };
+  // R16: the block's rows are {0..3, 16..19} + 4 * block, two blocks at a time.
   auto vswz8 = [](int row) {
+    if constexpr (R16) return D == 128 ? (((row >> 1) & 3) | (((row >> 4) & 1) << 2)) : (((row >> 2) & 1) | (((row >> 4) & 1) << 1));
     return D == 128 ? ((row & 3) | (((row >> 3) & 1) << 2)) : (((row >> 1) & 1) | (((row >> 3) & 1) << 1));
   };
+  // bf16 value rows.  R16: two blocks of four keys at one 32-byte piece are read together
+  auto vswz16 = [](int row) { return R16 && D == 128 ? G::vswz(row) ^ (((row >> 2) & 1) << 1) : G::vswz(row); };
   // fused step: the rotated query rows of the tile, then per new token its rotated key and its
   // value as they go into the cache (bf16 rows or code rows) -- behind the tile buffers.  With
   // D = 128 that is 16 KB: two 4-wave workgroups with their 64 KB of tile buffers fill the 160 KB
@@ -458,7 +475,9 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   const int wave_row0 = KP ? 0 : wave * 32;
 
   // --- this lane's query row (column of S^T / O^T) ----------------------------------
-  const int local_row = wave_row0 + i32;
+  const int i16 = lane & 15;
+  const int q4 = lane >> 4;
+  const int local_row = R16 ? i16 : wave_row0 + i32;
   const bool row_ok = local_row < it.row_count;
   const int row = it.row_begin + local_row;
   const int tok = row / g;
@@ -475,12 +494,14 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
 
   // MFMA B operands of this lane's query row: read here for the plain kernel, after the first
   // gathers have been issued for the fused one (the rotation then overlaps their latency)
-  bf16x8 qb[G::kSteps];
+  constexpr int kQSteps = R16 ? D / 32 : G::kSteps;  // MFMA steps over the head dimension
+  const int q_at = R16 ? 8 * q4 : 8 * hi;            // this lane's eight elements of a step
+  bf16x8 qb[kQSteps];
   if constexpr (!FUSED) {
 #pragma unroll
-    for (int s = 0; s < G::kSteps; ++s) {
+    for (int s = 0; s < kQSteps; ++s) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (row_ok) v = *reinterpret_cast<const u32x4*>(p.q + q_off + 16 * s + 8 * hi);
+      if (row_ok) v = *reinterpret_cast<const u32x4*>(p.q + q_off + (D / kQSteps) * s + q_at);
       qb[s] = __builtin_bit_cast(bf16x8, v);
     }
   }
@@ -490,6 +511,9 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   for (int d = 0; d < G::kDBlocks; ++d)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
+  f32x4 o16[D / 16];        // R16: head-dim blocks of 16 instead
+#pragma unroll
+  for (int d = 0; d < D / 16; ++d) o16[d] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY;  // reference max of the scaled scores (log2 units)
   float l_run = 0.f;        // this lane's share of the running sum
 
@@ -625,7 +649,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
 #pragma unroll
             for (int q = 0; q < GS; ++q) {
               const int tile_row = (idx0 + j + q) * kGKeysPerLoad + g_key;
-              const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? G::vswz(tile_row) : G::kswz(tile_row));
+              const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? vswz16(tile_row) : G::kswz(tile_row));
               const int src = PART ? (min(tile_row, last_row) - row0) * kGRowBytes + kBias - q * 1024 : g_key * kGRowBytes;
               off[q] = (uint32_t)(src + ((g_pc ^ swz) << 4));
             }
@@ -653,7 +677,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
           for (int j = 0; j < kLoadsPerWave; ++j) {
             const int row0 = (idx0 + j) * kGKeysPerLoad;  // first tile row of this load
             const int tile_row = row0 + g_key;
-            const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? G::vswz(tile_row) : G::kswz(tile_row));
+            const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? vswz16(tile_row) : G::kswz(tile_row));
             const uint32_t in_page = (uint32_t)(key0 + row0) & (uint32_t)page_mask;
             if (j == 0 || in_page == 0) {
               const uint32_t page = page_of(first_off + t * kKeyTile + row0);
@@ -679,7 +703,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       const int idx = is_v ? load - kGLoadsPerMatrix : load;
       const int row0 = idx * kGKeysPerLoad;                    // first tile row of this load
       const int tile_row = row0 + g_key;
-      const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? G::vswz(tile_row) : G::kswz(tile_row));
+      const int swz = KV8 ? (is_v ? vswz8(tile_row) : kswz8(tile_row)) : (is_v ? vswz16(tile_row) : G::kswz(tile_row));
       if constexpr (kGKeysPerLoad <= kMinPageSize) {
         if (full_tile) {
           // all rows of the load lie in one page and inside the range
@@ -1004,14 +1028,101 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       }
   };
 
+  // R16.  S^T = K Q^T in two blocks of 16 keys: a lane has keys 16 * kb + 4 * q4 + r of the half and one query
+  // row, which is the order in which the value product takes its 32 keys from both operands: eight
+  // per lane, {0..3} + 4 * q4 of either block.
+  const int k16_swz = KV8 ? kswz8(i16) : G::kswz(i16);  // same for key i16 + 16, + 32, ...
+  const int v16_key = KV8 ? 4 * q4 + (v8_e < 4 ? v8_e : v8_e + 12) : 4 * q4 + (w16 >> 2);  // bf16: + 16 for the second block
+  const int v16_swz = KV8 ? vswz8(v16_key) : vswz16(v16_key);
+  auto compute_half16 = [&](int t, uint32_t buf, int half, auto lo_c) __attribute__((always_inline)) {
+    constexpr bool LO = decltype(lo_c)::value;
+    const int key0 = k_begin + t * kKeyTile + half * 32;
+    const uint32_t at = lds0 + buf + half * 32 * kGRowBytes;
+    KRaw ka[2][kQSteps];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int s = 0; s < kQSteps; ++s) {
+        const int chunk = KV8 ? 2 * s + (q4 >> 1) : 4 * s + q4;
+        ka[kb][s] = *reinterpret_cast<const LDS_PTR(KRaw)>(at + i16 * kGRowBytes + ((chunk ^ k16_swz) << 4) +
+                                                           (KV8 ? 8 * (q4 & 1) : 0) + kb * 16 * kGRowBytes);
+      }
+    f32x4 sc[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      sc[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < kQSteps; ++s)
+        sc[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(k_operand(ka[kb][s]), qb[s], sc[kb], 0, 0, 0);
+    }
+    VRaw va[D / 16];
+#pragma unroll
+    for (int d = 0; d < D / 16; ++d) {
+      const uint32_t v_at = at + kVOff + v16_key * kGRowBytes + v_sub;
+      if constexpr (KV8) {
+        va[d] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr8_b64_v2i32((LDS_PTR(i32x2))(v_at + ((d ^ v16_swz) << 4))));
+      } else {
+        const uint32_t c_at = v_at + (((2 * d + ((w16 & 3) >> 1)) ^ v16_swz) << 4);
+        const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_PTR(bf16x4))(c_at));
+        const bf16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((LDS_PTR(bf16x4))(c_at + 16 * kGRowBytes));
+        va[d] = __builtin_bit_cast(u32x4, __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+    }
+    if (key0 + 32 > wave_min_vis) {
+      const int lim = n_vis - key0 - q4 * 4;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (kb * 16 + r >= lim) sc[kb][r] = -INFINITY;
+    }
+    if constexpr (!LO) {
+      float tmax = max3(max3(sc[0][0], sc[0][1], sc[0][2]), sc[0][3], max3(sc[1][0], sc[1][1], sc[1][2]));
+      tmax = cross_half_max(cross_quarter_max(fmaxf(tmax, sc[1][3])));
+      const float m_new = tmax * p.scale_log2;
+      const bool grow = m_new > m_run + kSlack;
+      if (__any(grow)) {
+        // (as above: a row moves by its own scores alone)
+        const float m_next = grow ? m_new : m_run;
+        const float m_safe = (m_next == -INFINITY) ? 0.f : m_next;
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+        l_run *= alpha;
+#pragma unroll
+        for (int d = 0; d < D / 16; ++d)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) o16[d][r] *= alpha;
+        m_run = m_next;
+      }
+    }
+    const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
+    bf16x8 pb;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const float pr = __builtin_amdgcn_exp2f(sc[r >> 2][r & 3] * p.scale_log2 - m_use);
+      pb[r] = LO ? (__bf16)(pr - (float)(__bf16)pr) : (__bf16)pr;
+    }
+    float acc = 0.f;
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb, pb, 0, 1), ones2, acc, false);
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb, pb, 2, 3), ones2, acc, false);
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb, pb, 4, 5), ones2, acc, false);
+    acc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb, pb, 6, 7), ones2, acc, false);
+    l_run += acc;
+#pragma unroll
+    for (int d = 0; d < D / 16; ++d) o16[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_operand(va[d]), pb, o16[d], 0, 0, 0);
+  };
+  auto half_of_tile = [&](int t, uint32_t buf, int half, auto lo_c) __attribute__((always_inline)) {
+    if constexpr (R16) compute_half16(t, buf, half, lo_c);
+    else compute_half(t, buf, half, lo_c);
+  };
+
   // rows with at most this many visible keys get the second (LO) pass over their first tile
   constexpr int kFineKeys = 16;
   const bool fine_wave = k_begin == 0 && wave_min_vis <= kFineKeys;  // wave-uniform
   auto step = [&](int t, uint32_t buf, auto first_c) __attribute__((always_inline)) {
     if (wave < 2 && k_begin + t * kKeyTile + wave * 32 < wave_max_vis) {
-      compute_half(t, buf, wave, std::false_type{});
+      half_of_tile(t, buf, wave, std::false_type{});
       if constexpr (decltype(first_c)::value)
-        if (fine_wave && t == 0 && wave == 0) compute_half(t, buf, wave, std::true_type{});
+        if (fine_wave && t == 0 && wave == 0) half_of_tile(t, buf, wave, std::true_type{});
     }
   };
   // Loop top for tile t (stage t of the pipelined kernels): the gathers of up to STAGES - 2 later
@@ -1150,9 +1261,9 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   }
   if constexpr (FUSED) {
 #pragma unroll
-    for (int s = 0; s < G::kSteps; ++s) {
+    for (int s = 0; s < kQSteps; ++s) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (row_ok) v = *reinterpret_cast<const u32x4*>(s_q + local_row * D + 16 * s + 8 * hi);
+      if (row_ok) v = *reinterpret_cast<const u32x4*>(s_q + local_row * D + (D / kQSteps) * s + q_at);
       qb[s] = __builtin_bit_cast(bf16x8, v);
     }
   }
@@ -1175,7 +1286,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       const int pos = min(key0 + row, k_end - 1);
       const u32x4 val = *reinterpret_cast<const u32x4*>(s_kv + (pos - rq.cached) * 2 * kGRowBytes +
                                                         (is_v ? kGRowBytes : 0) + c * 16);
-      const int swz = KV8 ? (is_v ? vswz8(row) : kswz8(row)) : (is_v ? G::vswz(row) : G::kswz(row));
+      const int swz = KV8 ? (is_v ? vswz8(row) : kswz8(row)) : (is_v ? vswz16(row) : G::kswz(row));
       char* tile = stages + slot * kStageBytes + (is_v ? kGTileBytes : 0);
       *reinterpret_cast<u32x4*>(tile + row * kGRowBytes + ((c ^ swz) << 4)) = val;
       if (key0 + row < k_end) {
@@ -1217,8 +1328,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     const int half = wave & 1;
     for (int t = wave >> 1; t < ntiles; t += WAVES / 2)
       if (k_begin + t * kKeyTile + half * 32 < wave_max_vis) {
-        compute_half(t, t * kSlotBytes, half, std::false_type{});
-        if (fine_wave && t == 0 && half == 0) compute_half(t, 0u, 0, std::true_type{});
+        half_of_tile(t, t * kSlotBytes, half, std::false_type{});
+        if (fine_wave && t == 0 && half == 0) half_of_tile(t, 0u, 0, std::true_type{});
       }
   } else if constexpr (KP) {
     for (int t0 = 0; t0 < ntiles; t0 += STAGES) {
@@ -1316,15 +1427,24 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     float* xl = xm + kSharers * 32;               // [sharer][32 rows][2 halves of the wave]
     __syncthreads();  // every wave is done with the tiles
     if (wave < kSharers && row_ok) {
-      float* mine = xo + (wave * 32 + i32) * kPitch + hi * 4;
+      if constexpr (R16) {
+        float* mine = xo + (wave * 32 + i16) * kPitch + q4 * 4;
 #pragma unroll
-      for (int d = 0; d < G::kDBlocks; ++d)
+        for (int d = 0; d < D / 16; ++d) *reinterpret_cast<f32x4*>(mine + d * 16) = o16[d];
+        if (q4 == 0) xm[wave * 32 + i16] = m_run;
+        const float pair = cross_quarter_sum(l_run);
+        if ((q4 & 1) == 0) xl[(wave * 32 + i16) * 2 + hi] = pair;
+      } else {
+        float* mine = xo + (wave * 32 + i32) * kPitch + hi * 4;
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-          *reinterpret_cast<f32x4*>(mine + d * 32 + rr * 8) =
-              f32x4{o[d][rr * 4], o[d][rr * 4 + 1], o[d][rr * 4 + 2], o[d][rr * 4 + 3]};
-      if (hi == 0) xm[wave * 32 + i32] = m_run;
-      xl[(wave * 32 + i32) * 2 + hi] = l_run;
+        for (int d = 0; d < G::kDBlocks; ++d)
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr)
+            *reinterpret_cast<f32x4*>(mine + d * 32 + rr * 8) =
+                f32x4{o[d][rr * 4], o[d][rr * 4 + 1], o[d][rr * 4 + 2], o[d][rr * 4 + 3]};
+        if (hi == 0) xm[wave * 32 + i32] = m_run;
+        xl[(wave * 32 + i32) * 2 + hi] = l_run;
+      }
     }
     __syncthreads();
     // N such pieces of as many rows at a time, so that their latencies pass together
@@ -1572,7 +1692,7 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
   if (i < count) words[i] = 0;
 }
 
-// few_rows: no work item has more than 32 query rows (always so for the decode step)
+// Key-parallel kernels: no work item has more than 32 query rows (R16: 16), always so for the decode step.
 // Four-wave kernels take two stages over bf16 rows and three over 8-bit rows, where a tile is half
 // as large.  The short step with head dim 64 takes the third stage with more than three work items
 // per compute unit: with two stages three workgroups fit a unit, with three only two, whose
@@ -1580,52 +1700,59 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 // three): 976 items of 14 tiles 45.3 / 42.4, 1012 of 28 tiles 102.5 / 91.4; up to 520 items two
 // are better, 512 of 10 tiles 25.1 / 32.0, 520 of 8 tiles (four layers) 68.7 / 82.8, 320 of 4
 // tiles 15.3 / 16.1.  The plain call over the same rows is not faster with three.
-template <bool FUSED>
-void launch_kernel(int head_dim, bool wide, bool fp8, bool few_rows, bool crowded, bool once, dim3 grid, const AttnParams& p,
-                   hipStream_t stream) {
-#define EFIM_ATTN_LAUNCH2(DD, F8, KP, P8)                                                             \
-  do {                                                                                             \
-    if (wide) extend_attention_kernel<DD, 8, 3, FUSED, F8, KP, false, P8><<<grid, 512, 0, stream>>>(p); \
-    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, FUSED, F8, KP, false, P8><<<grid, 256, 0, stream>>>(p); \
+template <bool FUSED, bool R16>
+void launch_key_parallel(int head_dim, bool wide, bool fp8, bool crowded, bool once, dim3 grid, const AttnParams& p,
+                         hipStream_t stream) {
+#define EFIM_KP(DD, WAVES, STAGES, F8, P8, ONCE) \
+  extend_attention_kernel<DD, WAVES, STAGES, FUSED, F8, true, false, P8, ONCE, R16><<<grid, 64 * (WAVES), 0, stream>>>(p)
+#define EFIM_KP_FORMS(DD, F8, P8)                            \
+  do {                                                       \
+    if (wide) EFIM_KP(DD, 8, 3, F8, P8, false);              \
+    else EFIM_KP(DD, 4, F8 ? 3 : 2, F8, P8, false);          \
   } while (0)
-#define EFIM_ATTN_LAUNCH(DD, F8, P8)                                           \
-  do {                                                                         \
-    if constexpr (FUSED) EFIM_ATTN_LAUNCH2(DD, F8, true, P8);                   \
-    else if (few_rows) EFIM_ATTN_LAUNCH2(DD, F8, true, P8);                     \
-    else EFIM_ATTN_LAUNCH2(DD, F8, FUSED, P8);                                   \
-  } while (0)
-  if (once && !(fp8 && head_dim == 64 && p.page_shift == 3)) {
-#define EFIM_ATTN_ONCE(DD, F8) \
-  extend_attention_kernel<DD, 8, once_tiles(DD), FUSED, F8, true, false, false, true><<<grid, 512, 0, stream>>>(p)
+  const bool two_pages = fp8 && head_dim == 64 && p.page_shift == 3;  // a load spans two pages
+  if (two_pages) {
+    EFIM_KP_FORMS(64, true, true);
+  } else if (once) {
     if (head_dim == 128) {
-      if (fp8) EFIM_ATTN_ONCE(128, true); else EFIM_ATTN_ONCE(128, false);
+      if (fp8) EFIM_KP(128, 8, once_tiles(128), true, false, true); else EFIM_KP(128, 8, once_tiles(128), false, false, true);
     } else {
-      if (fp8) EFIM_ATTN_ONCE(64, true); else EFIM_ATTN_ONCE(64, false);
+      if (fp8) EFIM_KP(64, 8, once_tiles(64), true, false, true); else EFIM_KP(64, 8, once_tiles(64), false, false, true);
     }
-#undef EFIM_ATTN_ONCE
+  } else if (head_dim == 128) {
+    if (fp8) EFIM_KP_FORMS(128, true, false); else EFIM_KP_FORMS(128, false, false);
+  } else if (fp8) {
+    EFIM_KP_FORMS(64, true, false);
+  } else if (FUSED && crowded && !wide) {
+    if constexpr (FUSED) EFIM_KP(64, 4, 3, false, false, false);
+  } else {
+    EFIM_KP_FORMS(64, false, false);
+  }
+#undef EFIM_KP_FORMS
+#undef EFIM_KP
+}
+
+template <bool FUSED>
+void launch_kernel(int head_dim, bool wide, bool fp8, int max_rows, bool crowded, bool once, dim3 grid, const AttnParams& p,
+                   hipStream_t stream) {
+  if (FUSED || max_rows <= 32) {
+    if (max_rows <= 16) launch_key_parallel<FUSED, true>(head_dim, wide, fp8, crowded, once, grid, p, stream);
+    else launch_key_parallel<FUSED, false>(head_dim, wide, fp8, crowded, once, grid, p, stream);
     return;
   }
-  if constexpr (FUSED) {
-    if (crowded && head_dim == 64 && !fp8 && !wide) {
-      extend_attention_kernel<64, 4, 3, true, false, true><<<grid, 256, 0, stream>>>(p);
-      return;
-    }
-  } else {
-    if (crowded && head_dim == 64 && !fp8 && !few_rows) {
-      if (wide) extend_attention_kernel<64, 8, 3, false, false, false, true><<<grid, 512, 0, stream>>>(p);
-      else extend_attention_kernel<64, 4, 2, false, false, false, true><<<grid, 256, 0, stream>>>(p);
-      return;
-    }
-  }
+#define EFIM_PIPE(DD, F8, PACK, P8)                                                                            \
+  do {                                                                                                        \
+    if (wide) extend_attention_kernel<DD, 8, 3, false, F8, false, PACK, P8><<<grid, 512, 0, stream>>>(p);       \
+    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, false, F8, false, PACK, P8><<<grid, 256, 0, stream>>>(p);  \
+  } while (0)
   if (head_dim == 128) {
-    if (fp8) EFIM_ATTN_LAUNCH(128, true, false); else EFIM_ATTN_LAUNCH(128, false, false);
+    if (fp8) EFIM_PIPE(128, true, false, false); else EFIM_PIPE(128, false, false, false);
   } else if (fp8) {
-    if (p.page_shift == 3) EFIM_ATTN_LAUNCH(64, true, true); else EFIM_ATTN_LAUNCH(64, true, false);
+    if (p.page_shift == 3) EFIM_PIPE(64, true, false, true); else EFIM_PIPE(64, true, false, false);
   } else {
-    EFIM_ATTN_LAUNCH(64, false, false);
+    if (crowded) EFIM_PIPE(64, false, true, false); else EFIM_PIPE(64, false, false, false);
   }
-#undef EFIM_ATTN_LAUNCH
-#undef EFIM_ATTN_LAUNCH2
+#undef EFIM_PIPE
 }
 
 int launch_merge(const efim_batch_t* b, const Plan& plan, const AttnParams& p, hipStream_t stream) {
@@ -1667,7 +1794,7 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows <= 32, plan.crowded, plan.once, grid, p, stream);
+  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows, plan.crowded, plan.once, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
@@ -1701,7 +1828,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
   const bool wide = plan.rows_per_item == 256;
-  launch_kernel<true>(D, wide, fmt.fp8, true, plan.crowded, plan.once, grid, p, stream);
+  launch_kernel<true>(D, wide, fmt.fp8, plan.max_item_rows, plan.crowded, plan.once, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }

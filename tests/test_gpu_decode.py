@@ -201,6 +201,36 @@ def test_ranges_gathered_at_once(E, heads, d, page_size):
     U.assert_close(got, ref, large_outputs=True)
 
 
+@pytest.mark.parametrize("row_tile,split", [(0, -1), (128, 64), (256, 64)])
+@pytest.mark.parametrize("page_size", [8, 16, 256])
+@pytest.mark.parametrize("heads,d", [((3, 3), 128), ((16, 1), 128), ((4, 2), 64)])
+def test_sixteen_rows_per_item(E, heads, d, page_size, row_tile, split):
+    """Launches whose largest item has exactly 16 query rows: first and last rows and keys of both 16-key
+    blocks of a half tile, in every form of the kernel, over bf16 rows and codes."""
+    from test_gpu_fp8 import oracle_cache8, oracle_step8, run_decode8
+    g = heads[0] // heads[1]
+    n = np.array([max(1, 16 // g), 1, max(1, 8 // g), 1, 1], dtype=np.int32)
+    c = np.array([113, 15, 16, 48, 700], dtype=np.int32)
+    b = W.make_batch("c1", seed=230 + d + g + page_size, lengths=(c, n), heads=heads, head_dim=d, page_size=page_size)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, row_tile)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, split)
+    try:
+        kc, vc = U.oracle_cache(b)
+        _, kc_ref, vc_ref, ref = oracle_step(b, kc, vc)
+        got, kc_got, vc_got, _ = run_decode(E, b, kc, vc)
+        assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+        U.assert_close(got, ref, large_outputs=True)
+        assert np.array_equal(got, two_call_path(E, b, kc, vc))
+        kc, vc = oracle_cache8(b, 0.0123, 0.031)
+        _, kc_ref, vc_ref, ref = oracle_step8(b, kc, vc, 0.0123, 0.031)
+        got, kc_got, vc_got, _ = run_decode8(E, b, kc, vc, 0.0123, 0.031)
+        assert np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+        U.assert_close(got, ref, large_outputs=True)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+
+
 @pytest.mark.parametrize("page_size", [8, 256])
 def test_short_step_other_page_sizes(E, page_size):
     c = np.array([0, 7, 8, 60, 64, 250, 256, 1000, 2049], dtype=np.int32)
