@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 # on: the digest of extend_attention.hip is recorded with it and checked at run time.
 MEASURED_TRAFFIC = {
     # workload: (bytes per launch, sha256 of csrc/extend_attention.hip when measured)
-    "c5": (2592279941, "8be60441a128fb3e009a53509f3e2d46c234d93976466eeea93bc8e58d40cc3d"),
+    "c5": (2593312730, "67680c69ae6212064971934907790304edf0c9fb144a3c6e47231e3c6b7aea81"),
 }
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak
