@@ -201,16 +201,23 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
 
   // Few rows per item and few tiles in all: cut so that every item fits the kernel that gathers its
   // whole range at once, if that makes at most one item per compute unit (that kernel takes the
-  // whole LDS of one).  Measured over 94 short steps on either kernel: 0.80 .. 0.95 of the time with a
-  // few tiles per item, even where the ring had them all in flight too (one request of 8000 keys, 4
-  // heads of 64: 11.8 / 11.7 us; 32/8 heads of 128, 256 items of four tiles: 14.7 / 14.8 us).
+  // whole LDS of one).  A range that the policy above leaves whole although it does not fit (five
+  // tiles of head dim 128) stays whole, and the launch with it on the ring kernel: its fp32 sums go
+  // to the output directly, and a cut would put them through binary16 parts, a workspace and, with
+  // more than 8 rows, a second launch.  (Speed goes either way.  8 layers, whole / cut: one request of
+  // 270 keys with 32 rows per kv head in two calls 120 / 133 us, two of 300 keys with 32 rows 114 / 128;
+  // one of 270 keys and one new token in one call, 32/8 heads 80 / 74, eight such 85 / 75.)
   plan->once = false;
   if (max_rows <= 32 && tn.split_kv < 0) {
     const int64_t most = once_tiles(D), units = M == 256 ? num_slots : num_slots / 2;
     const int64_t cut = chunk > 0 ? std::min(chunk, most) : most;
     int64_t pieces = 0;
-    for (const Tile& t : tiles) pieces += t.ktiles > most ? (t.ktiles + cut - 1) / cut : 1;
-    plan->once = pieces <= units;
+    bool fits = true;
+    for (const Tile& t : tiles) {
+      fits = fits && (t.ktiles <= most || pieces_of(t, chunk) > 1);
+      pieces += t.ktiles > most ? (t.ktiles + cut - 1) / cut : 1;
+    }
+    plan->once = fits && pieces <= units;
     if (plan->once) chunk = cut;
   }
   auto cuts_of = [&](const Tile& t) {

@@ -336,3 +336,19 @@ def test_short_steps_of_few_tiles_are_cut_into_ranges_that_fit_the_buffers(d, mo
         for h in range(4):
             mine = items[(items["req"] == r) & (items["kv_head"] == h)]
             assert (mine["key_end"] - mine["key_begin"]).sum() == x
+
+
+@pytest.mark.parametrize("heads", [(8, 4), (32, 8), (4, 4)])
+@pytest.mark.parametrize("lengths", [[257], [300], [320], [320] * 4, [257, 100], [310, 2344]])
+def test_short_ranges_stay_whole(lengths, heads):
+    """Five key tiles of head dim 128: more than the kernel that gathers a whole range at once holds, less than the split
+    policy cuts.  Such a range stays one item, whose fp32 sums go to the output directly and which needs no
+    workspace and no merge; the launch then runs the ring kernel."""
+    b = _desc([x - 1 for x in lengths], [1] * len(lengths), hq=heads[0], hkv=heads[1], d=128)
+    items = E.efim_extend_plan_items(b)
+    for r, x in enumerate(lengths):
+        mine = items[(items["req"] == r) & (items["row_count"] > 0)]
+        if x <= 320:
+            assert len(mine) == heads[1] and (mine["partial_slot"] < 0).all() and (mine["key_end"] == x).all()
+    if max(lengths) <= 320:
+        assert E.efim_extend_workspace_bytes(b) == 256 and E.efim_decode_workspace_bytes(b) == 256
