@@ -17,6 +17,9 @@ constexpr int kKeyTile = 64;          // keys staged in LDS per main-loop iterat
 constexpr int kWavesPerGroup = 4;     // wavefronts per attention workgroup
 // key tiles that the kernel which gathers a whole key range at the start of an item holds (128 KB of bf16 rows)
 constexpr int once_tiles(int head_dim) { return head_dim == 128 ? 4 : 8; }
+// and the most query rows of an item that it is launched for (reason at the planner's rule); one_call: the
+// batch is one that the fused short step takes
+constexpr int once_rows(int head_dim, bool one_call) { return head_dim == 128 && !one_call ? 16 : 32; }
 constexpr int kMaxRowsPerItem = 256;  // largest query-row tile of one workgroup
 constexpr int kStageSlots = 64;       // launch tokens in turn: a token comes round again after this many calls
 constexpr int kTicketSlots = kStageSlots;

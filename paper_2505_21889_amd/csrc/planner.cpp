@@ -207,8 +207,15 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   // more than 8 rows, a second launch.  (Speed goes either way.  8 layers, whole / cut: one request of
   // 270 keys with 32 rows per kv head in two calls 120 / 133 us, two of 300 keys with 32 rows 114 / 128;
   // one of 270 keys and one new token in one call, 32/8 heads 80 / 74, eight such 85 / 75.)
+  // Head dim 128 with 17 to 32 rows: the sums of eight waves are 128 KB that go through LDS behind the last
+  // tile.  The two calls do not gain that back, the step in one call does (its prologue runs on eight
+  // waves too), and both have to give the same `out`: only batches that the one call takes.  8 layers,
+  // ring / whole range gathered, two calls and one call: 8 requests of 1000 keys, 32 rows 161 / 169 and 152 /
+  // 146 us; 25 of 250 keys, 32 rows 129 / 137 and 123 / 114; one of 1000 keys, 32 rows 128 / 131 and 132 / 115;
+  // 24 of 250 keys, 28 rows 109 / 114 and 108 / 93.  Head dim 64, 32 rows: 32 of 500 keys 148 / 135 and 127 / 100.
   plan->once = false;
-  if (max_rows <= 32 && tn.split_kv < 0) {
+  const bool one_call = std::all_of(b->new_len, b->new_len + b->batch, [](int32_t n) { return n >= 1 && n <= kFusedMaxTokens; });
+  if (max_rows <= once_rows(D, one_call) && tn.split_kv < 0) {
     const int64_t most = once_tiles(D), units = M == 256 ? num_slots : num_slots / 2;
     const int64_t cut = chunk > 0 ? std::min(chunk, most) : most;
     int64_t pieces = 0;

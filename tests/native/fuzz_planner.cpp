@@ -9,14 +9,22 @@
 using namespace efim;
 int main() {
   std::mt19937 rng(7);
-  long items_total = 0;
-  for (int iter = 0; iter < 400; ++iter) {
+  long items_total = 0, once_plans = 0;
+  for (int iter = 0; iter < 1200; ++iter) {
     int batch = 1 + rng() % 12;
     std::vector<int32_t> c(batch), n(batch);
     for (int r = 0; r < batch; ++r) {
       int kind = rng() % 6;
       c[r] = kind == 0 ? 0 : (kind == 1 ? rng() % 70 : (kind == 2 ? rng() % 9000 : rng() % 40000));
       n[r] = (rng() % 5 == 0) ? 0 : (rng() % 3 == 0 ? 1 + rng() % 600 : 1 + rng() % 40);
+    }
+    // two of three batches are short steps: a few tokens per request, few key tiles
+    if (iter % 3) {
+      const int most = 1 + rng() % 8;
+      for (int r = 0; r < batch; ++r) {
+        n[r] = rng() % 7 == 0 ? 0 : 1 + rng() % most;
+        if (iter % 3 == 1) c[r] %= 700;
+      }
     }
     static const int hq[] = {1, 4, 8, 28, 32, 14, 6}, hkv[] = {1, 4, 2, 4, 8, 2, 1};
     int h = rng() % 7;
@@ -36,6 +44,23 @@ int main() {
     int slots = (rng() & 1) ? 256 : 512;
     build_plan(&b, slots, &plan);
     items_total += (long)plan.items.size();
+    // the kernel that gathers whole ranges at once reads past its buffers if an item has more tiles than it
+    // holds, and takes a whole compute unit per item
+    if (plan.once) {
+      ++once_plans;
+      long live = 0;
+      bool one_call = true;
+      for (int r = 0; r < batch; ++r) one_call = one_call && n[r] >= 1 && n[r] <= kFusedMaxTokens;
+      for (const WorkItem& w : plan.items) {
+        if (w.row_count == 0) continue;
+        ++live;
+        if ((w.key_end - w.key_begin + kKeyTile - 1) / kKeyTile > once_tiles(b.head_dim) || w.row_count > once_rows(b.head_dim, one_call)) {
+          printf("item too large for its kernel, iter %d\n", iter);
+          return 1;
+        }
+      }
+      if (live > slots / 2 || tuning().split_kv >= 0) { printf("whole-range kernel iter %d: %ld items\n", iter, live); return 1; }
+    }
     // coverage: every (req, kv head, row) x key range is covered exactly once
     const int g = b.num_q_heads / b.num_kv_heads;
     for (int r = 0; r < batch; ++r) {
@@ -56,6 +81,7 @@ int main() {
       }
     }
   }
-  printf("planner ok, %ld items\n", items_total);
+  if (once_plans < 50) { printf("only %ld plans for the whole-range kernel\n", once_plans); return 1; }
+  printf("planner ok, %ld items, %ld plans for the whole-range kernel\n", items_total, once_plans);
   return 0;
 }
