@@ -77,6 +77,7 @@ struct Plan {
   int max_item_rows = 0;    // largest row_count of a work item
   int partial_rows = 128;   // rows per partial-result slot of a split key range
   bool once = false;        // few work items of few rows, each short enough for the kernel that gathers a whole range at once
+  bool rows16 = false;      // key-parallel kernels: products of 16 rows instead of 32
   bool crowded = false;     // head dim 64: work items crowd the compute units (other forms of the bf16 kernels)
   std::vector<ReqInfo> reqs;
   std::vector<WorkItem> items;

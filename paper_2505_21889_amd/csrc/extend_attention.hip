@@ -1706,7 +1706,7 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
   if (i < count) words[i] = 0;
 }
 
-// Key-parallel kernels: no work item has more than 32 query rows (R16: 16), always so for the decode step.
+// Key-parallel kernels: no work item has more than 32 query rows (R16, Plan::rows16: 16), always so for the decode step.
 // Four-wave kernels take two stages over bf16 rows and three over 8-bit rows, where a tile is half
 // as large.  The short step with head dim 64 takes the third stage with more than three work items
 // per compute unit: with two stages three workgroups fit a unit, with three only two, whose
@@ -1747,11 +1747,11 @@ void launch_key_parallel(int head_dim, bool wide, bool fp8, bool crowded, bool o
 }
 
 template <bool FUSED>
-void launch_kernel(int head_dim, bool wide, bool fp8, int max_rows, bool crowded, bool once, dim3 grid, const AttnParams& p,
-                   hipStream_t stream) {
-  if (FUSED || max_rows <= 32) {
-    if (max_rows <= 16) launch_key_parallel<FUSED, true>(head_dim, wide, fp8, crowded, once, grid, p, stream);
-    else launch_key_parallel<FUSED, false>(head_dim, wide, fp8, crowded, once, grid, p, stream);
+void launch_kernel(int head_dim, const Plan& plan, bool fp8, dim3 grid, const AttnParams& p, hipStream_t stream) {
+  const bool wide = plan.rows_per_item == 256, crowded = plan.crowded;
+  if (FUSED || plan.max_item_rows <= 32) {
+    if (plan.rows16) launch_key_parallel<FUSED, true>(head_dim, wide, fp8, crowded, plan.once, grid, p, stream);
+    else launch_key_parallel<FUSED, false>(head_dim, wide, fp8, crowded, plan.once, grid, p, stream);
     return;
   }
 #define EFIM_PIPE(DD, F8, PACK, P8)                                                                            \
@@ -1807,8 +1807,7 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
-  const bool wide = plan.rows_per_item == 256;
-  launch_kernel<false>(b->head_dim, wide, fmt.fp8, plan.max_item_rows, plan.crowded, plan.once, grid, p, stream);
+  launch_kernel<false>(b->head_dim, plan, fmt.fp8, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
@@ -1841,8 +1840,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
-  const bool wide = plan.rows_per_item == 256;
-  launch_kernel<true>(D, wide, fmt.fp8, plan.max_item_rows, plan.crowded, plan.once, grid, p, stream);
+  launch_kernel<true>(D, plan, fmt.fp8, grid, p, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
