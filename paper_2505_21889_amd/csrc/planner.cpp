@@ -68,6 +68,7 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   plan->items.clear();
   plan->merges.clear();
   plan->num_partial_slots = 0;
+  plan->crowded = false;
 
   int64_t row = 0;
   int64_t max_rows = 0;

@@ -10,6 +10,7 @@ using namespace efim;
 int main() {
   std::mt19937 rng(7);
   long items_total = 0, once_plans = 0;
+  Plan again;  // built over and over, as the library's cached plan is
   for (int iter = 0; iter < 1200; ++iter) {
     int batch = 1 + rng() % 12;
     std::vector<int32_t> c(batch), n(batch);
@@ -43,6 +44,15 @@ int main() {
     Plan plan;
     int slots = (rng() & 1) ? 256 : 512;
     build_plan(&b, slots, &plan);
+    build_plan(&b, slots, &again);
+    if (again.items.size() != plan.items.size() || again.merges.size() != plan.merges.size() || again.reqs.size() != plan.reqs.size() ||
+        again.rows_per_item != plan.rows_per_item || again.max_item_rows != plan.max_item_rows || again.partial_rows != plan.partial_rows ||
+        again.once != plan.once || again.rows16 != plan.rows16 || again.crowded != plan.crowded ||
+        again.num_partial_slots != plan.num_partial_slots || again.total_bytes != plan.total_bytes ||
+        again.header_bytes != plan.header_bytes) {
+      printf("a plan built into a used object differs, iter %d\n", iter);
+      return 1;
+    }
     items_total += (long)plan.items.size();
     // the kernel that gathers whole ranges at once reads past its buffers if an item has more tiles than it
     // holds, and takes a whole compute unit per item
