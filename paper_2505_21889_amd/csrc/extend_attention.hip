@@ -437,8 +437,9 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   constexpr int kTableBytes = FUSED && ONCE ? kFusedMaxTokens * (D / 2) * 16 : 0;
   // key-parallel kernels: where the waves that share the rows leave their sums at the end
   constexpr int kSharers = ONCE ? WAVES : 2;
+  constexpr int kMaxRows = R16 ? 16 : 32;
   constexpr int kPitch = D + 4;  // floats from row to row: 16 bytes on, so that 16 rows spread over all banks
-  constexpr int kExchangeBytes = KP ? kSharers * 32 * (kPitch + 3) * 4 : 0;
+  constexpr int kExchangeBytes = KP ? kSharers * kMaxRows * (kPitch + 3) * 4 : 0;
   constexpr int kBufBytes = kTileBufBytes + kFusedBytes + kTableBytes;
   constexpr int kLdsBytes = kBufBytes > kExchangeBytes ? kBufBytes : kExchangeBytes;
   static_assert(STAGES >= 2 && kLdsBytes <= 160 * 1024, "stages must fit the 160 KB LDS");
@@ -1422,28 +1423,28 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     // for bit)
 #pragma clang fp contract(off)
     constexpr int kVec = D / 4;  // threads per row
-    float* xo = reinterpret_cast<float*>(lds);    // [sharer][32 rows] x kPitch
-    float* xm = xo + kSharers * 32 * kPitch;      // [sharer][32 rows]
-    float* xl = xm + kSharers * 32;               // [sharer][32 rows][2 halves of the wave]
+    float* xo = reinterpret_cast<float*>(lds);      // [sharer][row] x kPitch
+    float* xm = xo + kSharers * kMaxRows * kPitch;  // [sharer][row]
+    float* xl = xm + kSharers * kMaxRows;           // [sharer][row][2 halves of the wave]
     __syncthreads();  // every wave is done with the tiles
     if (wave < kSharers && row_ok) {
       if constexpr (R16) {
-        float* mine = xo + (wave * 32 + i16) * kPitch + q4 * 4;
+        float* mine = xo + (wave * kMaxRows + i16) * kPitch + q4 * 4;
 #pragma unroll
         for (int d = 0; d < D / 16; ++d) *reinterpret_cast<f32x4*>(mine + d * 16) = o16[d];
-        if (q4 == 0) xm[wave * 32 + i16] = m_run;
+        if (q4 == 0) xm[wave * kMaxRows + i16] = m_run;
         const float pair = cross_quarter_sum(l_run);
-        if ((q4 & 1) == 0) xl[(wave * 32 + i16) * 2 + hi] = pair;
+        if ((q4 & 1) == 0) xl[(wave * kMaxRows + i16) * 2 + hi] = pair;
       } else {
-        float* mine = xo + (wave * 32 + i32) * kPitch + hi * 4;
+        float* mine = xo + (wave * kMaxRows + i32) * kPitch + hi * 4;
 #pragma unroll
         for (int d = 0; d < G::kDBlocks; ++d)
 #pragma unroll
           for (int rr = 0; rr < 4; ++rr)
             *reinterpret_cast<f32x4*>(mine + d * 32 + rr * 8) =
                 f32x4{o[d][rr * 4], o[d][rr * 4 + 1], o[d][rr * 4 + 2], o[d][rr * 4 + 3]};
-        if (hi == 0) xm[wave * 32 + i32] = m_run;
-        xl[(wave * 32 + i32) * 2 + hi] = l_run;
+        if (hi == 0) xm[wave * kMaxRows + i32] = m_run;
+        xl[(wave * kMaxRows + i32) * 2 + hi] = l_run;
       }
     }
     __syncthreads();
@@ -1469,10 +1470,10 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
         f32x4 ow[kMine];
 #pragma unroll
         for (int w = 0; w < kMine; ++w) {
-          m[w] = xm[(w0 + w) * 32 + at];
-          a[w][0] = xl[((w0 + w) * 32 + at) * 2];
-          a[w][1] = xl[((w0 + w) * 32 + at) * 2 + 1];
-          ow[w] = *reinterpret_cast<const f32x4*>(xo + ((w0 + w) * 32 + at) * kPitch + c);
+          m[w] = xm[(w0 + w) * kMaxRows + at];
+          a[w][0] = xl[((w0 + w) * kMaxRows + at) * 2];
+          a[w][1] = xl[((w0 + w) * kMaxRows + at) * 2 + 1];
+          ow[w] = *reinterpret_cast<const f32x4*>(xo + ((w0 + w) * kMaxRows + at) * kPitch + c);
         }
         m_all[i] = m[0];
 #pragma unroll
@@ -1534,11 +1535,13 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
         }
       }
     };
+    // (The form for four pieces is compiled where a row count reaches it.  Leaving out the one for two as well,
+    // where none does, moves the code behind it: one request of 2344 keys, 32 layers 349 -> 355 us.)
     constexpr int kRowsAtOnce = 64 * WAVES / kVec;
     if (ONCE && it.row_count <= kRowsAtOnce / 2) write_rows(std::integral_constant<int, 1>{}, std::bool_constant<ONCE>{}, 0);
     else if (it.row_count <= kRowsAtOnce) write_rows(std::integral_constant<int, 1>{}, std::false_type{}, 0);
     else if (it.row_count <= 2 * kRowsAtOnce) write_rows(std::integral_constant<int, 2>{}, std::false_type{}, 0);
-    else
+    else if constexpr (kMaxRows > 2 * kRowsAtOnce)
       for (int r0 = 0; r0 < it.row_count; r0 += 4 * kRowsAtOnce) write_rows(std::integral_constant<int, 4>{}, std::false_type{}, r0);
   }
 
