@@ -352,13 +352,13 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // those that fall into its key range into its LDS tiles and stores them, with their values,
 // into the paged cache.
 //
-// KV8: the caches hold E4M3 codes.  The stages then hold code tiles (half the size); all
-// configurations run with three of them -- more tiles in flight measured slower, not faster.
+// KV8: the caches hold E4M3 codes.  The stages then hold code tiles (half the size); the rings
+// have three of them in all configurations -- more tiles in flight measured slower, not faster.
 //
 // KP ("key parallel"): every work item of the launch has at most 32 query rows (decode steps,
-// short increments).  One wave would be busy and the others idle: instead waves 0 and 1 both
-// take all the rows and one 32-key half of every key tile each, with their own running max and
-// sums, and their partial results are combined through LDS at the end.  In the four-wave
+// short increments).  One wave would be busy and the others idle: instead waves 0 and 1 (ONCE: all
+// eight, in pairs) take all the rows and one 32-key half of a key tile each, with their own running
+// max and sums, and their partial results are combined through LDS at the end.  In the four-wave
 // kernel the two waves without rows issue all the gathers.
 //
 // Head dim 64, few rows: a few registers less than the compiler takes by itself let two 8-wave (or
@@ -383,7 +383,10 @@ constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bo
 // 0.8 us each.  Here all of them are gathered at the start, each pair of waves takes tiles of its own,
 // and the eight waves' sums are combined at the end.  One request of 1000 keys, 32/8 heads 12.2 -> 10.4
 // us, 16 requests of 250 keys 10.2 -> 8.2 us, four requests of 300 + 32 tokens, 4 heads of 64, two
-// calls 16.8 -> 11.2 us.
+// calls 16.8 -> 11.2 us.  An item takes 128 to 160 KB of LDS over bf16 rows (64 to 138 KB over codes), so
+// launches on two streams share the device only while their items together are no more than the
+// units: two at once, one stream after the other / both, 2 x 64 items 8.3 + 8.3 / 9.5 us, 2 x 128
+// 10.8 + 10.8 / 11.8, 2 x 256 10.4 + 11.1 / 17.8 (on the ring 13.7 + 14.8 / 17.3).
 //
 // R16 (key parallel, no item has more than 16 query rows): products of 16 keys by 16 rows instead of 32 by
 // 32.  A 32 x 32 product over one to seven rows spends most of its time, of the softmax and of the
@@ -586,10 +589,10 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     // (not in the eight-wave key-parallel kernel over bf16 caches: measured 1.5-2.5 % slower there
     // -- that kernel is bound by HBM alone, and its loads do better spaced out)
     constexpr bool kGroupedIssue = !(KP && WAVES == 8 && !KV8) || ONCE;
-    // The key-parallel kernel of the plain call takes the last tile of a range the same way: through
-    // the general path below it waits for a page lookup in front of each load, one behind the
+    // The key-parallel kernels of the plain call and ONCE take the last tile of a range the same way: through
+    // the general path below they wait for a page lookup in front of each load, one behind the
     // other (one request of 256 + 32 tokens, 4 heads: 7.7 -> 7.2 us).  The other kernels have
-    // no registers for it (the decode step spilled: 13.3 -> 13.7 us) or longer ranges.
+    // no registers for it (the decode step's ring spilled: 13.3 -> 13.7 us) or longer ranges.
     constexpr bool kGroupedLast = KP && (!FUSED || ONCE);
     // P8: both page ids of a load come by scalar loads, all of the wave's together, and a lane picks
     // its page's; looked up lane by lane the ids wait on the counter of the gathers and drain the
@@ -1179,7 +1182,9 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     }
   }
   if constexpr (ONCE) {
-    TilePages pages[STAGES];  // of all tiles together: one latency
+    // (page ids of all tiles together, one latency, where a page holds the four loads of a wave: bf16 rows of head
+    // dim 128 on pages of 16 and more; elsewhere issue_tile looks them up tile by tile)
+    TilePages pages[STAGES];
 #pragma unroll
     for (int st = 0; st < STAGES; ++st) pages[st] = fetch_pages(min(st, ntiles - 1));
 #pragma unroll
@@ -1199,8 +1204,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     // Rotary embedding of the tile's query rows and of the new tokens' keys (token j of the
     // request sits at position C_r + j and is packed row rq.row_start + j), same arithmetic as
     // the stand-alone append kernel.  First the cosines and sines, one task per (token, pair),
-    // into the tile buffer that no gather has been issued into yet (the last one), while the raw
-    // rows are on their way; then one task per (row, pair) over the query rows and the key rows.
+    // into the tile buffer that no gather has been issued into yet (the last one; ONCE: an area of their own),
+    // while the raw rows are on their way; then one task per (row, pair) over the query rows and the key rows.
     const int rot_half = p.rotary_dim / 2;  // pairs per head row (D/2 when the whole row rotates)
     double* const s_cs =  // [token][pair] (cos, sin)
         reinterpret_cast<double*>(ONCE ? lds + kTileBufBytes + kFusedBytes : stages + (STAGES - 1) * kStageBytes);
@@ -1410,8 +1415,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     for (; t <= ntiles; ++t) top(t, (t + STAGES - 1) % STAGES);
   }
 
-  // --- waves 0 and 1 shared the rows: they leave their sums in LDS as rows, and all waves combine
-  // and write them.  With M = max(m_0, m_1) the sums of wave w are rescaled by 2^(m_w - M).
+  // --- waves 0 and 1 (ONCE: all eight) shared the rows: they leave their sums in LDS as rows, and all waves
+  // combine and write them.  With M = max_w m_w the sums of wave w are rescaled by 2^(m_w - M).
   // Only rows that exist are touched, four elements of a row per thread, and a row leaves as one
   // contiguous piece.  Bound by one wave's instruction stream when wave 0 did it alone, for all 32
   // columns of its accumulators whether they were rows or not: 1.65 us from the last tile to the
@@ -1448,9 +1453,10 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       }
     }
     __syncthreads();
-    // N such pieces of as many rows at a time, so that their latencies pass together.  HALVES (eight sharers,
-    // few rows): the halves of a wave take four sharers each (94 short steps of up to 8 rows 1.5 % faster,
-    // 16 and more rows 4-12 % slower that way).
+    // N such pieces of as many rows at a time, so that their latencies pass together.  HALVES (eight sharers, up
+    // to 8 rows of head dim 128 or 16 of 64, so that half of the threads would have no row): the halves of a wave
+    // take four sharers each (short steps of up to 8 rows 1.5 % faster; where the rows take all threads 4-12 %
+    // slower that way).
     auto write_rows = [&](auto n_c, auto halves_c, int first) __attribute__((always_inline)) {
       constexpr int N = decltype(n_c)::value;
       constexpr bool HALVES = decltype(halves_c)::value;
@@ -1694,9 +1700,12 @@ namespace {
 // Split key ranges are combined inside the main kernel or by merge_kernel in a second launch.
 // In-kernel merging sends the partial results through device-coherent (write-through) stores;
 // that pays when every tile has very few rows (decode steps of the usual head groupings),
-// where it saves a launch, and costs more than the launch as the rows grow (measured on a
-// 28/4-head step: 1.7 us gained at 7 rows per tile, 6 us lost at 28), so by default it is used
-// when no work item has more than 8 query rows.
+// where it saves a launch, and costs more than the launch as the rows grow, so by default it is used
+// when no work item has more than 8 query rows.  4 layers, second launch / in the kernel, us: 16 requests of
+// 3000 keys 4 rows 160.8 / 158.3, 8 rows 162.2 / 161.0, 14 rows 100.8 / 100.9 (28/4 heads), 16 rows 170.2 / 171.7, 32
+// rows 183.9 / 190.9; two calls 4 rows 185.3 / 183.8, 8 rows 186.6 / 187.4, 16 rows 190.7 / 195.8.  Many parts per
+// range cost the kernel a round of reads for every eight: two requests of 2344 keys, ten parts, 4 rows 43.1 /
+// 45.8; head dim 64 gains up to 16 rows with few parts (107.6 / 107.3) and loses as much with ten (40.1 / 44.0).
 constexpr int kTicketMergeMaxRows = 8;
 bool use_tickets(const Plan& plan) {
   const int knob = tuning().fused_merge;

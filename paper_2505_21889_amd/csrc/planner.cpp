@@ -202,7 +202,16 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
 
   // Few rows per item and few tiles in all: cut so that every item fits the kernel that gathers its
   // whole range at once, if that makes at most one item per compute unit (that kernel takes the
-  // whole LDS of one).  A range that the policy above leaves whole although it does not fit (five
+  // whole LDS of one).  Measured over 94 short steps on either kernel: 0.67 .. 1.007 of the ring's time, 0.89
+  // in the mean; with a few tiles per item 0.80 .. 0.95, nothing where the ring had them all in flight too (one
+  // request of 8000 keys, 4 heads of 64: 11.8 / 11.7 us; 32/8 heads of 128, 256 items of four tiles: 14.7 / 14.8).  Up
+  // to half as many items as units would leave room for a second stream's, but single launches of 129 to 256
+  // items are 5 to 20 % slower on the ring (32 requests of 200 keys, 8 layers 89 / 78 us).
+  // 8-bit caches with head dim 64 on pages of 8 have no such kernel (their loads span two pages) and run
+  // the ring over the same items: ranges of six to eight tiles that would be two parts are one there, which is
+  // faster too (8 layers, cut / whole: one request of 330 keys 66.6 / 62.0 us, 16 of 400 71.2 / 66.7, 8 of 500
+  // with 16 rows 87.0 / 82.0, two calls, 8 of 400 with 32 rows 123.3 / 116.9).
+  // A range that the policy above leaves whole although it does not fit (five
   // tiles of head dim 128) stays whole, and the launch with it on the ring kernel: its fp32 sums go
   // to the output directly, and a cut would put them through binary16 parts, a workspace and, with
   // more than 8 rows, a second launch.  (Speed goes either way.  8 layers, whole / cut: one request of
