@@ -69,8 +69,8 @@ struct AttnParams {
   int32_t rows_per_item;  // rows of one partial-result slot
   float scale_log2;       // sm_scale * log2(e) (times the key scale of an 8-bit cache)
   float out_scale;        // 1, or the value scale of an 8-bit cache
-  float k_scale;          // 8-bit caches, fused decode step: code = value / scale
-  float v_scale;
+  double k_inv;           // 8-bit caches, fused decode step: 1 / scale (code = value / scale)
+  double v_inv;
   // --- fused decode step only (one new token per request) ---
   const uint16_t* k_new;  // [B, Hkv, D] raw keys of the new tokens
   const uint16_t* v_new;  // [B, Hkv, D]
@@ -1249,8 +1249,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       if (KV8 && is_key) {
         // the key goes into the cache as a code
         uint8_t* krow = reinterpret_cast<uint8_t*>(s_kv + tk * 2 * kGRowBytes);
-        krow[e1] = (uint8_t)bf16_bits_to_e4m3(y1, p.k_scale);
-        krow[e2] = (uint8_t)bf16_bits_to_e4m3(y2, p.k_scale);
+        krow[e1] = (uint8_t)bf16_bits_to_e4m3(y1, p.k_inv);
+        krow[e2] = (uint8_t)bf16_bits_to_e4m3(y2, p.k_inv);
       } else {
         row[e1] = (uint16_t)y1;
         row[e2] = (uint16_t)y2;
@@ -1260,7 +1260,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       for (int idx = tid; idx < n_tok * D; idx += 64 * WAVES) {
         const int tk = idx / D, e = idx - tk * D;
         reinterpret_cast<uint8_t*>(s_kv + tk * 2 * kGRowBytes + kGRowBytes)[e] =
-            (uint8_t)bf16_bits_to_e4m3(s_raw[(tk * 2 + 1) * D + e], p.v_scale);
+            (uint8_t)bf16_bits_to_e4m3(s_raw[(tk * 2 + 1) * D + e], p.v_inv);
       }
     }
     __syncthreads();
@@ -1673,8 +1673,8 @@ void fill_params(AttnParams* p, const efim_batch_t* b, const Plan& plan, const c
   p->rows_per_item = plan.partial_rows;
   p->scale_log2 = sm_scale * 1.4426950408889634f;
   p->out_scale = 1.f;
-  p->k_scale = fmt.k_scale;
-  p->v_scale = fmt.v_scale;
+  p->k_inv = 1.0 / (double)fmt.k_scale;
+  p->v_inv = 1.0 / (double)fmt.v_scale;
   if (fmt.fp8) {
     p->scale_log2 *= fmt.k_scale;
     p->out_scale = fmt.v_scale;

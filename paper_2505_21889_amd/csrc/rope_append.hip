@@ -4,9 +4,7 @@
 // C_r + i).  Streaming kernel, bound by HBM bandwidth: 2*(Hq + 2*Hkv)*D*2 bytes per token.
 //
 // The rotation is done in fp64 and rounded once to bf16 so that the cache contents agree
-// bit for bit with a double-precision definition.  One workgroup handles kTokens tokens:
-// first one thread per (token, pair index) evaluates sincos once and parks it in LDS, then
-// all threads stream the (Hq + 2*Hkv) head rows of those tokens with 16-byte accesses.
+// bit for bit with a double-precision definition.
 //
 // KV8 variant: the caches hold E4M3 codes (one byte per element, same [page, head, slot, D]
 // layout); the rotated key (after its rounding to bf16) and the value are divided by the
@@ -19,197 +17,242 @@ namespace efim {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kPasses = 2;  // passes of a wave over its token's head rows
+// From this many bytes of head rows on a workgroup takes all rows of a token (see launch_with).
+constexpr int64_t kWholeTokenBytes = (int64_t)1 << 29;
 constexpr int kMaxReqPerLaunch = 384;
 
+template <int MAXREQ>
 struct RopeArgs {
-  double inv_freq[64];                      // rotation frequency of pair j (rotary_dim/2 entries)
-  int32_t cached[kMaxReqPerLaunch];         // C_r of the requests of this launch
-  int32_t row_start[kMaxReqPerLaunch + 1];  // first packed row of each request, and the end
+  double inv_freq[64];            // rotation frequency of pair j (rotary_dim/2 entries)
+  int32_t cached[MAXREQ];         // C_r of the requests of this launch
+  int32_t row_start[MAXREQ + 1];  // first packed row of each request, and the end
   int32_t nreq;
-  int32_t req_base;                         // index of the first request (block_table row)
+  int32_t tokens;                 // new tokens of this launch
+  int32_t tok_shift;              // log2 of the tokens of a workgroup
+  int32_t parts;                  // waves per token in a workgroup
+  int32_t req_base;               // index of the first request (block_table row)
   int32_t max_pages;
   int32_t num_q_heads;
   int32_t num_kv_heads;
-  int32_t rotate_q;                         // 0 when q is NULL
-  int32_t rotary_dim;                       // leading elements of a head row that are rotated
-  int32_t page_shift;                       // log2 of the page size (tokens per page)
-  float k_scale;                            // 8-bit caches: code = value / scale
-  float v_scale;
+  int32_t rotary_dim;             // leading elements of a head row that are rotated
+  int32_t page_shift;             // log2 of the page size (tokens per page)
+  double k_inv;                   // 8-bit caches: 1 / scale (code = value / scale)
+  double v_inv;
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-// E4M3 codes of eight bf16 values
-__device__ __forceinline__ u32x2 quantize8(u32x4 x, float scale) {
+// E4M3 codes of eight bf16 values; inv = 1 / (double)scale.
+__device__ __forceinline__ u32x2 quantize8(u32x4 x, double inv) {
+  float f[8];
+  bool nan = false;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    f[2 * t] = bf16_quotient(x[t] << 16, inv);
+    f[2 * t + 1] = bf16_quotient(x[t] & 0xFFFF0000u, inv);
+    nan |= __builtin_isunordered(f[2 * t], f[2 * t + 1]);
+  }
   u32x2 r;
 #pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    const uint32_t lo = x[2 * t], hi = x[2 * t + 1];
-    r[t] = bf16_bits_to_e4m3(lo & 0xFFFFu, scale) | (bf16_bits_to_e4m3(lo >> 16, scale) << 8) |
-           (bf16_bits_to_e4m3(hi & 0xFFFFu, scale) << 16) | (bf16_bits_to_e4m3(hi >> 16, scale) << 24);
+  for (int t = 0; t < 2; ++t)
+    r[t] = e4m3_pair<true>(f[4 * t + 2], f[4 * t + 3], e4m3_pair<false>(f[4 * t], f[4 * t + 1], 0u));
+  if (nan) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+      r[t] = f32_to_e4m3(f[4 * t]) | (f32_to_e4m3(f[4 * t + 1]) << 8) | (f32_to_e4m3(f[4 * t + 2]) << 16) |
+             (f32_to_e4m3(f[4 * t + 3]) << 24);
   }
   return r;
 }
 
-// kTokens = tokens per workgroup: 4 for large steps (all threads busy in the sincos phase),
-// 1 for small ones so that even a few hundred tokens spread over the whole device.
-template <int D, bool INTERLEAVED, int kTokens, bool KV8>
-__global__ __launch_bounds__(kThreads) void rope_append_kernel(
-    const RopeArgs args, uint16_t* __restrict__ q, const uint16_t* __restrict__ k_new,
-    const uint16_t* __restrict__ v_new, void* __restrict__ k_cache_raw,
-    void* __restrict__ v_cache_raw, const int32_t* __restrict__ block_table) {
-#pragma clang fp contract(off)
-  uint16_t* k_cache = static_cast<uint16_t*>(k_cache_raw);
-  uint16_t* v_cache = static_cast<uint16_t*>(v_cache_raw);
-  constexpr int HALF = D / 2;
-  const int rot_half = args.rotary_dim / 2;  // pairs per head row (D/2 when the whole row rotates)
-  __shared__ double s_cos[kTokens][HALF];
-  __shared__ double s_sin[kTokens][HALF];
-  __shared__ int64_t s_dst[kTokens];  // element offset of (page, head 0, slot, 0) in the caches
-
-  const int tid = threadIdx.x;
-  const int first_row = args.row_start[0];
-  const int end_row = args.row_start[args.nreq];
-  const int tok0 = first_row + blockIdx.x * kTokens;
-
-  {
-    const int tt = tid >> 6;
-    const int j = tid & 63;
-    const int row = tok0 + tt;
-    if (tt < kTokens && j < rot_half && row < end_row) {
-      // request of this row: last r with row_start[r] <= row < row_start[r + 1]
-      int lo = 0, hi = args.nreq;  // invariant: row_start[lo] <= row, row_start[hi] > row
-      while (hi - lo > 1) {
-        int mid = (lo + hi) >> 1;
-        if (args.row_start[mid] <= row) lo = mid; else hi = mid;
-      }
-      const int pos = args.cached[lo] + (row - args.row_start[lo]);
-      double s, c;
-      sincos((double)pos * args.inv_freq[j], &s, &c);
-      s_cos[tt][j] = c;
-      s_sin[tt][j] = s;
-      if (j == 0) {
-        const int64_t page =
-            block_table[(int64_t)(args.req_base + lo) * args.max_pages + (pos >> args.page_shift)];
-        s_dst[tt] = (((page * args.num_kv_heads) << args.page_shift) + (pos & ((1 << args.page_shift) - 1))) * D;
-      }
-    }
+// Rotates the eight pairs of a unit.  The results go through fp32 two at a time; the one pattern for
+// which that could round twice is looked for once per unit (one unit in 4000 has it) and the unit
+// then done again value by value.  (With the check and the integer rounding at every value they
+// were half of the kernel's instructions.)
+template <bool INTERLEAVED>
+__device__ __forceinline__ void rotate_units(u32x4& a, u32x4& b, const double (&cs)[8], const double (&sn)[8]) {
+  typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+  uint32_t x1[8], x2[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    // INTERLEAVED: 16 consecutive elements = pairs 0..7, stored (even, odd)
+    const uint32_t w = INTERLEAVED ? (t < 4 ? a[t & 3] : b[t & 3]) : a[t >> 1];
+    const uint32_t v = INTERLEAVED ? w : b[t >> 1];
+    x1[t] = INTERLEAVED || !(t & 1) ? w & 0xFFFFu : w >> 16;
+    x2[t] = INTERLEAVED || (t & 1) ? v >> 16 : v & 0xFFFFu;
   }
-  __syncthreads();
-
-  const int hq = args.num_q_heads, hkv = args.num_kv_heads;
-  // A unit is 16 bytes of one head row together with its partner 16 bytes.  Units inside the
-  // rotated part: for rotate-half the chunk rotary_dim/2 elements further on, for interleaved
-  // pairing the next chunk.  Units behind the rotated part (and all of V) are plain copies of
-  // two neighbouring chunks.
-  constexpr int UNITS_PER_ROW = D / 16;
-  const int rows_per_tok = hq + 2 * hkv;
-  const int units_per_tok = rows_per_tok * UNITS_PER_ROW;
-  const int ntok = min(kTokens, end_row - tok0);
-  for (int u = tid; u < ntok * units_per_tok; u += kThreads) {
-    const int tt = kTokens == 1 ? 0 : u / units_per_tok;  // (the division was 2-3 % of a one-token launch)
-    const int w = u - tt * units_per_tok;
-    const int hr = w / UNITS_PER_ROW;   // 0..Hq-1: q heads, then Hkv k heads, then Hkv v heads
-    const int cp = w - hr * UNITS_PER_ROW;
-    const int64_t row = tok0 + tt;
-    int e0, e1;  // element offsets of the two chunks inside the head row
-    const bool in_rotary = cp * 16 < args.rotary_dim;
-    if (INTERLEAVED || !in_rotary) { e0 = cp * 16; e1 = cp * 16 + 8; } else { e0 = cp * 8; e1 = cp * 8 + rot_half; }
-
-    const uint16_t* src;
-    uint16_t* dst;
-    int64_t cache_off = 0;  // element offset of the head row in the cache
-    bool rotate = in_rotary;
-    if (hr < hq) {
-      if (!args.rotate_q) continue;
-      src = q + (row * hq + hr) * D;
-      dst = q + (row * hq + hr) * D;
-    } else if (hr < hq + hkv) {
-      const int h = hr - hq;
-      src = k_new + (row * hkv + h) * D;
-      cache_off = s_dst[tt] + (((int64_t)h * D) << args.page_shift);
-      dst = k_cache + cache_off;
-    } else {
-      const int h = hr - hq - hkv;
-      src = v_new + (row * hkv + h) * D;
-      cache_off = s_dst[tt] + (((int64_t)h * D) << args.page_shift);
-      dst = v_cache + cache_off;
-      rotate = false;
+  float f1[8], f2[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    double y1, y2;
+    rotate_pair_f64(x1[t], x2[t], cs[t], sn[t], &y1, &y2);
+    f1[t] = (float)y1;
+    f2[t] = (float)y2;
+  }
+  u16x2 off = __builtin_bit_cast(u16x2, off_midpoint(f1[0], f2[0]));
+#pragma unroll
+  for (int t = 1; t < 8; ++t)
+    off = __builtin_elementwise_min(off, __builtin_bit_cast(u16x2, off_midpoint(f1[t], f2[t])));
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    a[t] = INTERLEAVED ? pack_bf16(f1[t], f2[t]) : pack_bf16(f1[2 * t], f1[2 * t + 1]);
+    b[t] = INTERLEAVED ? pack_bf16(f1[4 + t], f2[4 + t]) : pack_bf16(f2[2 * t], f2[2 * t + 1]);
+  }
+  if (off[0] == 0 || off[1] == 0) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      uint32_t y1, y2;
+      rotate_pair_bf16(x1[t], x2[t], cs[t], sn[t], &y1, &y2);
+      x1[t] = y1;
+      x2[t] = y2;
     }
-    u32x4 a = *reinterpret_cast<const u32x4*>(src + e0);
-    u32x4 b = *reinterpret_cast<const u32x4*>(src + e1);
-    if (rotate) {
-      uint32_t xa[8], xb[8];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        xa[2 * t] = a[t] & 0xFFFFu; xa[2 * t + 1] = a[t] >> 16;
-        xb[2 * t] = b[t] & 0xFFFFu; xb[2 * t + 1] = b[t] >> 16;
-      }
-      uint32_t ya[8], yb[8];
-      if (INTERLEAVED) {
-        // 16 consecutive elements = pairs 8*cp .. 8*cp+7, stored (even, odd)
-        uint32_t x[16], y[16];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) { x[t] = xa[t]; x[8 + t] = xb[t]; }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int j = cp * 8 + t;
-          const double c = s_cos[tt][j], s = s_sin[tt][j];
-          rotate_pair_bf16(x[2 * t], x[2 * t + 1], c, s, &y[2 * t], &y[2 * t + 1]);
-        }
-#pragma unroll
-        for (int t = 0; t < 8; ++t) { ya[t] = y[t]; yb[t] = y[8 + t]; }
-      } else {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const int j = cp * 8 + t;
-          const double c = s_cos[tt][j], s = s_sin[tt][j];
-          rotate_pair_bf16(xa[t], xb[t], c, s, &ya[t], &yb[t]);
-        }
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        a[t] = ya[2 * t] | (ya[2 * t + 1] << 16);
-        b[t] = yb[2 * t] | (yb[2 * t + 1] << 16);
-      }
-    }
-    if (KV8 && hr >= hq) {
-      const bool is_k = hr < hq + hkv;
-      uint8_t* row8 = static_cast<uint8_t*>(is_k ? k_cache_raw : v_cache_raw) + cache_off;
-      const float scale = is_k ? args.k_scale : args.v_scale;
-      *reinterpret_cast<u32x2*>(row8 + e0) = quantize8(a, scale);
-      *reinterpret_cast<u32x2*>(row8 + e1) = quantize8(b, scale);
-    } else {
-      *reinterpret_cast<u32x4*>(dst + e0) = a;
-      *reinterpret_cast<u32x4*>(dst + e1) = b;
+    for (int t = 0; t < 4; ++t) {
+      a[t] = INTERLEAVED ? x1[t] | (x2[t] << 16) : x1[2 * t] | (x1[2 * t + 1] << 16);
+      b[t] = INTERLEAVED ? x1[4 + t] | (x2[4 + t] << 16) : x2[2 * t] | (x2[2 * t + 1] << 16);
     }
   }
 }
 
-}  // namespace
+// A wave takes one token and kPasses passes of 64 / (D / 16) head rows of it (a unit is 16 bytes of one head
+// row together with its partner 16 bytes; a lane has the same place in the row in every pass, so that
+// it needs the cosines and sines of the same eight pairs).
+//
+// Up to some ten thousand tokens the kernel is as long as one wave's chain: request of the token, page,
+// cosines, rows.  All loads that need no answer of another go out first -- the request table (64
+// requests per load, the position found by a ballot), the frequency, the wave's rows -- and the page id
+// and the cosines (one pair per lane, exchanged through LDS inside the wave, no barrier) are formed
+// while the rows are on their way.  Before, a workgroup searched the table with one dependent load per
+// step, evaluated the cosines with one of its four waves and read the rows behind a barrier.  us, before / now,
+// passes over the same buffers: 2176 tokens of 16 requests, 32/8 heads 18.6 / 15.0 (other buffers every
+// pass); 1113 tokens, 32/32 heads 11.2 / 9.1; 1014 tokens, 28/4 heads 6.7 / 5.5 (5 us of it the host's), 8-bit
+// cache 8.7 / 5.8; 87286 tokens, 32/8 heads 384 / 365 = 5.9 TB/s.  One pass per wave is 6-10 % slower
+// at 1000 to 2000 tokens, three 0-5 % either way.
+template <int D, bool INTERLEAVED, bool KV8, int MAXREQ>
+__global__ __launch_bounds__(kThreads) void rope_append_kernel(
+    const RopeArgs<MAXREQ> args, uint16_t* __restrict__ q, const uint16_t* __restrict__ k_new,
+    const uint16_t* __restrict__ v_new, void* __restrict__ k_cache_raw,
+    void* __restrict__ v_cache_raw, const int32_t* __restrict__ block_table) {
+#pragma clang fp contract(off)
+  constexpr int HALF = D / 2;
+  constexpr int UNITS_PER_ROW = D / 16;
+  constexpr int ROWS_PER_PASS = 64 / UNITS_PER_ROW;
+  __shared__ __attribute__((aligned(16))) double s_cs[kThreads / 64][HALF][2];  // (cos, sin) of the wave's token
 
-int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const void* k_new,
-                       const void* v_new, void* k_cache, void* v_cache, const double* inv_freq,
-                       int rotary_dim, int interleaved, const CacheFormat& fmt, hipStream_t stream) {
-  (void)total_new;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tok = (blockIdx.x << args.tok_shift) + (wave & ((1 << args.tok_shift) - 1));
+  if (tok >= args.tokens) return;
+  const int part = blockIdx.y * args.parts + (wave >> args.tok_shift);
+  const int row = args.row_start[0] + tok;
+  const int rot_half = args.rotary_dim / 2;  // pairs per head row (D/2 when the whole row rotates)
+
+  const int nreq = args.nreq;
+  int32_t starts[MAXREQ / 64], lens[MAXREQ / 64];
+#pragma unroll
+  for (int i = 0; i < MAXREQ / 64; ++i) {
+    const int r = i * 64 + lane;
+    starts[i] = args.row_start[min(r, nreq)];
+    lens[i] = args.cached[min(r, nreq - 1)];
+  }
+  const double freq = args.inv_freq[lane % HALF];
+
+  const int hq = args.num_q_heads, hkv = args.num_kv_heads;
+  const int rows_per_tok = hq + 2 * hkv;
+  const int cp = lane % UNITS_PER_ROW;
+  const bool in_rotary = cp * 16 < args.rotary_dim;
+  // element offsets of the unit's two chunks inside the head row: inside the rotated part, for rotate-half
+  // the chunk rotary_dim/2 elements further on, for interleaved pairing the next chunk.  Units
+  // behind the rotated part (and all of V) are plain copies of two neighbouring chunks.
+  const bool apart = !INTERLEAVED && in_rotary;
+  const int e0 = apart ? cp * 8 : cp * 16, e1 = apart ? cp * 8 + rot_half : cp * 16 + 8;
+  const int hr0 = part * (kPasses * ROWS_PER_PASS) + lane / UNITS_PER_ROW;
+  u32x4 a[kPasses], b[kPasses];
+#pragma unroll
+  for (int i = 0; i < kPasses; ++i) {
+    // (0..Hq-1: q heads, then Hkv k heads, then Hkv v heads)
+    const int hr = min(hr0 + i * ROWS_PER_PASS, rows_per_tok - 1);
+    const uint16_t* src = k_new + ((int64_t)row * hkv + (hr - hq)) * D;
+    if (hr < hq) src = (q ? q : k_new) + ((int64_t)row * (q ? hq : 0) + (q ? hr : 0)) * D;
+    if (hr >= hq + hkv) src = v_new + ((int64_t)row * hkv + (hr - hq - hkv)) * D;
+    a[i] = *reinterpret_cast<const u32x4*>(src + e0);
+    b[i] = *reinterpret_cast<const u32x4*>(src + e1);
+  }
+
+  // request of this row: the last r with row_start[r] <= row
+  int req = -1;
+#pragma unroll
+  for (int i = 0; i < MAXREQ / 64; ++i)
+    req += __popcll(__ballot(i * 64 + lane < nreq && starts[i] <= row));
+  int pos = 0;
+#pragma unroll
+  for (int i = 0; i < MAXREQ / 64; ++i)
+    if (MAXREQ == 64 || req >> 6 == i)
+      pos = __builtin_amdgcn_readlane(lens[i], req & 63) + row - __builtin_amdgcn_readlane(starts[i], req & 63);
+  const int32_t page_id = block_table[(int64_t)(args.req_base + req) * args.max_pages + (pos >> args.page_shift)];
+  if (lane < rot_half) {
+    double s, c;
+    sincos((double)pos * freq, &s, &c);
+    s_cs[wave][lane][0] = c;
+    s_cs[wave][lane][1] = s;
+  }
+  // (one wave writes and reads: its LDS accesses are in order, the compiler is told by the fence)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  double cs[8], sn[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    cs[t] = s_cs[wave][cp * 8 + t][0];
+    sn[t] = s_cs[wave][cp * 8 + t][1];
+  }
+  // element offset of (page, head 0, slot, 0) in the caches
+  const int64_t slot = ((((int64_t)page_id * hkv) << args.page_shift) + (pos & ((1 << args.page_shift) - 1))) * D;
+
+#pragma unroll
+  for (int i = 0; i < kPasses; ++i) {
+    const int hr = hr0 + i * ROWS_PER_PASS;
+    const bool is_q = hr < hq, is_k = !is_q && hr < hq + hkv;
+    if (in_rotary && hr < hq + hkv) rotate_units<INTERLEAVED>(a[i], b[i], cs, sn);
+    if (hr >= rows_per_tok || (is_q && !q)) continue;
+    const int64_t cache_off = slot + (((int64_t)(hr - hq - (is_k ? 0 : hkv)) * D) << args.page_shift);
+    if (KV8 && !is_q) {
+      uint8_t* row8 = static_cast<uint8_t*>(is_k ? k_cache_raw : v_cache_raw) + cache_off;
+      const double inv = is_k ? args.k_inv : args.v_inv;
+      *reinterpret_cast<u32x2*>(row8 + e0) = quantize8(a[i], inv);
+      *reinterpret_cast<u32x2*>(row8 + e1) = quantize8(b[i], inv);
+    } else {
+      uint16_t* dst = is_q ? q + ((int64_t)row * hq + hr) * D
+                           : static_cast<uint16_t*>(is_k ? k_cache_raw : v_cache_raw) + cache_off;
+      *reinterpret_cast<u32x4*>(dst + e0) = a[i];
+      *reinterpret_cast<u32x4*>(dst + e1) = b[i];
+    }
+  }
+}
+
+template <int MAXREQ>
+int launch_with(const efim_batch_t* b, void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
+                const double* inv_freq, int rotary_dim, int interleaved, const CacheFormat& fmt, hipStream_t stream) {
   const int D = b->head_dim;
-  RopeArgs args;
-  for (int j = 0; j < 64; ++j) args.inv_freq[j] = 0.0;
-  for (int j = 0; j < rotary_dim / 2; ++j) args.inv_freq[j] = inv_freq[j];
+  RopeArgs<MAXREQ> args;
+  for (int j = 0; j < 64; ++j) args.inv_freq[j] = j < rotary_dim / 2 ? inv_freq[j] : 0.0;
   args.rotary_dim = rotary_dim;
   args.page_shift = 0;
   while ((1 << args.page_shift) < b->page_size) ++args.page_shift;
   args.max_pages = b->max_pages_per_req;
   args.num_q_heads = b->num_q_heads;
   args.num_kv_heads = b->num_kv_heads;
-  args.rotate_q = q != nullptr;
-  args.k_scale = fmt.k_scale;
-  args.v_scale = fmt.v_scale;
+  args.k_inv = 1.0 / (double)fmt.k_scale;
+  args.v_inv = 1.0 / (double)fmt.v_scale;
+  const int rows_per_pass = 64 / (D / 16);
+  const int per_wave = kPasses * rows_per_pass;
+  const int waves = (b->num_q_heads + 2 * b->num_kv_heads + per_wave - 1) / per_wave;  // per token
 
   int64_t row = 0;
-  for (int r0 = 0; r0 < b->batch; r0 += kMaxReqPerLaunch) {
-    const int n = (b->batch - r0 < kMaxReqPerLaunch) ? b->batch - r0 : kMaxReqPerLaunch;
+  for (int r0 = 0; r0 < b->batch; r0 += MAXREQ) {
+    const int n = (b->batch - r0 < MAXREQ) ? b->batch - r0 : MAXREQ;
     const int64_t first = row;
     for (int i = 0; i < n; ++i) {
       args.cached[i] = b->cached_len[r0 + i];
@@ -221,21 +264,34 @@ int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const 
     args.req_base = r0;
     const int64_t ntok = row - first;
     if (ntok == 0) continue;
+    args.tokens = (int32_t)ntok;
+    // Workgroups of four waves.  Usually a workgroup takes the same part of four tokens, and all tokens' first
+    // parts go before their second ones.  A large step then reads and writes places far apart
+    // at any time, and the workgroup takes all rows of a token (of two or four where a token has
+    // two waves or one).  us, parts of four tokens / whole tokens: 28/4 heads of 128, 65536 tokens (604
+    // MB) 234 / 216, 32768 106.9 / 105.9, 16384 47.2 / 46.0, 4096 13.3 / 14.5; 32/8 heads of 128, 65536 (805 MB) 299 /
+    // 295, 16384 59.8 / 68.9, 2048 8.9 / 9.6; 32/8 heads of 64, 65536 (403 MB) 148 / 155, 32768 64.7 / 78.8.
+    unsigned groups = (unsigned)waves;
+    args.parts = 1;
+    args.tok_shift = 2;
+    if (ntok * (b->num_q_heads + 2 * b->num_kv_heads) * D * 2 >= kWholeTokenBytes) {
+      groups = (unsigned)((waves + kThreads / 64 - 1) / (kThreads / 64));
+      args.parts = (waves + (int)groups - 1) / (int)groups;
+      args.tok_shift = args.parts == 1 ? 2 : args.parts == 2 ? 1 : 0;
+    }
+    const dim3 grid((unsigned)((ntok + (1 << args.tok_shift) - 1) >> args.tok_shift), groups);
     auto qp = static_cast<uint16_t*>(q);
     auto kn = static_cast<const uint16_t*>(k_new);
     auto vn = static_cast<const uint16_t*>(v_new);
-#define EFIM_ROPE_LAUNCH3(DD, IL, TOK, F8)                                                        \
-  rope_append_kernel<DD, IL, TOK, F8><<<dim3((unsigned)((ntok + TOK - 1) / TOK)), kThreads, 0, stream>>>( \
-      args, qp, kn, vn, k_cache, v_cache, b->block_table)
-#define EFIM_ROPE_LAUNCH(DD, IL, TOK) \
-  do { if (fmt.fp8) EFIM_ROPE_LAUNCH3(DD, IL, TOK, true); else EFIM_ROPE_LAUNCH3(DD, IL, TOK, false); } while (0)
-    const bool small = ntok < 16384;
+#define EFIM_ROPE_LAUNCH3(DD, IL, F8)                                                                       \
+  rope_append_kernel<DD, IL, F8, MAXREQ><<<grid, 64 * args.parts << args.tok_shift, 0, stream>>>(args, qp, kn, vn, k_cache, \
+                                                                                                v_cache, b->block_table)
+#define EFIM_ROPE_LAUNCH(DD, IL) \
+  do { if (fmt.fp8) EFIM_ROPE_LAUNCH3(DD, IL, true); else EFIM_ROPE_LAUNCH3(DD, IL, false); } while (0)
     if (D == 128) {
-      if (interleaved) { if (small) EFIM_ROPE_LAUNCH(128, true, 1); else EFIM_ROPE_LAUNCH(128, true, 4); }
-      else { if (small) EFIM_ROPE_LAUNCH(128, false, 1); else EFIM_ROPE_LAUNCH(128, false, 4); }
+      if (interleaved) EFIM_ROPE_LAUNCH(128, true); else EFIM_ROPE_LAUNCH(128, false);
     } else {
-      if (interleaved) { if (small) EFIM_ROPE_LAUNCH(64, true, 1); else EFIM_ROPE_LAUNCH(64, true, 4); }
-      else { if (small) EFIM_ROPE_LAUNCH(64, false, 1); else EFIM_ROPE_LAUNCH(64, false, 4); }
+      if (interleaved) EFIM_ROPE_LAUNCH(64, true); else EFIM_ROPE_LAUNCH(64, false);
     }
 #undef EFIM_ROPE_LAUNCH
 #undef EFIM_ROPE_LAUNCH3
@@ -243,6 +299,16 @@ int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const 
     if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
   }
   return EFIM_OK;
+}
+
+}  // namespace
+
+int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const void* k_new,
+                       const void* v_new, void* k_cache, void* v_cache, const double* inv_freq,
+                       int rotary_dim, int interleaved, const CacheFormat& fmt, hipStream_t stream) {
+  (void)total_new;
+  auto* launch = b->batch <= 64 ? launch_with<64> : launch_with<kMaxReqPerLaunch>;
+  return launch(b, q, k_new, v_new, k_cache, v_cache, inv_freq, rotary_dim, interleaved, fmt, stream);
 }
 
 }  // namespace efim
