@@ -45,6 +45,8 @@ def build_library(verbose=False, extra_flags=()):
         hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
         "-Wno-unused-command-line-argument",
+        # leading kernel arguments arrive in scalar registers (extend_attention.hip)
+        "-mllvm", "-amdgpu-kernarg-preload-count=16",
         "-I", os.path.join(ROOT, "include"), "-I", CSRC,
         '-DEFIM_SOURCE_DIGEST="%s"' % source_digest(),
     ]

@@ -87,6 +87,9 @@ struct AttnParams {
 };
 
 
+// Bytes of the kernel's arguments in front of its struct (EFIM_ARGS): five pointers and four integers.
+constexpr int kArgsInFront = 5 * 8 + 4 * 4;
+
 constexpr float kSlack = 8.f;  // log2 units by which a row max may outgrow its reference
 
 // Plain nested maxima: the compiler turns them into three-operand max instructions itself and,
@@ -394,7 +397,9 @@ constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bo
 // of 2344 keys, 32/8 heads 11.9 -> 11.2 us, 20 requests of 500..3000 keys, 32/32 heads 124.6 -> 118.4 us, 24
 // drawn steps 3.4 % in the mean, none slower.  With 17 to 32 rows it would take two column blocks.
 template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false, bool ONCE = false, bool R16 = false>
-__global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(const AttnParams p) {
+__global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(
+    const DevItem* items, const int32_t* block_table, const uint16_t* q_rows, const uint16_t* k_pages, const uint16_t* v_pages,
+    const int32_t max_pages, const int32_t kv_heads, const int32_t g, const int32_t ps, const AttnParams p) {
   static_assert(!ONCE || (KP && WAVES == 8 && STAGES == once_tiles(D) && !P8), "the form for few work items");
   static_assert(!PACK || (D == 64 && !KV8 && !KP), "the packed form is for head dim 64, bf16, many rows");
   static_assert(!P8 || (D == 64 && KV8), "other rows are longer");
@@ -457,14 +462,26 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   // the "this workgroup merges" flag is only used once the tile buffers are dead
   int* const s_last = reinterpret_cast<int*>(lds);
 
-  // fused step: rotation frequency of this thread's pair (thread = (token, pair)), read and waited
-  // for in the shadow of the work item's load -- behind the gathers it would wait for them
-  double inv_freq = 0.0;
-  if constexpr (FUSED) inv_freq = p.inv_freq[threadIdx.x % (D / 2)];
+  // Fused step: the rotation frequencies go straight from the kernel's arguments to LDS, a copy for each
+  // wave, ahead of everything (a load into registers would be moved behind the work item's, and waited
+  // for there).  The copy lies where this wave will put its first tokens' cosines and sines.
+  char* const s_table = ONCE ? lds + kTileBufBytes + kFusedBytes : lds + (STAGES - 1) * kStageBytes;
+  char* const s_freq = s_table + (threadIdx.x >> 6) * 1024;
+  if constexpr (FUSED) {
+    typedef const __attribute__((address_space(4))) char* ArgPtr;
+    const ArgPtr freq = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr() + kArgsInFront + offsetof(AttnParams, inv_freq);
+    load_to_lds_16((const void*)(uintptr_t)freq, (threadIdx.x & 31u) * 16u, (uint32_t)(uintptr_t)(LDS_PTR(char))s_freq);
+  }
 
-  const DevItem staged = p.items[blockIdx.x];
+  const DevItem staged = items[blockIdx.x];
   const WorkItem it = staged.w;
-  if (it.row_count == 0) return;
+  // (asked for together with the work item, not one after another where they are used)
+  if constexpr (FUSED) asm volatile("" ::"s"(p.k_new), "s"(p.v_new), "s"(p.rotary_dim), "s"(p.interleaved));
+  asm volatile("" ::"s"(p.num_q_heads), "s"(p.out), "s"(p.part_o), "s"(p.scale_log2), "s"(it.row_count), "s"(staged.cached));
+  if (it.row_count == 0) {
+    if constexpr (FUSED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
+    return;
+  }
   struct { int32_t cached, row_start; } rq;
   rq.cached = staged.cached;
   rq.row_start = staged.row_start;
@@ -474,7 +491,6 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i32 = lane & 31;
   const int hi = lane >> 5;
-  const int g = p.group;
 
   const int wave_row0 = KP ? 0 : wave * 32;
 
@@ -505,7 +521,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
 #pragma unroll
     for (int s = 0; s < kQSteps; ++s) {
       u32x4 v = {0u, 0u, 0u, 0u};
-      if (row_ok) v = *reinterpret_cast<const u32x4*>(p.q + q_off + (D / kQSteps) * s + q_at);
+      if (row_ok) v = *reinterpret_cast<const u32x4*>(q_rows + q_off + (D / kQSteps) * s + q_at);
       qb[s] = __builtin_bit_cast(bf16x8, v);
     }
   }
@@ -524,8 +540,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   const int k_begin = it.key_begin;
   const int k_end = it.key_end;
   const int ntiles = (k_end - k_begin + kKeyTile - 1) / kKeyTile;
-  const int32_t* bt = p.block_table + (int64_t)it.req * p.max_pages;
-  const int ps = p.page_shift;
+  const int32_t* bt = block_table + (int64_t)it.req * max_pages;
   const int page_mask = (1 << ps) - 1;
   const int last_page = (k_end - 1) >> ps;
 
@@ -541,7 +556,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   auto page_of = [&](int rel) -> uint32_t {
     return (uint32_t)btc[__builtin_amdgcn_readfirstlane(min(first_page + (rel >> ps), last_page))];
   };
-  const int64_t page_bytes = ((int64_t)p.num_kv_heads * kGRowBytes) << ps;
+  const int64_t page_bytes = ((int64_t)kv_heads * kGRowBytes) << ps;
   const int64_t head_bytes = ((int64_t)it.kv_head * kGRowBytes) << ps;
   const bool offsets_fit_32 = page_bytes < ((int64_t)1 << 32);  // offsets inside a page, that is
   const int page_loads = (1 << ps) / kGKeysPerLoad;  // 1 KB loads that one page of one head holds
@@ -584,8 +599,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     const uint32_t vbuf = kbuf + kVOff;
     const int key0 = k_begin + t * kKeyTile;
     const bool full_tile = key0 + kKeyTile <= k_end;  // no row of the tile lies past the key range
-    const char* kc = reinterpret_cast<const char*>(p.k_cache);
-    const char* vc = reinterpret_cast<const char*>(p.v_cache);
+    const char* kc = reinterpret_cast<const char*>(k_pages);
+    const char* vc = reinterpret_cast<const char*>(v_pages);
     // (not in the eight-wave key-parallel kernel over bf16 caches: measured 1.5-2.5 % slower there
     // -- that kernel is bound by HBM alone, and its loads do better spaced out)
     constexpr bool kGroupedIssue = !(KP && WAVES == 8 && !KV8) || ONCE;
@@ -1156,8 +1171,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   // 32 requests of 2048..8192 keys, 28/4 heads 74.9 -> 72.3 us, 8-bit cache 43.7 -> 41.6 us; 16
   // requests of 1024..4096 keys, 32/32 heads 124.9 -> 118.9 us.
   const int n_tok = it.row_count / g;  // fused: all rows of the (request, kv head) pair are in this tile
+  double inv_freq = 0.0;  // of this thread's pair (thread = (token, pair))
   if constexpr (FUSED) {
-    asm volatile("" ::"v"(inv_freq) : "memory");
     constexpr int kRawChunks = D / 8;            // 16-byte chunks of a bf16 row
     constexpr int kRowsPerLoad = 64 / kRawChunks;
     static_assert(kFusedRows % kRowsPerLoad == 0 && kFusedMaxTokens * 2 % kRowsPerLoad == 0, "loads fill whole areas");
@@ -1171,15 +1186,25 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
         // (rows past the last are loads of the last one)
         const int r = min(l * kRowsPerLoad + lane / kRawChunks, it.row_count - 1);
         const int tk = r / g;
-        src = p.q + ((int64_t)(rq.row_start + tk) * p.num_q_heads + it.kv_head * g + (r - tk * g)) * D + c8;
+        src = q_rows + ((int64_t)(rq.row_start + tk) * p.num_q_heads + it.kv_head * g + (r - tk * g)) * D + c8;
         dst = (uint32_t)(uintptr_t)(LDS_PTR(char))s_q + l * 1024;
       } else {
         const int r = min((l - q_loads) * kRowsPerLoad + lane / kRawChunks, 2 * n_tok - 1);
-        src = (r & 1 ? p.v_new : p.k_new) + ((int64_t)(rq.row_start + (r >> 1)) * p.num_kv_heads + it.kv_head) * D + c8;
+        src = (r & 1 ? p.v_new : p.k_new) + ((int64_t)(rq.row_start + (r >> 1)) * kv_heads + it.kv_head) * D + c8;
         dst = (uint32_t)(uintptr_t)(LDS_PTR(char))s_raw + (l - q_loads) * 1024;
       }
       load_to_lds_16(src, dst);
     }
+    // the frequencies have landed: all but this wave's raw rows
+    static_assert((kFusedRows + 2 * kFusedMaxTokens) / kRowsPerLoad <= 4 * WAVES, "the wait counts that many loads");
+    switch ((q_loads + kv_loads - wave + WAVES - 1) / WAVES) {
+      case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+      case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+      case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+      case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+      default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    }
+    inv_freq = reinterpret_cast<const double*>(s_freq)[tid % (D / 2)];
   }
   if constexpr (ONCE) {
     // (page ids of all tiles together, one latency, where a page holds the four loads of a wave: bf16 rows of head
@@ -1207,8 +1232,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     // into the tile buffer that no gather has been issued into yet (the last one; ONCE: an area of their own),
     // while the raw rows are on their way; then one task per (row, pair) over the query rows and the key rows.
     const int rot_half = p.rotary_dim / 2;  // pairs per head row (D/2 when the whole row rotates)
-    double* const s_cs =  // [token][pair] (cos, sin)
-        reinterpret_cast<double*>(ONCE ? lds + kTileBufBytes + kFusedBytes : stages + (STAGES - 1) * kStageBytes);
+    double* const s_cs = reinterpret_cast<double*>(s_table);  // [token][pair] (cos, sin)
     static_assert(kFusedMaxTokens * (D / 2) * 16 <= (ONCE ? kTableBytes : kStageBytes), "the cos/sin table must fit");
     {
       const int j = tid % (D / 2);
@@ -1299,7 +1323,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
         const int64_t page = bt[pos >> ps];
         char* cache = reinterpret_cast<char*>(is_v ? p.v_cache_w : p.k_cache_w);
         *reinterpret_cast<u32x4*>(
-            cache + (((page * p.num_kv_heads + it.kv_head) << ps) + (pos & page_mask)) * kGRowBytes + c * 16) = val;
+            cache + (((page * kv_heads + it.kv_head) << ps) + (pos & page_mask)) * kGRowBytes + c * 16) = val;
       }
     }
     return true;
@@ -1718,6 +1742,12 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
   if (i < count) words[i] = 0;
 }
 
+// The kernel's arguments.  Those in front of the struct are in scalar registers when a wave starts (the build asks
+// for that), so that the work item is the first thing it waits for.  With them, the rest of the arguments asked for
+// beside the work item and the frequencies copied to LDS instead of loaded behind it: one request of 2344 keys, 32
+// layers 354 -> 346 us; 32 requests of 2048..8192 keys, 28/4 heads 69.9 -> 69.3 us per layer.
+#define EFIM_ARGS(p) p.items, p.block_table, p.q, p.k_cache, p.v_cache, p.max_pages, p.num_kv_heads, p.group, p.page_shift, p
+
 // Key-parallel kernels: no work item has more than 32 query rows (R16, Plan::rows16: 16), always so for the decode step.
 // Four-wave kernels take two stages over bf16 rows and three over 8-bit rows, where a tile is half
 // as large.  The short step with head dim 64 takes the third stage with more than three work items
@@ -1730,7 +1760,7 @@ template <bool FUSED, bool R16>
 void launch_key_parallel(int head_dim, bool wide, bool fp8, bool crowded, bool once, dim3 grid, const AttnParams& p,
                          hipStream_t stream) {
 #define EFIM_KP(DD, WAVES, STAGES, F8, P8, ONCE) \
-  extend_attention_kernel<DD, WAVES, STAGES, FUSED, F8, true, false, P8, ONCE, R16><<<grid, 64 * (WAVES), 0, stream>>>(p)
+  extend_attention_kernel<DD, WAVES, STAGES, FUSED, F8, true, false, P8, ONCE, R16><<<grid, 64 * (WAVES), 0, stream>>>(EFIM_ARGS(p))
 #define EFIM_KP_FORMS(DD, F8, P8)                            \
   do {                                                       \
     if (wide) EFIM_KP(DD, 8, 3, F8, P8, false);              \
@@ -1768,8 +1798,8 @@ void launch_kernel(int head_dim, const Plan& plan, bool fp8, dim3 grid, const At
   }
 #define EFIM_PIPE(DD, F8, PACK, P8)                                                                            \
   do {                                                                                                        \
-    if (wide) extend_attention_kernel<DD, 8, 3, false, F8, false, PACK, P8><<<grid, 512, 0, stream>>>(p);       \
-    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, false, F8, false, PACK, P8><<<grid, 256, 0, stream>>>(p);  \
+    if (wide) extend_attention_kernel<DD, 8, 3, false, F8, false, PACK, P8><<<grid, 512, 0, stream>>>(EFIM_ARGS(p));       \
+    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, false, F8, false, PACK, P8><<<grid, 256, 0, stream>>>(EFIM_ARGS(p));  \
   } while (0)
   if (head_dim == 128) {
     if (fp8) EFIM_PIPE(128, true, false, false); else EFIM_PIPE(128, false, false, false);
