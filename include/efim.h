@@ -22,7 +22,8 @@
  *    memory at run time.  It keeps a small ring of pinned host staging buffers (host
  *    memory only) for the work list it sends to the device, and its code object carries
  *    static device memory: 2 MiB of arrival counters (one block per launch in flight) with
- *    which the workgroups of a split key range elect the one that combines them, and two
+ *    which the workgroups of a split key range elect the one that combines them and from
+ *    which workgroups that start late draw their work, and two
  *    2 MiB buffers that hold the work lists of batches launched more than once.
  *    If a kernel is killed half-way (device fault, reset) the counters may be left
  *    non-zero; after such an event the process should not keep using the library.

@@ -23,7 +23,7 @@ constexpr int once_rows(int head_dim, bool one_call) { return head_dim == 128 &&
 constexpr int kMaxRowsPerItem = 256;  // largest query-row tile of one workgroup
 constexpr int kStageSlots = 64;       // launch tokens in turn: a token comes round again after this many calls
 constexpr int kTicketSlots = kStageSlots;
-constexpr int kTicketsPerSlot = 8192; // split query tiles one launch can combine in-kernel
+constexpr int kTicketsPerSlot = 8192; // split query tiles one launch can combine in-kernel, and (the last one) its queue
 
 // Device-side view of one request.
 struct ReqInfo {
@@ -82,6 +82,9 @@ struct Plan {
   std::vector<ReqInfo> reqs;
   std::vector<WorkItem> items;
   std::vector<MergeItem> merges;
+  // The items from static_items on may be drawn by the workgroups that start later (0 queued items: none are), of
+  // which `draws` are launched, more than there are items.  mean_tiles: key tiles of an item, in the mean.
+  int static_items = 0, queued_items = 0, draws = 0, mean_tiles = 0;
   int64_t num_partial_slots = 0;
   // byte offsets of the items (as DevItem) and merges inside the staged plan header
   size_t off_items = 0, off_merges = 0, header_bytes = 0;
@@ -117,10 +120,12 @@ int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const 
 // between launches); given, the split key ranges are combined inside the main kernel with these
 // counters and no launch token is needed.  `quiet`: the timing hook is not served (a launch that
 // may be under graph capture records no events).
+// `queue` (optional): a DEVICE counter owned by the caller, zero between launches, from which workgroups draw the
+// plan's queued items; with a launch token the library's own.  Neither: items follow the workgroup ids.
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
-                            int32_t* tickets = nullptr, bool quiet = false);
+                            int32_t* tickets = nullptr, int32_t* queue = nullptr, bool quiet = false);
 
 // Fused short step (every request has 1 .. kFusedMaxTokens new tokens and at most kFusedMaxRows
 // query rows per kv head; the decode step is the case of one token): one launch does the rotary
@@ -132,7 +137,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
                        const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets = nullptr,
-                       bool quiet = false);
+                       int32_t* queue = nullptr, bool quiet = false);
 
 // Clears `count` 32-bit words at `words` with a kernel (a fill that a captured graph may hold).
 int launch_zero_words(int32_t* words, size_t count, hipStream_t stream);

@@ -62,6 +62,7 @@ struct AttnParams {
   uint16_t* part_o;  // [slot][rows_per_item][D] binary16 bits
   float* part_ml;    // [slot][rows_per_item][4] = (running max in log2 units, running sum, a, unused)
   const int32_t* block_table;
+  int32_t static_items;   // the workgroup's item is its id below this
   int32_t max_pages;
   int32_t num_q_heads;
   int32_t num_kv_heads;
@@ -80,6 +81,10 @@ struct AttnParams {
   int32_t ticket_base;    // first arrival counter of this launch in g_tickets (or in `tickets`),
                           // or -1: the split key ranges are combined by merge_kernel in a second launch
   int32_t* tickets;       // the caller's arrival counters, or nullptr: the library's own
+  int32_t* queue;         // the caller's counter of drawn items, or nullptr: the library's own, g_tickets[queue_at]
+  int32_t queue_at;
+  int32_t queued_items;   // items from static_items on are drawn from the queue
+  int32_t draws;          // workgroups that draw
   int32_t page_shift;     // log2 of the page size (tokens per page)
   int32_t interleaved;    // rotary pairing
   int32_t rotary_dim;     // leading elements of a head row that are rotated
@@ -338,6 +343,20 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
   }
 }
 
+// The next queued item for this workgroup, or -1: none is left.  The last of the launch's draws puts the counter back.
+__device__ __forceinline__ int draw_item(const AttnParams& p, int static_items, int* s_draw) {
+  if (threadIdx.x == 0) {
+    int32_t* queue = p.queue ? p.queue : g_tickets + p.queue_at;
+    const int n = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n == p.draws - 1) __hip_atomic_store(queue, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_draw = n;
+  }
+  __syncthreads();
+  const int n = __builtin_amdgcn_readfirstlane(*s_draw);
+  __syncthreads();  // (the word is part of a tile buffer)
+  return n < p.queued_items ? static_items + n : -1;
+}
+
 // WAVES wavefronts per workgroup, 32 query rows each; STAGES LDS buffers of one 64-key K/V
 // tile each.  Launched are
 //   <4 waves, 2 stages>  128 rows, 64 KB LDS with head dim 128, two workgroups per compute unit --
@@ -399,7 +418,8 @@ constexpr int waves_per_simd(int d, int waves, bool fused, bool kv8, bool kp, bo
 template <int D, int WAVES, int STAGES, bool FUSED, bool KV8, bool KP, bool PACK = false, bool P8 = false, bool ONCE = false, bool R16 = false>
 __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUSED, KV8, KP, PACK)) void extend_attention_kernel(
     const DevItem* items, const int32_t* block_table, const uint16_t* q_rows, const uint16_t* k_pages, const uint16_t* v_pages,
-    const int32_t max_pages, const int32_t kv_heads, const int32_t g, const int32_t ps, const AttnParams p) {
+    const int32_t max_pages, const int32_t kv_heads, const int32_t shape, const int32_t static_items, const AttnParams p) {
+  const int g = shape & 0xFF, ps = shape >> 8;  // heads per group (at most 64), log2 of the page size
   static_assert(!ONCE || (KP && WAVES == 8 && STAGES == once_tiles(D) && !P8), "the form for few work items");
   static_assert(!PACK || (D == 64 && !KV8 && !KP), "the packed form is for head dim 64, bf16, many rows");
   static_assert(!P8 || (D == 64 && KV8), "other rows are longer");
@@ -473,7 +493,15 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
     load_to_lds_16((const void*)(uintptr_t)freq, (threadIdx.x & 31u) * 16u, (uint32_t)(uintptr_t)(LDS_PTR(char))s_freq);
   }
 
-  const DevItem staged = items[blockIdx.x];
+  int index = blockIdx.x;
+  if (index >= static_items) {
+    index = draw_item(p, static_items, reinterpret_cast<int*>(lds));
+    if (index < 0) {
+      if constexpr (FUSED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
+      return;
+    }
+  }
+  const DevItem staged = items[index];
   const WorkItem it = staged.w;
   // (asked for together with the work item, not one after another where they are used)
   if constexpr (FUSED) asm volatile("" ::"s"(p.k_new), "s"(p.v_new), "s"(p.rotary_dim), "s"(p.interleaved));
@@ -1709,6 +1737,10 @@ void fill_params(AttnParams* p, const efim_batch_t* b, const Plan& plan, const c
   p->v_cache_w = nullptr;
   p->ticket_base = -1;
   p->tickets = nullptr;
+  p->queue = nullptr;
+  p->queue_at = 0;
+  p->static_items = (int32_t)plan.items.size();
+  p->queued_items = p->draws = 0;
   p->merges = reinterpret_cast<const MergeItem*>(header + plan.off_merges);
   p->page_shift = 0;
   while ((1 << p->page_shift) < b->page_size) ++p->page_shift;
@@ -1734,7 +1766,27 @@ constexpr int kTicketMergeMaxRows = 8;
 bool use_tickets(const Plan& plan) {
   const int knob = tuning().fused_merge;
   const bool want = knob < 0 ? plan.max_item_rows <= kTicketMergeMaxRows : knob != 0;
-  return want && !plan.merges.empty() && plan.merges.size() <= (size_t)kTicketsPerSlot;
+  return want && !plan.merges.empty() && plan.merges.size() < (size_t)kTicketsPerSlot;
+}
+
+// Workgroups of a launch; with a counter to draw from and long items, the plan's queued ones are drawn.  A draw costs
+// a workgroup 1 to 1.5 us before it can start: 16..24 tiles per item 0.8-4.5 % slower drawn (17 requests of 714..1181 +
+// 69..230 tokens, 32/32 heads 110 / 115 us), 28 and more 1-7.5 % faster (57 requests of 5319..16384 keys, one new
+// token, 32/32 heads 1804 / 1669).  A tile of codes takes half the time, and so the line lies at twice the length there
+// (45 requests of 3767..14730 + 8..16 in one call 633 / 617); with at most 16
+// rows per item two workgroups share a unit over codes, start at once and gain nothing (27 requests of
+// 1649..5713 keys, one new token, 175.2 / 179.0).
+unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, int32_t* queue, AttnParams* p) {
+  constexpr int kLongItems = 28;
+  if (plan.queued_items == 0 || plan.mean_tiles < (fp8 ? 2 : 1) * kLongItems || (fp8 && plan.rows16) ||
+      (!queue && stage_slot < 0))
+    return (unsigned)plan.items.size();
+  p->queue = queue;
+  p->queue_at = (stage_slot + 1) * kTicketsPerSlot - 1;
+  p->static_items = plan.static_items;
+  p->queued_items = plan.queued_items;
+  p->draws = plan.draws;
+  return (unsigned)(plan.static_items + plan.draws);
 }
 
 __global__ void zero_words_kernel(int32_t* words, size_t count) {
@@ -1746,7 +1798,8 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 // for that), so that the work item is the first thing it waits for.  With them, the rest of the arguments asked for
 // beside the work item and the frequencies copied to LDS instead of loaded behind it: one request of 2344 keys, 32
 // layers 354 -> 346 us; 32 requests of 2048..8192 keys, 28/4 heads 69.9 -> 69.3 us per layer.
-#define EFIM_ARGS(p) p.items, p.block_table, p.q, p.k_cache, p.v_cache, p.max_pages, p.num_kv_heads, p.group, p.page_shift, p
+#define EFIM_ARGS(p) \
+  p.items, p.block_table, p.q, p.k_cache, p.v_cache, p.max_pages, p.num_kv_heads, p.group | p.page_shift << 8, p.static_items, p
 
 // Key-parallel kernels: no work item has more than 32 query rows (R16, Plan::rows16: 16), always so for the decode step.
 // Four-wave kernels take two stages over bf16 rows and three over 8-bit rows, where a tile is half
@@ -1835,7 +1888,7 @@ int launch_zero_words(int32_t* words, size_t count, hipStream_t stream) {
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
-                            int32_t* tickets, bool quiet) {
+                            int32_t* tickets, int32_t* queue, bool quiet) {
   AttnParams p;
   fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
   if (tickets) {
@@ -1845,7 +1898,7 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
     p.ticket_base = stage_slot * kTicketsPerSlot;
   }
 
-  const dim3 grid((unsigned)plan.items.size());
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, queue, &p));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
@@ -1860,7 +1913,8 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
 int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
-                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets, bool quiet) {
+                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets, int32_t* queue,
+                       bool quiet) {
   AttnParams p;
   fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
   if (tickets) {
@@ -1878,7 +1932,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   const int D = b->head_dim;
   for (int j = 0; j < rotary_dim / 2; ++j) p.inv_freq[j] = inv_freq[j];
 
-  const dim3 grid((unsigned)plan.items.size());
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, queue, &p));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);

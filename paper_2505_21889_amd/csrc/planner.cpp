@@ -389,6 +389,36 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
     while (!plan->items.empty() && plan->items.back().row_count == 0) plan->items.pop_back();
   }
 
+  // Items past the ones that start at once can be drawn from a counter by the workgroups that start later,
+  // longest first, where no two read the same keys.  The dispatcher deals workgroups to the eight XCDs in turn,
+  // the same number to each, but an XCD streams up to 10 % faster or slower than another (which ones
+  // differs from one set of buffers to the next): bound by HBM, with the second half of the items dealt out, the
+  // XCDs ended up to 19 us of 128 apart, drawn 5 of 119.  More workgroups draw than there are items, so that a
+  // fast XCD can take more than its share; the others end at once.  us, dealt out / drawn: 16 requests of
+  // 1024..4096 + 16..128 tokens, 32/32 heads 141.2 / 137.1; one new token, 46 of 2323..2785 keys 355 / 333, 19 of
+  // 3158..10002 368 / 345.  Not where items share keys (28/4 heads, 8..64 new tokens: 117.4 / 122.2): they belong on one XCD.
+  // Nor does it pay to cut ranges for it (28/4 heads, one new token, 496 items that all start at once: with a fifth
+  // of every range as queued pieces of 6 tiles 69.3 / 71.2, 8-bit cache 34.8 / 38.6).  Head dim 64: twice as
+  // many workgroups start at once (four waves: 328 items over codes 20.0 / 24.2 when half of them drew).
+  plan->static_items = (int)plan->items.size();
+  plan->queued_items = plan->draws = 0;
+  int64_t pairs = 0;  // (request, kv head) pairs with work
+  for (int r = 0; r < b->batch; ++r) pairs += b->new_len[r] > 0 ? b->num_kv_heads : 0;
+  const size_t at_once = (size_t)num_slots * (D == 64 ? 2 : 1);
+  plan->mean_tiles = pend.empty() ? 0 : (int)((total_cost - 4 * (int64_t)tiles.size()) / (int64_t)pend.size());
+  if ((int64_t)tiles.size() == pairs && !plan->once && tn.xcd_grouping && plan->items.size() > at_once) {
+    std::vector<WorkItem> rest(plan->items.begin() + at_once, plan->items.end());
+    plan->items.resize(at_once);
+    rest.erase(std::remove_if(rest.begin(), rest.end(), [](const WorkItem& w) { return w.row_count == 0; }), rest.end());
+    std::stable_sort(rest.begin(), rest.end(), [](const WorkItem& a, const WorkItem& c) {
+      return a.key_end - a.key_begin > c.key_end - c.key_begin;
+    });
+    plan->items.insert(plan->items.end(), rest.begin(), rest.end());
+    plan->static_items = (int)at_once;
+    plan->queued_items = (int)rest.size();
+    plan->draws = (plan->queued_items * 3 / 2 + 15) / 8 * 8;
+  }
+
   plan->max_item_rows = 0;
   for (const WorkItem& w : plan->items) plan->max_item_rows = std::max(plan->max_item_rows, (int)w.row_count);
   // Products of 16 rows where no item has more (measured at the kernel).  Not with row tile and ranges both

@@ -1,0 +1,101 @@
+"""Launches with more work items than start at once, none of which share keys: the later ones are drawn from a
+counter.  Every launch has to take each item once and to leave the counter at zero for the next."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_21889_amd import workloads as W
+
+import gpu_util as U
+from test_gpu_decode import oracle_step, run_decode
+
+pytestmark = pytest.mark.gpu
+
+UNITS = 16   # compute units the planner is told to balance for, so that few items are more than start at once
+
+
+@pytest.fixture(scope="module")
+def E():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2505_21889_amd import binding
+    return binding
+
+
+@pytest.fixture(params=[(128, 0), (256, 0), (128, -1), (256, 128)], ids=lambda p: "tile%d split%d" % p)
+def knobs(E, request):
+    E.efim_set_tuning(E.EFIM_TUNE_NUM_SLOTS, 2 * UNITS)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, request.param[0])
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, request.param[1])
+    yield request.param
+    E.efim_set_tuning(E.EFIM_TUNE_NUM_SLOTS, 0)
+    E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+
+
+def batch(pairs, most_new, d, seed):
+    """About `pairs` (request, kv head) pairs of 8/8 heads, one of them without new tokens."""
+    rng = np.random.default_rng(seed)
+    n = rng.integers(1, most_new + 1, size=pairs // 8 + 2).astype(np.int32)
+    c = rng.integers(1900, 2300, size=len(n)).astype(np.int32)
+    c[1] = 40
+    n[2] = 0
+    return W.make_batch("c1", seed=seed, lengths=(c, n), heads=(8, 8), head_dim=d)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("pairs,most_new", [(UNITS + 1, 40), (2 * UNITS + 9, 40), (4 * UNITS + 8, 3), (7 * UNITS, 2)])
+def test_every_item_once_and_again(E, knobs, pairs, most_new, d):
+    b = batch(pairs, most_new, d, pairs + most_new + d)
+    q, kc, vc = U.oracle_inputs(b)
+    first = U.gpu_extend_attention(E, b, q, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_XCD_GROUPING, 0)   # items by workgroup id
+    dealt = U.gpu_extend_attention(E, b, q, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_XCD_GROUPING, 1)
+    assert np.array_equal(first, dealt)
+    for _ in range(2):
+        assert np.array_equal(U.gpu_extend_attention(E, b, q, kc, vc), first)
+    from oracle import efim_oracle as O
+    U.assert_close(first, O.extend_attention(b.cached_len, b.new_len, b.block_table, b.page_size, q, kc, vc),
+                   large_outputs=True)
+
+
+def test_plan_object_launched_again_and_captured(E, knobs):
+    """The counter lies in the plan's workspace: launches in a row and replays of a graph, with other work between."""
+    rng = np.random.default_rng(9)
+    c = rng.integers(1900, 2300, size=4 * UNITS // 8 + 3).astype(np.int32)
+    b = W.make_batch("c1", seed=9, lengths=(c, np.ones_like(c)), heads=(8, 8), head_dim=64)
+    kc, vc = U.oracle_cache(b)
+    _, kc_ref, vc_ref, ref = oracle_step(b, kc, vc)
+    want = run_decode(E, b, kc, vc)[0]
+    U.assert_close(want, ref, large_outputs=True)
+    table = torch.from_numpy(b.block_table).cuda()
+    desc = U.make_desc(E, b, table)
+    plan = E.Plan(desc, decode=True)
+    nbytes = E.efim_plan_workspace_bytes(plan)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    q, kn, vn = U.dev_bits(b.q_new), U.dev_bits(b.k_new), U.dev_bits(b.v_new)
+    kcd, vcd, out = U.dev_bits(kc), U.dev_bits(vc), torch.zeros_like(q)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        E.efim_plan_upload(plan, ws, nbytes, stream)
+
+        def launch():
+            E.efim_decode_step_planned(plan, table, q, kn, vn, kcd, vcd, out, b.rope_base, 0, 0.0, ws, stream)
+        for _ in range(3):
+            out.zero_()
+            launch()
+            stream.synchronize()
+            assert np.array_equal(U.host_bits(out), want)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            launch()
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            stream.synchronize()
+            assert np.array_equal(U.host_bits(out), want)
+            launch()
+            stream.synchronize()
+            assert np.array_equal(U.host_bits(out), want)
+    assert np.array_equal(U.host_bits(kcd), kc_ref) and np.array_equal(U.host_bits(vcd), vc_ref)
