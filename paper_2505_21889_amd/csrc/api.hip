@@ -1,4 +1,5 @@
 // C ABI entry points of libefim: argument checks, planning, staging of the work list.
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -9,8 +10,8 @@
 // for the partial results of split key ranges.  Every device the library runs on holds its own
 // copy until the process ends.  In host code this name is only a handle for
 // hipGetSymbolAddress, never an address.
-constexpr size_t kScratchListBytes = size_t(2) << 20;
-constexpr size_t kScratchPartialBytes = size_t(30) << 20;
+constexpr size_t kScratchListBytes = efim::kStaticListBytes;
+constexpr size_t kScratchPartialBytes = efim::kStaticPartialBytes;
 constexpr size_t kScratchBytes = kScratchListBytes + kScratchPartialBytes;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -310,15 +311,16 @@ void finish_stage(const Plan& plan, hipStream_t stream, const Staged& st) {
 }
 
 // A serving engine calls efim_extend_attention once per layer with the same batch, so the last
-// plan is kept and reused while the host-visible batch description and the knobs are unchanged.
+// plan is kept and reused while the host-visible batch description and the knobs are unchanged:
+// one for bf16 caches and for the size queries, one for 8-bit caches.
 struct PlanCache {
   std::vector<int32_t> key;
   Plan plan;
-  uint64_t next_id = 0;
   bool valid = false;
 };
-PlanCache g_plan_cache;
-std::mutex g_plan_mutex;
+PlanCache g_plan_cache[2];
+uint64_t g_next_plan_id = 0;
+std::mutex g_plan_mutex;  // guards the two
 
 void plan_key(const efim_batch_t* b, int slots, std::vector<int32_t>* key) {
   const Tuning& t = tuning();
@@ -337,17 +339,30 @@ void plan_key(const efim_batch_t* b, int slots, std::vector<int32_t>* key) {
 }
 
 // Returns a copy-free reference valid while g_plan_mutex is held by the caller.
-const Plan& cached_plan(const efim_batch_t* b) {
+const Plan& cached_plan(const efim_batch_t* b, bool fp8 = false) {
   static thread_local std::vector<int32_t> key;
+  PlanCache& cache = g_plan_cache[fp8];
   const int slots = num_slots();
   plan_key(b, slots, &key);
-  if (!g_plan_cache.valid || g_plan_cache.key != key) {
-    build_plan(b, slots, &g_plan_cache.plan);
-    g_plan_cache.plan.id = ++g_plan_cache.next_id;
-    g_plan_cache.key = key;
-    g_plan_cache.valid = true;
+  if (!cache.valid || cache.key != key) {
+    cache.valid = false;
+    build_plan(b, slots, &cache.plan, fp8);
+    cache.plan.id = ++g_next_plan_id;
+    cache.key = key;
+    cache.valid = true;
   }
-  return g_plan_cache.plan;
+  return cache.plan;
+}
+
+// The plan of a call over 8-bit caches, where the workspace (whose size comes from a query that does not know the
+// format) is large enough for it; else the other one.
+const Plan& fp8_plan(const efim_batch_t* b, size_t workspace_bytes) {
+  const int g = b->num_q_heads / b->num_kv_heads;
+  int64_t rows = 0;
+  for (int r = 0; r < b->batch; ++r) rows = std::max(rows, (int64_t)g * b->new_len[r]);
+  if (rows <= 128) return cached_plan(b);  // (they are the same)
+  const Plan& plan = cached_plan(b, true);
+  return plan.total_bytes <= workspace_bytes ? plan : cached_plan(b);
 }
 
 }  // namespace
@@ -471,7 +486,7 @@ int extend_attention_base(const efim_batch_t* batch, const void* q, const void* 
       (reinterpret_cast<uintptr_t>(batch->block_table) & 3u))
     return EFIM_ERR_INVALID_ARG;
   std::lock_guard<std::mutex> lock(g_plan_mutex);
-  const Plan& plan = cached_plan(batch);
+  const Plan& plan = fmt.fp8 ? fp8_plan(batch, workspace_bytes) : cached_plan(batch);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < plan.total_bytes)
     return EFIM_ERR_WORKSPACE;
   if (sm_scale == 0.f) sm_scale = 1.0f / sqrtf((float)batch->head_dim);
@@ -712,7 +727,6 @@ int efim_decode_step_fp8_table(const efim_batch_t* batch, const void* q, const v
 struct efim_plan {
   efim::Plan plan;
   bool decode = false;
-  bool in_kernel_merge = false;
   // scalar fields of the batch the plan was made for
   int32_t batch = 0, num_q_heads = 0, num_kv_heads = 0, head_dim = 0, page_size = 0, max_pages = 0;
   int64_t num_pages = 0, total_new = 0;
@@ -757,7 +771,7 @@ efim_plan_t* efim_plan_create(const efim_batch_t* batch, int decode) {
   pl->num_pages = batch->num_pages;
   pl->total_new = total;
   build_plan(batch, num_slots(), &pl->plan);
-  pl->in_kernel_merge = plan_merges_in_kernel(pl->plan);
+  pl->plan.merge_in_kernel = plan_merges_in_kernel(pl->plan);
   const Plan& plan = pl->plan;
   pl->image.assign(plan.header_bytes, 0);
   DevItem* items = reinterpret_cast<DevItem*>(pl->image.data() + plan.off_items);
@@ -804,9 +818,8 @@ int efim_extend_attention_planned(const efim_plan_t* plan, const int32_t* block_
   const efim_batch_t b = plan_batch_view(plan, block_table);
   char* ws = static_cast<char*>(workspace);
   int32_t* counters = reinterpret_cast<int32_t*>(ws + plan->off_tickets);
-  int32_t* tickets = plan->in_kernel_merge ? counters : nullptr;
   return launch_extend_attention(&b, plan->plan, ws, -1, q, k_cache, v_cache, out, sm_scale, CacheFormat(),
-                                 ws + plan->off_partials, static_cast<hipStream_t>(stream), tickets, counters + plan->plan.merges.size(), true);
+                                 ws + plan->off_partials, static_cast<hipStream_t>(stream), counters, true);
 }
 
 int efim_decode_step_planned(const efim_plan_t* plan, const int32_t* block_table, const void* q,
@@ -831,10 +844,9 @@ int efim_decode_step_planned(const efim_plan_t* plan, const int32_t* block_table
   const efim_batch_t b = plan_batch_view(plan, block_table);
   char* ws = static_cast<char*>(workspace);
   int32_t* counters = reinterpret_cast<int32_t*>(ws + plan->off_tickets);
-  int32_t* tickets = plan->in_kernel_merge ? counters : nullptr;
   return launch_decode_step(&b, plan->plan, ws, -1, q, k_new, v_new, k_cache, v_cache, out, inv_freq, D,
                             rope_interleaved, sm_scale, CacheFormat(), ws + plan->off_partials,
-                            static_cast<hipStream_t>(stream), tickets, counters + plan->plan.merges.size(), true);
+                            static_cast<hipStream_t>(stream), counters, true);
 }
 
 int efim_stream_release(void* stream) {

@@ -25,6 +25,13 @@ constexpr int kStageSlots = 64;       // launch tokens in turn: a token comes ro
 constexpr int kTicketSlots = kStageSlots;
 constexpr int kTicketsPerSlot = 8192; // split query tiles one launch can combine in-kernel, and (the last one) its queue
 
+// Key tiles that the items of a launch have in the mean for its later ones to be drawn (reason at the launch).
+constexpr int kLongItems = 28;
+
+// Fixed device memory of efim_extend_attention_static: for the work list and for the partial results of split key ranges.
+constexpr size_t kStaticListBytes = size_t(2) << 20;
+constexpr size_t kStaticPartialBytes = size_t(30) << 20;
+
 // Device-side view of one request.
 struct ReqInfo {
   int32_t cached;     // C_r
@@ -79,6 +86,7 @@ struct Plan {
   bool once = false;        // few work items of few rows, each short enough for the kernel that gathers a whole range at once
   bool rows16 = false;      // key-parallel kernels: products of 16 rows instead of 32
   bool crowded = false;     // head dim 64: work items crowd the compute units (other forms of the bf16 kernels)
+  int merge_in_kernel = -1; // plan objects: where split ranges are combined, as it was decided with the plan (0 / 1)
   std::vector<ReqInfo> reqs;
   std::vector<WorkItem> items;
   std::vector<MergeItem> merges;
@@ -103,8 +111,8 @@ struct CacheFormat {
 // Validates the host-visible part of a batch. total_new receives T.
 int validate_batch(const efim_batch_t* b, int64_t* total_new);
 
-// Builds the work list. num_slots = number of 4-wave workgroups the device runs concurrently.
-void build_plan(const efim_batch_t* b, int num_slots, Plan* plan);
+// Builds the work list. num_slots = number of 4-wave workgroups the device runs concurrently; fp8: for 8-bit caches.
+void build_plan(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8 = false);
 
 // inv_freq: rotary_dim/2 host values; the leading rotary_dim elements of every head row rotate.
 int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const void* k_new,
@@ -116,16 +124,15 @@ int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const 
 // `stage_slot` is the index of the call's launch token (0 .. kStageSlots-1): it selects the
 // launch's block of arrival counters.  Negative: no token, split key ranges are combined by the
 // second launch.
-// `tickets` (optional): DEVICE arrival counters owned by the caller (one per split query tile, zero
-// between launches); given, the split key ranges are combined inside the main kernel with these
-// counters and no launch token is needed.  `quiet`: the timing hook is not served (a launch that
-// may be under graph capture records no events).
-// `queue` (optional): a DEVICE counter owned by the caller, zero between launches, from which workgroups draw the
-// plan's queued items; with a launch token the library's own.  Neither: items follow the workgroup ids.
+// `counters` (optional): DEVICE counters owned by the caller, one per split query tile and one more, zero between
+// launches; given, they elect the workgroups that combine split key ranges (where the plan does so inside the main
+// kernel) and the last one deals out the plan's queued items, and no launch token is needed.  Neither: the
+// ranges are combined by the second launch and items follow the workgroup ids.  `quiet`: the timing hook is not
+// served (a launch that may be under graph capture records no events).
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
-                            int32_t* tickets = nullptr, int32_t* queue = nullptr, bool quiet = false);
+                            int32_t* counters = nullptr, bool quiet = false);
 
 // Fused short step (every request has 1 .. kFusedMaxTokens new tokens and at most kFusedMaxRows
 // query rows per kv head; the decode step is the case of one token): one launch does the rotary
@@ -136,8 +143,8 @@ constexpr int kFusedMaxTokens = 16;  // new tokens of one request (their rotated
 int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
-                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets = nullptr,
-                       int32_t* queue = nullptr, bool quiet = false);
+                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* counters = nullptr,
+                       bool quiet = false);
 
 // Clears `count` 32-bit words at `words` with a kernel (a fill that a captured graph may hold).
 int launch_zero_words(int32_t* words, size_t count, hipStream_t stream);

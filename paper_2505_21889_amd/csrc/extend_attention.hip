@@ -49,6 +49,8 @@ typedef __attribute__((ext_vector_type(2))) int i32x2;
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
+// (12 lines of 64 bytes with the arguments in front of it; with a thirteenth one request of 2344 keys through 32 layers
+// takes 352 us instead of 345)
 struct AttnParams {
   const DevItem* items;
   const uint16_t* q;
@@ -62,7 +64,6 @@ struct AttnParams {
   uint16_t* part_o;  // [slot][rows_per_item][D] binary16 bits
   float* part_ml;    // [slot][rows_per_item][4] = (running max in log2 units, running sum, a, unused)
   const int32_t* block_table;
-  int32_t static_items;   // the workgroup's item is its id below this
   int32_t max_pages;
   int32_t num_q_heads;
   int32_t num_kv_heads;
@@ -80,20 +81,21 @@ struct AttnParams {
   const MergeItem* merges;
   int32_t ticket_base;    // first arrival counter of this launch in g_tickets (or in `tickets`),
                           // or -1: the split key ranges are combined by merge_kernel in a second launch
-  int32_t* tickets;       // the caller's arrival counters, or nullptr: the library's own
-  int32_t* queue;         // the caller's counter of drawn items, or nullptr: the library's own, g_tickets[queue_at]
-  int32_t queue_at;
-  int32_t queued_items;   // items from static_items on are drawn from the queue
-  int32_t draws;          // workgroups that draw
+  int32_t* tickets;       // the caller's counters, or nullptr: the library's own
   int32_t page_shift;     // log2 of the page size (tokens per page)
   int32_t interleaved;    // rotary pairing
   int32_t rotary_dim;     // leading elements of a head row that are rotated
   double inv_freq[64];    // rotation frequency of pair j (rotary_dim / 2 entries)
+  int32_t queue_at;       // the counter of drawn items, behind the arrival counters (`tickets`, or g_tickets)
+  int32_t queued_items;   // items from static_items on are drawn from the queue
+  int32_t draws;          // workgroups that draw
+  int32_t static_items;   // the workgroup's item is its id below this
 };
 
 
 // Bytes of the kernel's arguments in front of its struct (EFIM_ARGS): five pointers and four integers.
 constexpr int kArgsInFront = 5 * 8 + 4 * 4;
+static_assert(kArgsInFront + sizeof(AttnParams) <= 12 * 64, "lines of the kernel's arguments");
 
 constexpr float kSlack = 8.f;  // log2 units by which a row max may outgrow its reference
 
@@ -346,7 +348,7 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // The next queued item for this workgroup, or -1: none is left.  The last of the launch's draws puts the counter back.
 __device__ __forceinline__ int draw_item(const AttnParams& p, int static_items, int* s_draw) {
   if (threadIdx.x == 0) {
-    int32_t* queue = p.queue ? p.queue : g_tickets + p.queue_at;
+    int32_t* queue = (p.tickets ? p.tickets : g_tickets) + p.queue_at;
     const int n = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == p.draws - 1) __hip_atomic_store(queue, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *s_draw = n;
@@ -494,11 +496,15 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   }
 
   int index = blockIdx.x;
-  if (index >= static_items) {
-    index = draw_item(p, static_items, reinterpret_cast<int*>(lds));
-    if (index < 0) {
-      if constexpr (FUSED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
-      return;
+  // (ONCE: all items start at once.  Out of the way elsewhere, too: with the draw in the straight line of the code one
+  // request of 2344 keys through 32 layers took 353 us instead of 346, two of 4290 and 10819 18.3 instead of 17.5.)
+  if constexpr (!ONCE) {
+    if (__builtin_expect(index >= static_items, 0)) {
+      index = draw_item(p, static_items, reinterpret_cast<int*>(lds));
+      if (index < 0) {
+        if constexpr (FUSED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
+        return;
+      }
     }
   }
   const DevItem staged = items[index];
@@ -1737,7 +1743,6 @@ void fill_params(AttnParams* p, const efim_batch_t* b, const Plan& plan, const c
   p->v_cache_w = nullptr;
   p->ticket_base = -1;
   p->tickets = nullptr;
-  p->queue = nullptr;
   p->queue_at = 0;
   p->static_items = (int32_t)plan.items.size();
   p->queued_items = p->draws = 0;
@@ -1764,6 +1769,7 @@ namespace {
 // 45.8; head dim 64 gains up to 16 rows with few parts (107.6 / 107.3) and loses as much with ten (40.1 / 44.0).
 constexpr int kTicketMergeMaxRows = 8;
 bool use_tickets(const Plan& plan) {
+  if (plan.merge_in_kernel >= 0) return plan.merge_in_kernel != 0;
   const int knob = tuning().fused_merge;
   const bool want = knob < 0 ? plan.max_item_rows <= kTicketMergeMaxRows : knob != 0;
   return want && !plan.merges.empty() && plan.merges.size() < (size_t)kTicketsPerSlot;
@@ -1776,13 +1782,11 @@ bool use_tickets(const Plan& plan) {
 // (45 requests of 3767..14730 + 8..16 in one call 633 / 617); with at most 16
 // rows per item two workgroups share a unit over codes, start at once and gain nothing (27 requests of
 // 1649..5713 keys, one new token, 175.2 / 179.0).
-unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, int32_t* queue, AttnParams* p) {
-  constexpr int kLongItems = 28;
+unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, int32_t* counters, AttnParams* p) {
   if (plan.queued_items == 0 || plan.mean_tiles < (fp8 ? 2 : 1) * kLongItems || (fp8 && plan.rows16) ||
-      (!queue && stage_slot < 0))
+      (!counters && stage_slot < 0))
     return (unsigned)plan.items.size();
-  p->queue = queue;
-  p->queue_at = (stage_slot + 1) * kTicketsPerSlot - 1;
+  p->queue_at = counters ? (int32_t)plan.merges.size() : (stage_slot + 1) * kTicketsPerSlot - 1;
   p->static_items = plan.static_items;
   p->queued_items = plan.queued_items;
   p->draws = plan.draws;
@@ -1888,17 +1892,17 @@ int launch_zero_words(int32_t* words, size_t count, hipStream_t stream) {
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
-                            int32_t* tickets, int32_t* queue, bool quiet) {
+                            int32_t* counters, bool quiet) {
   AttnParams p;
   fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
-  if (tickets) {
-    p.tickets = tickets;
-    p.ticket_base = 0;
+  p.tickets = counters;
+  if (counters) {
+    if (use_tickets(plan)) p.ticket_base = 0;
   } else if (stage_slot >= 0 && use_tickets(plan)) {
     p.ticket_base = stage_slot * kTicketsPerSlot;
   }
 
-  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, queue, &p));
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, counters, &p));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
@@ -1913,13 +1917,12 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
 int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
-                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets, int32_t* queue,
-                       bool quiet) {
+                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* counters, bool quiet) {
   AttnParams p;
   fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
-  if (tickets) {
-    p.tickets = tickets;
-    p.ticket_base = 0;
+  p.tickets = counters;
+  if (counters) {
+    if (use_tickets(plan)) p.ticket_base = 0;
   } else if (stage_slot >= 0 && use_tickets(plan)) {
     p.ticket_base = stage_slot * kTicketsPerSlot;
   }
@@ -1932,7 +1935,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   const int D = b->head_dim;
   for (int j = 0; j < rotary_dim / 2; ++j) p.inv_freq[j] = inv_freq[j];
 
-  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, queue, &p));
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, counters, &p));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);

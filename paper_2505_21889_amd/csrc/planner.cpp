@@ -59,9 +59,9 @@ struct Tile {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-}  // namespace
-
-void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
+// Builds the plan.  wide: compute-heavy steps and steps of many tiles take 256 rows whatever their ranges.  Returns
+// whether it took 128 where `wide` would take 256.
+bool build(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8, bool wide) {
   const int g = b->num_q_heads / b->num_kv_heads;
   const int D = b->head_dim;
   plan->reqs.clear();
@@ -78,30 +78,47 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
     row += b->new_len[r];
     max_rows = std::max<int64_t>(max_rows, (int64_t)g * b->new_len[r]);
   }
-  // Query-row tile of a workgroup: 128 rows (each of the 4 waves owns 32; two workgroups per
-  // compute unit, suits steps bound by HBM) or, when some kv head has more rows than that and
-  // the step is therefore compute-heavy, 256 rows (8 waves of 32; one workgroup per unit).
-  // "Compute-heavy" = arithmetic intensity (flop per K/V/Q/O byte) above the machine balance
-  // of about 315 flop/byte (2.5 PFLOP/s over 8 TB/s).
+  // Query-row tile of a workgroup: 128 rows (each of the 4 waves owns 32; two workgroups per compute unit) or 256 (8
+  // waves; one workgroup per unit, which gathers a key tile once for twice the rows and two tiles ahead).
+  // The loops of both do the same work in the same time (8 waves 1.84 us per key tile of a unit, two times 4 waves
+  // 1.83), so what surrounds them decides.  Two workgroups on a unit cover each other's start and end, and half
+  // the tile leaves less of a last tile empty and packs better; with long ranges the gathers count and little else
+  // does.  A compute-heavy step ("compute-heavy": more than the machine balance of about 315 flop per byte, 2.5
+  // PFLOP/s over 8 TB/s) takes 128 rows up to 32 key tiles in the mean, 64 with head dim 64, and always over 8-bit
+  // caches.  256 / 128 rows, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim
+  // 128, up to 32 tiles 0.95 (0.77 .. 1.02), 32 to 100 tiles 0.99 (0.95 .. 1.02), above 1.01 (0.94 .. 1.06); head dim 64,
+  // up to 64 tiles 0.96 (0.87 .. 1.01); 8-bit caches, 9 to 214 tiles, 0.92 (0.80 .. 0.98).
+  // A step bound by HBM takes 256 rows when it has at least two such tiles per compute unit, which then balance
+  // over the units without cutting key ranges (no merge pass), and few of its key ranges are read by more
+  // than one tile (34 requests of 824..1782 + 203..512 tokens, 32/32 heads: 416 / 396 us).
   const Tuning& tn0 = tuning();
-  double flops = 0.0, bytes = 0.0;
+  const double long_keys = 32.0 * kKeyTile * 128 / D;  // keys a row sees, in the mean over the work
+  double flops = 0.0, bytes = 0.0, work = 0.0, work_keys = 0.0, keys = 0.0, keys_read = 0.0;
+  int64_t wide_tiles = 0;
   for (int r = 0; r < b->batch; ++r) {
     const double n = b->new_len[r], c = b->cached_len[r];
     if (n == 0) continue;
-    flops += 4.0 * D * b->num_q_heads * n * (c + 0.5 * (n + 1));
+    const double seen = c + 0.5 * (n + 1);  // keys a row sees, in the mean
+    const int64_t t = ((int64_t)g * b->new_len[r] + 255) / 256;
+    flops += 4.0 * D * b->num_q_heads * n * seen;
     bytes += 4.0 * D * ((c + n) * b->num_kv_heads + n * b->num_q_heads);
+    work += n * seen;
+    work_keys += n * seen * seen;
+    keys += c + n;
+    keys_read += t * c + n * (t + 1) / 2;
+    wide_tiles += b->num_kv_heads * t;
   }
-  // A step bound by HBM also takes the 256-row configuration when it has at least two such
-  // tiles per compute unit: the tiles then balance over the 256 slots without cutting key
-  // ranges (no merge pass), and that configuration gathers two tiles ahead.
   int M = 128;
+  bool narrowed = false;
   if (tn0.row_tile == 256) {
     M = 256;
   } else if (tn0.row_tile == 0) {
-    int64_t wide_tiles = 0;
-    for (int r = 0; r < b->batch; ++r)
-      wide_tiles += (int64_t)b->num_kv_heads * (((int64_t)g * b->new_len[r] + 255) / 256);
-    if ((max_rows > 128 && flops > 315.0 * bytes) || wide_tiles >= num_slots) M = 256;
+    const bool heavy = max_rows > 128 && flops > 315.0 * bytes;
+    if (heavy || wide_tiles >= num_slots) {
+      const bool narrow = heavy ? fp8 || work_keys < long_keys * work : max_rows > 128 && keys_read >= 1.5 * keys;
+      narrowed = narrow && !wide;
+      if (!narrowed) M = 256;
+    }
   }
   plan->rows_per_item = M;
   if (M == 256) num_slots = std::max(1, num_slots / 2);  // 8-wave workgroups: one per compute unit
@@ -356,10 +373,16 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
     // heaviest item first): the workgroups resident at any time then read the K/V of only one
     // or two (request, kv head) pairs, which fits the 4 MB L2, instead of a slice of all of them.
     // With few query tiles per pair there is little to share and plain heaviest-first order
-    // balances better.
+    // balances better, unless K/V are read twice and more and are larger than the 256 MB cache behind
+    // the L2s (34 requests of 824..1782 + 203..512 tokens, 32/32 heads, 920 MB: 466 us heaviest first, 396 by
+    // group; 10 requests of which three are full misses, the others one tile per pair: 113 / 117).
     int64_t live_groups = 0;
     for (int64_t gi = 0; gi < ngroups; ++gi) live_groups += gcost[gi] > 0;
-    const bool group_major = (int64_t)tiles.size() >= 4 * std::max<int64_t>(1, live_groups);
+    double tile_keys = 0.0;
+    for (const Tile& t : tiles) tile_keys += t.key_end;
+    const double pair_keys = keys * b->num_kv_heads;
+    const bool group_major = (int64_t)tiles.size() >= 4 * std::max<int64_t>(1, live_groups) ||
+                             (tile_keys >= 2.0 * pair_keys && pair_keys * 4.0 * D > 256.0 * (1 << 20));
     std::vector<Pending> per[kXcds];
     for (auto& p : pend) per[gx[p.group]].push_back(p);
     size_t longest = 0;
@@ -406,7 +429,8 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   for (int r = 0; r < b->batch; ++r) pairs += b->new_len[r] > 0 ? b->num_kv_heads : 0;
   const size_t at_once = (size_t)num_slots * (D == 64 ? 2 : 1);
   plan->mean_tiles = pend.empty() ? 0 : (int)((total_cost - 4 * (int64_t)tiles.size()) / (int64_t)pend.size());
-  if ((int64_t)tiles.size() == pairs && !plan->once && tn.xcd_grouping && plan->items.size() > at_once) {
+  if ((int64_t)tiles.size() == pairs && !plan->once && tn.xcd_grouping && plan->items.size() > at_once &&
+      plan->mean_tiles >= kLongItems) {
     std::vector<WorkItem> rest(plan->items.begin() + at_once, plan->items.end());
     plan->items.resize(at_once);
     rest.erase(std::remove_if(rest.begin(), rest.end(), [](const WorkItem& w) { return w.row_count == 0; }), rest.end());
@@ -444,6 +468,17 @@ void build_plan(const efim_batch_t* b, int num_slots, Plan* plan) {
   plan->off_part_ml = off;
   off = align_up(off + (size_t)plan->num_partial_slots * prows * 4 * sizeof(float), 256);
   plan->total_bytes = off < 256 ? 256 : off;  // never zero, so callers always pass a real buffer
+  return narrowed;
+}
+
+}  // namespace
+
+void build_plan(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8) {
+  // 128 rows make up to twice the items and other cuts.  Where those outgrow what efim_extend_attention_static
+  // holds, the step stays at 256: nothing that call takes there is refused.
+  if (build(b, num_slots, plan, fp8, false) &&
+      (plan->header_bytes > kStaticListBytes || plan->total_bytes > kStaticPartialBytes))
+    (void)build(b, num_slots, plan, fp8, true);
 }
 
 }  // namespace efim
