@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 # on: the digest of extend_attention.hip is recorded with it and checked at run time.
 MEASURED_TRAFFIC = {
     # workload: (bytes per launch, sha256 of csrc/extend_attention.hip when measured)
-    "c5": (2531706000, "3696ad401aab91a82ca862c27219c5edf4d80ee23e24d049ed95ebdcc3ff57b8"),
+    "c5": (2531706000, "cf316faa7cc59d31f3dd3b7519e543f66eee727f965e0106093ea56b790d459f"),
 }
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak

@@ -361,13 +361,12 @@ __device__ __forceinline__ int draw_item(const AttnParams& p, int static_items, 
 
 // WAVES wavefronts per workgroup, 32 query rows each; STAGES LDS buffers of one 64-key K/V
 // tile each.  Launched are
-//   <4 waves, 2 stages>  128 rows, 64 KB LDS with head dim 128, two workgroups per compute unit --
-//                        steps bound by HBM, where many small independent gathers in flight
-//                        matter; three stages where a tile is half as large (8-bit caches; the
-//                        short step with head dim 64 and many work items);
-//   <8 waves, 3 stages>  256 rows, 96 KB LDS with head dim 128, one workgroup per compute unit --
-//                        compute-heavy steps, where each gathered K/V byte is used by twice as
-//                        many rows and the gather runs two tiles ahead.
+//   <4 waves, 2 stages>  128 rows, 64 KB LDS with head dim 128, two workgroups per compute unit, which cover each
+//                        other's start and end; three stages where a tile is half as large (8-bit caches;
+//                        the short step with head dim 64 and many work items);
+//   <8 waves, 3 stages>  256 rows, 96 KB LDS with head dim 128, one workgroup per compute unit: each gathered
+//                        K/V byte is used by twice as many rows and the gather runs two tiles ahead.
+// The planner's rule of the row tile chooses.
 //
 // FUSED (decode step and other short steps: every request has at most kFusedMaxTokens new
 // tokens and at most 32 query rows per kv head, so all rows of a (request, kv head) pair are
