@@ -348,7 +348,9 @@ int64_t efim_session_count(efim_session_pool_t* pool);
  *                             enqueued behind it on the same stream (or ordered behind it by
  *                             events).  Not capturable (it copies).  One workspace belongs to
  *                             one plan; launches that use the same workspace at the same time
- *                             race, launches on one stream or in one graph do not.
+ *                             race where the plan cuts key ranges (arrival counters and partial
+ *                             results lie there), launches one after the other on a stream or
+ *                             in a graph do not.
  *   efim_extend_attention_planned / efim_decode_step_planned
  *                             efim_extend_attention / efim_decode_step for the planned batch:
  *                             same arguments minus the batch description, plus the batch's

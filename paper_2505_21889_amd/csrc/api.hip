@@ -727,6 +727,7 @@ int efim_decode_step_fp8_table(const efim_batch_t* batch, const void* q, const v
 struct efim_plan {
   efim::Plan plan;
   bool decode = false;
+  bool in_kernel_merge = false;
   // scalar fields of the batch the plan was made for
   int32_t batch = 0, num_q_heads = 0, num_kv_heads = 0, head_dim = 0, page_size = 0, max_pages = 0;
   int64_t num_pages = 0, total_new = 0;
@@ -771,7 +772,7 @@ efim_plan_t* efim_plan_create(const efim_batch_t* batch, int decode) {
   pl->num_pages = batch->num_pages;
   pl->total_new = total;
   build_plan(batch, num_slots(), &pl->plan);
-  pl->plan.merge_in_kernel = plan_merges_in_kernel(pl->plan);
+  pl->in_kernel_merge = plan_merges_in_kernel(pl->plan);
   const Plan& plan = pl->plan;
   pl->image.assign(plan.header_bytes, 0);
   DevItem* items = reinterpret_cast<DevItem*>(pl->image.data() + plan.off_items);
@@ -783,7 +784,7 @@ efim_plan_t* efim_plan_create(const efim_batch_t* batch, int decode) {
   if (!plan.merges.empty())
     std::memcpy(pl->image.data() + plan.off_merges, plan.merges.data(), plan.merges.size() * sizeof(MergeItem));
   pl->off_tickets = align256(plan.header_bytes);
-  pl->off_partials = pl->off_tickets + align256((plan.merges.size() + 1) * sizeof(int32_t));
+  pl->off_partials = pl->off_tickets + align256(plan.merges.size() * sizeof(int32_t));
   pl->total_bytes = pl->off_partials + plan.total_bytes;
   return pl;
 }
@@ -800,7 +801,7 @@ int efim_plan_upload(efim_plan_t* plan, void* workspace, size_t workspace_bytes,
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   EFIM_HIP(hipMemcpyAsync(ws, plan->image.data(), plan->image.size(), hipMemcpyHostToDevice, s));
-  return launch_zero_words(reinterpret_cast<int32_t*>(ws + plan->off_tickets), plan->plan.merges.size() + 1, s);
+  return launch_zero_words(reinterpret_cast<int32_t*>(ws + plan->off_tickets), plan->plan.merges.size(), s);
 }
 
 int efim_extend_attention_planned(const efim_plan_t* plan, const int32_t* block_table, const void* q,
@@ -817,9 +818,9 @@ int efim_extend_attention_planned(const efim_plan_t* plan, const int32_t* block_
   if (sm_scale == 0.f) sm_scale = 1.0f / sqrtf((float)plan->head_dim);
   const efim_batch_t b = plan_batch_view(plan, block_table);
   char* ws = static_cast<char*>(workspace);
-  int32_t* counters = reinterpret_cast<int32_t*>(ws + plan->off_tickets);
+  int32_t* tickets = plan->in_kernel_merge ? reinterpret_cast<int32_t*>(ws + plan->off_tickets) : nullptr;
   return launch_extend_attention(&b, plan->plan, ws, -1, q, k_cache, v_cache, out, sm_scale, CacheFormat(),
-                                 ws + plan->off_partials, static_cast<hipStream_t>(stream), counters, true);
+                                 ws + plan->off_partials, static_cast<hipStream_t>(stream), tickets, true);
 }
 
 int efim_decode_step_planned(const efim_plan_t* plan, const int32_t* block_table, const void* q,
@@ -843,10 +844,10 @@ int efim_decode_step_planned(const efim_plan_t* plan, const int32_t* block_table
   for (int j = 0; j < D / 2; ++j) inv_freq[j] = pow(rope_base, -2.0 * j / D);
   const efim_batch_t b = plan_batch_view(plan, block_table);
   char* ws = static_cast<char*>(workspace);
-  int32_t* counters = reinterpret_cast<int32_t*>(ws + plan->off_tickets);
+  int32_t* tickets = plan->in_kernel_merge ? reinterpret_cast<int32_t*>(ws + plan->off_tickets) : nullptr;
   return launch_decode_step(&b, plan->plan, ws, -1, q, k_new, v_new, k_cache, v_cache, out, inv_freq, D,
                             rope_interleaved, sm_scale, CacheFormat(), ws + plan->off_partials,
-                            static_cast<hipStream_t>(stream), counters, true);
+                            static_cast<hipStream_t>(stream), tickets, true);
 }
 
 int efim_stream_release(void* stream) {

@@ -86,7 +86,6 @@ struct Plan {
   bool once = false;        // few work items of few rows, each short enough for the kernel that gathers a whole range at once
   bool rows16 = false;      // key-parallel kernels: products of 16 rows instead of 32
   bool crowded = false;     // head dim 64: work items crowd the compute units (other forms of the bf16 kernels)
-  int merge_in_kernel = -1; // plan objects: where split ranges are combined, as it was decided with the plan (0 / 1)
   std::vector<ReqInfo> reqs;
   std::vector<WorkItem> items;
   std::vector<MergeItem> merges;
@@ -124,15 +123,14 @@ int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const 
 // `stage_slot` is the index of the call's launch token (0 .. kStageSlots-1): it selects the
 // launch's block of arrival counters.  Negative: no token, split key ranges are combined by the
 // second launch.
-// `counters` (optional): DEVICE counters owned by the caller, one per split query tile and one more, zero between
-// launches; given, they elect the workgroups that combine split key ranges (where the plan does so inside the main
-// kernel) and the last one deals out the plan's queued items, and no launch token is needed.  Neither: the
-// ranges are combined by the second launch and items follow the workgroup ids.  `quiet`: the timing hook is not
-// served (a launch that may be under graph capture records no events).
+// `tickets` (optional): DEVICE arrival counters owned by the caller (one per split query tile, zero between launches);
+// given, the split key ranges are combined inside the main kernel with these counters and no launch token is needed.
+// Without a token items follow the workgroup ids.  `quiet`: the timing hook is not served (a launch that may be
+// under graph capture records no events).
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
-                            int32_t* counters = nullptr, bool quiet = false);
+                            int32_t* tickets = nullptr, bool quiet = false);
 
 // Fused short step (every request has 1 .. kFusedMaxTokens new tokens and at most kFusedMaxRows
 // query rows per kv head; the decode step is the case of one token): one launch does the rotary
@@ -143,7 +141,7 @@ constexpr int kFusedMaxTokens = 16;  // new tokens of one request (their rotated
 int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
-                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* counters = nullptr,
+                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets = nullptr,
                        bool quiet = false);
 
 // Clears `count` 32-bit words at `words` with a kernel (a fill that a captured graph may hold).

@@ -82,12 +82,12 @@ struct AttnParams {
   const MergeItem* merges;
   int32_t ticket_base;    // first arrival counter of this launch in g_tickets (or in `tickets`),
                           // or -1: the split key ranges are combined by merge_kernel in a second launch
-  int32_t* tickets;       // the caller's counters, or nullptr: the library's own
+  int32_t* tickets;       // the caller's arrival counters, or nullptr: the library's own
   int32_t page_shift;     // log2 of the page size (tokens per page)
   int32_t interleaved;    // rotary pairing
   int32_t rotary_dim;     // leading elements of a head row that are rotated
   double inv_freq[64];    // rotation frequency of pair j (rotary_dim / 2 entries)
-  int32_t queue_at;       // the counter of drawn items, behind the arrival counters (`tickets`, or g_tickets)
+  int32_t queue_at;       // the counter of drawn items, in g_tickets
   int32_t queued_items;   // items from static_items on are drawn from the queue
   int32_t draws;          // workgroups that draw
   int32_t static_items;   // the workgroup's item is its id below this
@@ -348,7 +348,7 @@ __device__ __forceinline__ void merge_rows(const AttnParams& p, const MergeItem&
 // The next queued item for this workgroup, or -1: none is left.  The last of the launch's draws puts the counter back.
 __device__ __forceinline__ int draw_item(const AttnParams& p, int static_items, int* s_draw) {
   if (threadIdx.x == 0) {
-    int32_t* queue = (p.tickets ? p.tickets : g_tickets) + p.queue_at;
+    int32_t* queue = g_tickets + p.queue_at;
     const int n = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (n == p.draws - 1) __hip_atomic_store(queue, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     *s_draw = n;
@@ -1768,24 +1768,24 @@ namespace {
 // 45.8; head dim 64 gains up to 16 rows with few parts (107.6 / 107.3) and loses as much with ten (40.1 / 44.0).
 constexpr int kTicketMergeMaxRows = 8;
 bool use_tickets(const Plan& plan) {
-  if (plan.merge_in_kernel >= 0) return plan.merge_in_kernel != 0;
   const int knob = tuning().fused_merge;
   const bool want = knob < 0 ? plan.max_item_rows <= kTicketMergeMaxRows : knob != 0;
   return want && !plan.merges.empty() && plan.merges.size() < (size_t)kTicketsPerSlot;
 }
 
-// Workgroups of a launch; with a counter to draw from and long items, the plan's queued ones are drawn.  A draw costs
+// Workgroups of a launch; with a launch token, whose block of counters is this launch's alone, and long items, the
+// plan's queued ones are drawn.  (A plan object's launches have none: a counter in the workspace would be
+// shared by launches of one plan that run at the same time, which where no range is cut only read it.)  A draw costs
 // a workgroup 1 to 1.5 us before it can start: 16..24 tiles per item 0.8-4.5 % slower drawn (17 requests of 714..1181 +
 // 69..230 tokens, 32/32 heads 110 / 115 us), 28 and more 1-7.5 % faster (57 requests of 5319..16384 keys, one new
 // token, 32/32 heads 1804 / 1669).  A tile of codes takes half the time, and so the line lies at twice the length there
 // (45 requests of 3767..14730 + 8..16 in one call 633 / 617); with at most 16
 // rows per item two workgroups share a unit over codes, start at once and gain nothing (27 requests of
 // 1649..5713 keys, one new token, 175.2 / 179.0).
-unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, int32_t* counters, AttnParams* p) {
-  if (plan.queued_items == 0 || plan.mean_tiles < (fp8 ? 2 : 1) * kLongItems || (fp8 && plan.rows16) ||
-      (!counters && stage_slot < 0))
+unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, AttnParams* p) {
+  if (plan.queued_items == 0 || plan.mean_tiles < (fp8 ? 2 : 1) * kLongItems || (fp8 && plan.rows16) || stage_slot < 0)
     return (unsigned)plan.items.size();
-  p->queue_at = counters ? (int32_t)plan.merges.size() : (stage_slot + 1) * kTicketsPerSlot - 1;
+  p->queue_at = (stage_slot + 1) * kTicketsPerSlot - 1;
   p->static_items = plan.static_items;
   p->queued_items = plan.queued_items;
   p->draws = plan.draws;
@@ -1891,17 +1891,17 @@ int launch_zero_words(int32_t* words, size_t count, hipStream_t stream) {
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
-                            int32_t* counters, bool quiet) {
+                            int32_t* tickets, bool quiet) {
   AttnParams p;
   fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
-  p.tickets = counters;
-  if (counters) {
-    if (use_tickets(plan)) p.ticket_base = 0;
+  if (tickets) {
+    p.tickets = tickets;
+    p.ticket_base = 0;
   } else if (stage_slot >= 0 && use_tickets(plan)) {
     p.ticket_base = stage_slot * kTicketsPerSlot;
   }
 
-  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, counters, &p));
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, &p));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
@@ -1916,12 +1916,12 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
 int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
-                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* counters, bool quiet) {
+                       const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets, bool quiet) {
   AttnParams p;
   fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
-  p.tickets = counters;
-  if (counters) {
-    if (use_tickets(plan)) p.ticket_base = 0;
+  if (tickets) {
+    p.tickets = tickets;
+    p.ticket_base = 0;
   } else if (stage_slot >= 0 && use_tickets(plan)) {
     p.ticket_base = stage_slot * kTicketsPerSlot;
   }
@@ -1934,7 +1934,7 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   const int D = b->head_dim;
   for (int j = 0; j < rotary_dim / 2; ++j) p.inv_freq[j] = inv_freq[j];
 
-  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, counters, &p));
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, &p));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);

@@ -61,7 +61,8 @@ def test_every_item_once_and_again(E, knobs, pairs, most_new, d):
 
 
 def test_plan_object_launched_again_and_captured(E, knobs):
-    """The counter lies in the plan's workspace: launches in a row and replays of a graph, with other work between."""
+    """Plan objects draw nothing (their items follow the workgroup ids): launches in a row and replays of a graph, with
+    other work between, against the batch call, which draws."""
     rng = np.random.default_rng(9)
     c = rng.integers(1900, 2300, size=4 * UNITS // 8 + 3).astype(np.int32)
     b = W.make_batch("c1", seed=9, lengths=(c, np.ones_like(c)), heads=(8, 8), head_dim=64)
@@ -99,3 +100,64 @@ def test_plan_object_launched_again_and_captured(E, knobs):
             stream.synchronize()
             assert np.array_equal(U.host_bits(out), want)
     assert np.array_equal(U.host_bits(kcd), kc_ref) and np.array_equal(U.host_bits(vcd), vc_ref)
+
+
+def test_one_plan_on_two_streams_at_once(E):
+    """Launches of a plan whose ranges are whole only read its workspace: they may run at the same time, on two streams
+    or as branches of one graph.  More items than the device starts at once; all requests read the same few pages."""
+    requests, heads, d, keys, page = 40, 32, 128, 2000, 16
+    per = keys // page
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    q = torch.randn(requests, heads, d, dtype=torch.bfloat16, device="cuda", generator=gen)
+    k, v = (torch.randn(per, heads, page, d, dtype=torch.bfloat16, device="cuda", generator=gen) for _ in range(2))
+    table = torch.arange(per, dtype=torch.int32).repeat(requests, 1).cuda()
+    desc = E.BatchDesc([keys - 1] * requests, [1] * requests, table, heads, heads, d, page, per)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, 0)
+    E.efim_set_tuning(E.EFIM_TUNE_XCD_GROUPING, 0)   # items by workgroup id
+    try:
+        want = torch.zeros_like(q)
+        nbytes = E.efim_extend_workspace_bytes(desc)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        E.efim_extend_attention(desc, q, k, v, want, 0.0, ws, nbytes)
+        E.efim_set_tuning(E.EFIM_TUNE_XCD_GROUPING, 1)
+        items = E.efim_extend_plan_items(desc)
+        plan = E.Plan(desc)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+        E.efim_set_tuning(E.EFIM_TUNE_XCD_GROUPING, 1)
+    assert len(items) == requests * heads and (items["partial_slot"] < 0).all()
+    some = [torch.nn.functional.softmax(k[:, h].reshape(keys, d).float() @ q[r, h].float() / d ** 0.5, 0) @
+            v[:, h].reshape(keys, d).float() - want[r, h].float() for r, h in ((0, 0), (17, 5), (39, 31))]
+    assert max(float(x.abs().max()) for x in some) <= U.MAX_ABS_TOL
+    nbytes = E.efim_plan_workspace_bytes(plan)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    E.efim_plan_upload(plan, ws, nbytes)
+    outs = [[torch.zeros_like(q) for _ in range(10)] for _ in range(2)]
+    main, streams = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def both():
+        for s in streams:
+            s.wait_stream(main)
+        for i in range(10):
+            for s, o in zip(streams, outs):
+                E.efim_extend_attention_planned(plan, table, q, k, v, o[i], 0.0, ws, s)
+        for s in streams:
+            main.wait_stream(s)
+
+    def check(what):
+        torch.cuda.synchronize()
+        for x, o in enumerate(outs):
+            for i in range(10):
+                assert torch.equal(o[i], want), "%s: stream %d launch %d" % (what, x, i)
+                o[i].zero_()
+        torch.cuda.synchronize()
+
+    both()
+    check("two streams")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=main):
+        both()
+    for replay in range(3):
+        graph.replay()
+        check("replay %d" % replay)
