@@ -57,6 +57,26 @@ def test_head_layouts(E, heads, d, interleaved):
         assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("interleaved", [0, 1])
+@pytest.mark.parametrize("heads,d", [((7, 1), 128), ((28, 4), 128), ((32, 8), 64), ((32, 32), 128)])
+def test_keys_only(E, heads, d, interleaved):
+    """Without queries a token has its key and value rows alone: one wave or several, and a wave that is not full."""
+    b = W.make_batch("c1", seed=heads[0] + d, lengths=(np.array([3, 0, 40], np.int32), np.array([5, 0, 9], np.int32)),
+                     heads=heads, head_dim=d)
+    kc, vc = U.oracle_cache(b)
+    kc8, vc8 = oracle_cache8(b, 0.0123, 0.031)
+    _, *got = U.gpu_rope_append(E, b, kc, vc, interleaved, with_q=False)
+    table = torch.from_numpy(b.block_table).cuda()
+    got8 = [torch.from_numpy(x.copy()).cuda() for x in (kc8, vc8)]
+    E.efim_rope_append_fp8(U.make_desc(E, b, table), None, U.dev_bits(b.k_new), U.dev_bits(b.v_new), *got8, b.rope_base,
+                           interleaved, 0.0123, 0.031)
+    O.rope_append(b.cached_len, b.new_len, b.block_table, b.page_size, None, b.k_new, b.v_new, kc, vc, b.rope_base,
+                  interleaved=bool(interleaved))
+    _, kc8, vc8, _ = oracle_step8(b, kc8, vc8, 0.0123, 0.031, interleaved=bool(interleaved))
+    for x, y in zip(got + [x.cpu().numpy() for x in got8], (kc, vc, kc8, vc8)):
+        assert np.array_equal(x, y)
+
+
 @pytest.mark.parametrize("heads,d", [((4, 1), 64), ((28, 4), 128)])
 def test_large_step_equals_small_ones(E, heads, d):
     """A step of more than 512 MiB of head rows (workgroups of whole tokens; (4, 1): of four each) against the same
