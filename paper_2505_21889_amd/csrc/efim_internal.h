@@ -113,6 +113,36 @@ int validate_batch(const efim_batch_t* b, int64_t* total_new);
 // Builds the work list. num_slots = number of 4-wave workgroups the device runs concurrently; fp8: for 8-bit caches.
 void build_plan(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8 = false);
 
+// Launch of the append kernel: x by y workgroups of 64 * parts << tok_shift threads; a workgroup has `parts` waves
+// for each of 1 << tok_shift tokens, a wave kAppendPasses passes of 1024 / head_dim head rows.
+constexpr int kAppendThreads = 256;
+constexpr int kAppendPasses = 2;
+struct AppendShape {
+  unsigned x, y;
+  int parts, tok_shift;
+};
+inline AppendShape append_shape(int64_t tokens, int rows, int head_dim) {
+  // Usually a workgroup takes the same part of four tokens, and all tokens' first
+  // parts go before their second ones.  A large step then reads and writes places far apart
+  // at any time, and the workgroup takes all rows of a token (of two or four where a token has
+  // two waves or one).  us, parts of four tokens / whole tokens: 28/4 heads of 128, 65536 tokens (604
+  // MB) 234 / 216, 32768 106.9 / 105.9, 16384 47.2 / 46.0, 4096 13.3 / 14.5; 32/8 heads of 128, 65536 (805 MB) 299 /
+  // 295, 16384 59.8 / 68.9, 2048 8.9 / 9.6; 32/8 heads of 64, 65536 (403 MB) 148 / 155, 32768 64.7 / 78.8.
+  constexpr int64_t kWholeTokenBytes = (int64_t)1 << 29;
+  constexpr int64_t kMostThreads = ((int64_t)1 << 32) - 1;  // of a launch along x
+  const int per_wave = kAppendPasses * (1024 / head_dim);
+  const int waves = (rows + per_wave - 1) / per_wave;  // per token
+  auto groups_of = [&](int tok_shift) { return (tokens + (1 << tok_shift) - 1) >> tok_shift; };
+  if (tokens * rows * head_dim * 2 >= kWholeTokenBytes) {
+    const int y = (waves + kAppendThreads / 64 - 1) / (kAppendThreads / 64);
+    const int parts = (waves + y - 1) / y;
+    const int tok_shift = parts == 1 ? 2 : parts == 2 ? 1 : 0;
+    if (groups_of(tok_shift) * (64 * parts << tok_shift) <= kMostThreads)
+      return AppendShape{(unsigned)groups_of(tok_shift), (unsigned)y, parts, tok_shift};
+  }
+  return AppendShape{(unsigned)groups_of(2), (unsigned)waves, 1, 2};
+}
+
 // inv_freq: rotary_dim/2 host values; the leading rotary_dim elements of every head row rotate.
 int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const void* k_new,
                        const void* v_new, void* k_cache, void* v_cache, const double* inv_freq,

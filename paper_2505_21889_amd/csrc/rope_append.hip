@@ -16,10 +16,8 @@
 namespace efim {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kPasses = 2;  // passes of a wave over its token's head rows
-// From this many bytes of head rows on a workgroup takes all rows of a token (see launch_with).
-constexpr int64_t kWholeTokenBytes = (int64_t)1 << 29;
+constexpr int kThreads = kAppendThreads;
+constexpr int kPasses = kAppendPasses;
 constexpr int kMaxReqPerLaunch = 384;
 
 template <int MAXREQ>
@@ -248,10 +246,6 @@ int launch_with(const efim_batch_t* b, void* q, const void* k_new, const void* v
   args.num_kv_heads = b->num_kv_heads;
   args.k_inv = 1.0 / (double)fmt.k_scale;
   args.v_inv = 1.0 / (double)fmt.v_scale;
-  const int rows_per_pass = 64 / (D / 16);
-  const int per_wave = kPasses * rows_per_pass;
-  const int rows = args.num_q_heads + 2 * b->num_kv_heads;  // head rows of a token
-  const int waves = (rows + per_wave - 1) / per_wave;       // per token
 
   int64_t row = 0;
   for (int r0 = 0; r0 < b->batch; r0 += MAXREQ) {
@@ -268,21 +262,10 @@ int launch_with(const efim_batch_t* b, void* q, const void* k_new, const void* v
     const int64_t ntok = row - first;
     if (ntok == 0) continue;
     args.tokens = (int32_t)ntok;
-    // Workgroups of four waves.  Usually a workgroup takes the same part of four tokens, and all tokens' first
-    // parts go before their second ones.  A large step then reads and writes places far apart
-    // at any time, and the workgroup takes all rows of a token (of two or four where a token has
-    // two waves or one).  us, parts of four tokens / whole tokens: 28/4 heads of 128, 65536 tokens (604
-    // MB) 234 / 216, 32768 106.9 / 105.9, 16384 47.2 / 46.0, 4096 13.3 / 14.5; 32/8 heads of 128, 65536 (805 MB) 299 /
-    // 295, 16384 59.8 / 68.9, 2048 8.9 / 9.6; 32/8 heads of 64, 65536 (403 MB) 148 / 155, 32768 64.7 / 78.8.
-    unsigned groups = (unsigned)waves;
-    args.parts = 1;
-    args.tok_shift = 2;
-    if (ntok * rows * D * 2 >= kWholeTokenBytes) {
-      groups = (unsigned)((waves + kThreads / 64 - 1) / (kThreads / 64));
-      args.parts = (waves + (int)groups - 1) / (int)groups;
-      args.tok_shift = args.parts == 1 ? 2 : args.parts == 2 ? 1 : 0;
-    }
-    const dim3 grid((unsigned)((ntok + (1 << args.tok_shift) - 1) >> args.tok_shift), groups);
+    const AppendShape shape = append_shape(ntok, args.num_q_heads + 2 * b->num_kv_heads, D);
+    args.parts = shape.parts;
+    args.tok_shift = shape.tok_shift;
+    const dim3 grid(shape.x, shape.y);
     auto qp = static_cast<uint16_t*>(q);
     auto kn = static_cast<const uint16_t*>(k_new);
     auto vn = static_cast<const uint16_t*>(v_new);

@@ -1,4 +1,4 @@
-"""The host side of the library (planner, session pool) under AddressSanitizer and UBSan: the two
+"""The host side of the library (planner, launch shapes, session pool) under AddressSanitizer and UBSan: the
 drivers in tests/native/ push random inputs through the C++ code compiled by g++ with the
 sanitizers on, and check coverage / consistency properties on the way.  No GPU, no HIP runtime
 (only its headers, for the types the internal header names)."""
@@ -37,6 +37,15 @@ def test_planner_under_sanitizers(tmp_path):
                          [os.path.join(NATIVE, "fuzz_planner.cpp"), os.path.join(CSRC, "planner.cpp")],
                          ["-D__HIP_PLATFORM_AMD__", "-I", hip_include])
     assert "planner ok" in out
+
+
+def test_append_launch_shapes_under_sanitizers(tmp_path):
+    hip_include = "/opt/rocm/include"
+    if not os.path.exists(os.path.join(hip_include, "hip", "hip_runtime.h")):
+        pytest.skip("HIP headers not available")
+    out = _build_and_run(tmp_path, "append_shape", [os.path.join(NATIVE, "append_shape.cpp")],
+                         ["-D__HIP_PLATFORM_AMD__", "-I", hip_include])
+    assert "append shape ok" in out
 
 
 def test_session_pool_under_sanitizers(tmp_path):
