@@ -59,9 +59,61 @@ struct Tile {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Builds the plan.  wide: compute-heavy steps and steps of many tiles take 256 rows whatever their ranges.  Returns
-// whether it took 128 where `wide` would take 256.
-bool build(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8, bool wide) {
+// Query-row tile of a workgroup: 128 rows (each of the 4 waves owns 32; two workgroups per compute unit) or 256 (8
+// waves; one workgroup per unit, which gathers a key tile once for twice the rows and two tiles ahead).
+// The loops of both do the same work in the same time (8 waves 1.84 us per key tile of a unit, two times 4 waves
+// 1.83), so what surrounds them decides.  Two workgroups on a unit cover each other's start and end, and half
+// the tile leaves less of a last tile empty and packs better; with long ranges the gathers count and little else
+// does.  A compute-heavy step ("compute-heavy": more than the machine balance of about 315 flop per byte, 2.5
+// PFLOP/s over 8 TB/s) takes 128 rows up to 32 key tiles in the mean, 64 with head dim 64, and always over 8-bit
+// caches.  256 / 128 rows, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim
+// 128, up to 32 tiles 0.95 (0.77 .. 1.02), 32 to 100 tiles 0.99 (0.95 .. 1.02), above 1.01 (0.94 .. 1.06); head dim 64,
+// up to 64 tiles 0.96 (0.87 .. 1.01); 8-bit caches, 9 to 214 tiles, 0.92 (0.80 .. 0.98).
+// A step bound by HBM takes 256 rows when it has at least two such tiles per compute unit, which then balance
+// over the units without cutting key ranges (no merge pass), and few of its key ranges are read by more
+// than one tile (34 requests of 824..1782 + 203..512 tokens, 32/32 heads: 416 / 396 us).
+struct RowTile {
+  int bf16 = 128, fp8 = 128;  // rows, by the format of the caches
+  bool narrowed = false;      // bf16: 128 where the step's size alone says 256
+  size_t wide_tiles = 0;      // of 256 rows
+};
+
+RowTile choose_row_tile(const efim_batch_t* b, int num_slots) {
+  RowTile tile;
+  const Tuning& tn = tuning();
+  if (tn.row_tile != 0) {
+    tile.bf16 = tile.fp8 = tn.row_tile;
+    return tile;
+  }
+  const int g = b->num_q_heads / b->num_kv_heads;
+  const int D = b->head_dim;
+  const double long_keys = 32.0 * kKeyTile * 128 / D;  // keys a row sees, in the mean over the work
+  double flops = 0.0, bytes = 0.0, work = 0.0, work_keys = 0.0, keys = 0.0, keys_read = 0.0;
+  int64_t max_rows = 0;
+  for (int r = 0; r < b->batch; ++r) {
+    const double n = b->new_len[r], c = b->cached_len[r];
+    if (n == 0) continue;
+    const double seen = c + 0.5 * (n + 1);  // keys a row sees, in the mean
+    const int64_t rows = (int64_t)g * b->new_len[r], t = (rows + 255) / 256;
+    max_rows = std::max(max_rows, rows);
+    flops += 4.0 * D * b->num_q_heads * n * seen;
+    bytes += 4.0 * D * ((c + n) * b->num_kv_heads + n * b->num_q_heads);
+    work += n * seen;
+    work_keys += n * seen * seen;
+    keys += c + n;
+    keys_read += t * c + n * (t + 1) / 2;
+    tile.wide_tiles += (size_t)(b->num_kv_heads * t);
+  }
+  const bool heavy = max_rows > 128 && flops > 315.0 * bytes;
+  if (!heavy && tile.wide_tiles < (size_t)num_slots) return tile;
+  tile.narrowed = heavy ? work_keys < long_keys * work : max_rows > 128 && keys_read >= 1.5 * keys;
+  tile.bf16 = tile.narrowed ? 128 : 256;
+  tile.fp8 = heavy ? 128 : tile.bf16;
+  return tile;
+}
+
+// Builds the plan with row tiles of M rows.
+void build(const efim_batch_t* b, int num_slots, int M, Plan* plan) {
   const int g = b->num_q_heads / b->num_kv_heads;
   const int D = b->head_dim;
   plan->reqs.clear();
@@ -72,53 +124,13 @@ bool build(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8, bool wide
 
   int64_t row = 0;
   int64_t max_rows = 0;
+  double keys = 0.0;
   for (int r = 0; r < b->batch; ++r) {
     ReqInfo ri{b->cached_len[r], b->new_len[r], (int32_t)row, 0};
     plan->reqs.push_back(ri);
     row += b->new_len[r];
     max_rows = std::max<int64_t>(max_rows, (int64_t)g * b->new_len[r]);
-  }
-  // Query-row tile of a workgroup: 128 rows (each of the 4 waves owns 32; two workgroups per compute unit) or 256 (8
-  // waves; one workgroup per unit, which gathers a key tile once for twice the rows and two tiles ahead).
-  // The loops of both do the same work in the same time (8 waves 1.84 us per key tile of a unit, two times 4 waves
-  // 1.83), so what surrounds them decides.  Two workgroups on a unit cover each other's start and end, and half
-  // the tile leaves less of a last tile empty and packs better; with long ranges the gathers count and little else
-  // does.  A compute-heavy step ("compute-heavy": more than the machine balance of about 315 flop per byte, 2.5
-  // PFLOP/s over 8 TB/s) takes 128 rows up to 32 key tiles in the mean, 64 with head dim 64, and always over 8-bit
-  // caches.  256 / 128 rows, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim
-  // 128, up to 32 tiles 0.95 (0.77 .. 1.02), 32 to 100 tiles 0.99 (0.95 .. 1.02), above 1.01 (0.94 .. 1.06); head dim 64,
-  // up to 64 tiles 0.96 (0.87 .. 1.01); 8-bit caches, 9 to 214 tiles, 0.92 (0.80 .. 0.98).
-  // A step bound by HBM takes 256 rows when it has at least two such tiles per compute unit, which then balance
-  // over the units without cutting key ranges (no merge pass), and few of its key ranges are read by more
-  // than one tile (34 requests of 824..1782 + 203..512 tokens, 32/32 heads: 416 / 396 us).
-  const Tuning& tn0 = tuning();
-  const double long_keys = 32.0 * kKeyTile * 128 / D;  // keys a row sees, in the mean over the work
-  double flops = 0.0, bytes = 0.0, work = 0.0, work_keys = 0.0, keys = 0.0, keys_read = 0.0;
-  int64_t wide_tiles = 0;
-  for (int r = 0; r < b->batch; ++r) {
-    const double n = b->new_len[r], c = b->cached_len[r];
-    if (n == 0) continue;
-    const double seen = c + 0.5 * (n + 1);  // keys a row sees, in the mean
-    const int64_t t = ((int64_t)g * b->new_len[r] + 255) / 256;
-    flops += 4.0 * D * b->num_q_heads * n * seen;
-    bytes += 4.0 * D * ((c + n) * b->num_kv_heads + n * b->num_q_heads);
-    work += n * seen;
-    work_keys += n * seen * seen;
-    keys += c + n;
-    keys_read += t * c + n * (t + 1) / 2;
-    wide_tiles += b->num_kv_heads * t;
-  }
-  int M = 128;
-  bool narrowed = false;
-  if (tn0.row_tile == 256) {
-    M = 256;
-  } else if (tn0.row_tile == 0) {
-    const bool heavy = max_rows > 128 && flops > 315.0 * bytes;
-    if (heavy || wide_tiles >= num_slots) {
-      const bool narrow = heavy ? fp8 || work_keys < long_keys * work : max_rows > 128 && keys_read >= 1.5 * keys;
-      narrowed = narrow && !wide;
-      if (!narrowed) M = 256;
-    }
+    if (b->new_len[r] > 0) keys += (double)b->cached_len[r] + b->new_len[r];
   }
   plan->rows_per_item = M;
   if (M == 256) num_slots = std::max(1, num_slots / 2);  // 8-wave workgroups: one per compute unit
@@ -468,17 +480,20 @@ bool build(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8, bool wide
   plan->off_part_ml = off;
   off = align_up(off + (size_t)plan->num_partial_slots * prows * 4 * sizeof(float), 256);
   plan->total_bytes = off < 256 ? 256 : off;  // never zero, so callers always pass a real buffer
-  return narrowed;
 }
 
 }  // namespace
 
 void build_plan(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8) {
-  // 128 rows make up to twice the items and other cuts.  Where those outgrow what efim_extend_attention_static
-  // holds, the step stays at 256: nothing that call takes there is refused.
-  if (build(b, num_slots, plan, fp8, false) &&
-      (plan->header_bytes > kStaticListBytes || plan->total_bytes > kStaticPartialBytes))
-    (void)build(b, num_slots, plan, fp8, true);
+  const RowTile tile = choose_row_tile(b, num_slots);
+  build(b, num_slots, fp8 ? tile.fp8 : tile.bf16, plan);
+  // 128 rows make up to twice the items and other cuts.  Where those outgrow what efim_extend_attention_static (bf16
+  // only) holds and 256 rows do not, the step stays at 256: nothing that call takes there is refused.
+  auto fits = [](const Plan& p) { return p.header_bytes <= kStaticListBytes && p.total_bytes <= kStaticPartialBytes; };
+  if (fp8 || !tile.narrowed || fits(*plan) || tile.wide_tiles * sizeof(DevItem) > kStaticListBytes) return;
+  Plan wide;
+  build(b, num_slots, 256, &wide);
+  if (fits(wide)) *plan = std::move(wide);
 }
 
 }  // namespace efim

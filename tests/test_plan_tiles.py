@@ -30,10 +30,12 @@ def test_steps_bound_by_hbm_by_their_shared_ranges(new, tile):
 
 
 def test_a_step_that_the_static_call_takes_in_256_rows_stays_within_its_limits():
-    """Work list (48 bytes per item) of at most 2 MiB and partial results of at most 30 MiB wherever 256 rows stay there."""
+    """Work list (48 bytes per item) of at most 2 MiB and partial results of at most 30 MiB wherever 256 rows stay there;
+    where they do not either, the tile that the ranges ask for."""
     rng = np.random.default_rng(5)
-    cases = [([100] * 2000, [200] * 2000, (32, 8), 128)]     # 14000 items of 256 rows, 28000 of 128
-    cases += [([600] * 900, [500] * 900, (32, 8), 128)]      # 57600 items of 256 rows: beyond the limit already
+    list_too_long = ([100] * 900, [200] * 900, (32, 8), 128)   # 28800 items of 256 rows (1.4 MB), 50400 of 128 (2.4 MB)
+    both_too_long = ([100] * 2000, [200] * 2000, (32, 8), 128) # 64000 and 112000
+    cases = []
     for _ in range(40):
         batch = int(rng.integers(1, 24))
         heads = [(32, 8), (28, 4), (32, 32)][int(rng.integers(0, 3))]
@@ -53,10 +55,16 @@ def test_a_step_that_the_static_call_takes_in_256_rows_stays_within_its_limits()
             E.efim_set_tuning(E.EFIM_TUNE_ROW_TILE, 0)
 
     limits = (2 << 20, 30 << 20)
-    seen = 0
+    for case, tile in ((list_too_long, 256), (both_too_long, 128)):
+        narrow, wide = sizes(128, case), sizes(256, case)
+        assert narrow[0] > limits[0] and (wide[0] > limits[0]) == (tile == 128), case
+        assert sizes(0, case) == (narrow if tile == 128 else wide), case
+    narrowed = held_back = 0
     for case in cases:
         chosen, wide = sizes(0, case), sizes(256, case)
-        if wide[0] <= limits[0] - 65536 and wide[1] <= limits[1] and chosen == sizes(128, case) != wide:
-            seen += 1
+        if wide[0] <= limits[0] - 65536 and wide[1] <= limits[1]:
             assert chosen[0] <= limits[0] and chosen[1] <= limits[1], case
-    assert seen >= 5
+            narrow = sizes(128, case)
+            narrowed += chosen == narrow != wide
+            held_back += narrow[1] > limits[1] and chosen == wide != narrow   # by their partial results
+    assert narrowed >= 5 and held_back >= 1
