@@ -38,6 +38,23 @@ typedef struct efim_work_item {
 int64_t efim_extend_plan_items(const efim_batch_t* batch, efim_work_item_t* items, int64_t capacity);
 
 /*
+ * What a batch call (attention or decode step) over bf16 (fp8 = 0) or 8-bit caches (1) launches for this batch when it
+ * is given a workspace of that size: row tile, split query tiles to merge, items that workgroups draw from a counter
+ * and workgroups that draw, workspace it uses; and the plans the process has built so far for batch calls and size
+ * queries.  (efim_extend_plan_items lists the items of a call over bf16 caches.)
+ */
+typedef struct efim_plan_info {
+  int64_t row_tile;
+  int64_t merges;
+  int64_t queued_items;
+  int64_t draws;
+  int64_t workspace_bytes;
+  int64_t plans_built;
+} efim_plan_info_t;
+
+int efim_plan_info(const efim_batch_t* batch, int fp8, size_t workspace_bytes, efim_plan_info_t* info);
+
+/*
  * Process-wide tuning knobs for tests and benchmarks (not needed in normal use).
  * Returns EFIM_OK or EFIM_ERR_INVALID_ARG for an unknown key / bad value.
  */

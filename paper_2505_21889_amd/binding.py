@@ -67,6 +67,12 @@ class EfimPromptInfo(ctypes.Structure):
                 ("cached_len", ctypes.c_int64), ("new_len", ctypes.c_int64)]
 
 
+class EfimPlanInfo(ctypes.Structure):
+    """efim_plan_info_t"""
+    _fields_ = [(n, ctypes.c_int64) for n in (
+        "row_tile", "merges", "queued_items", "draws", "workspace_bytes", "plans_built")]
+
+
 def _load():
     path = os.environ.get("EFIM_LIBRARY")  # explicit path to an already built libefim.so
     if not path:
@@ -128,6 +134,8 @@ def _load():
     lib.efim_decode_step_fp8_table.restype = i32
     lib.efim_extend_plan_items.argtypes = [bp, vp, i64]
     lib.efim_extend_plan_items.restype = i64
+    lib.efim_plan_info.argtypes = [bp, i32, ctypes.c_size_t, ctypes.POINTER(EfimPlanInfo)]
+    lib.efim_plan_info.restype = i32
     lib.efim_set_tuning.argtypes = [i32, i32]
     lib.efim_set_tuning.restype = i32
     lib.efim_set_kernel_events.argtypes = [vp, vp]
@@ -162,7 +170,7 @@ EXPORTED_SYMBOLS = (
     "efim_decode_workspace_bytes", "efim_decode_step", "efim_decode_step_table",
     "efim_rope_append_fp8", "efim_extend_attention_fp8", "efim_decode_step_fp8",
     "efim_rope_append_fp8_table", "efim_decode_step_fp8_table",
-    "efim_extend_plan_items", "efim_set_tuning", "efim_set_kernel_events", "efim_status_string",
+    "efim_extend_plan_items", "efim_plan_info", "efim_set_tuning", "efim_set_kernel_events", "efim_status_string",
     "efim_last_hip_error", "efim_version", "efim_source_digest", "efim_stream_release",
     "efim_plan_create", "efim_plan_destroy", "efim_plan_workspace_bytes", "efim_plan_upload",
     "efim_extend_attention_planned", "efim_decode_step_planned",
@@ -390,6 +398,13 @@ def efim_extend_plan_items(batch):
         m = _lib.efim_extend_plan_items(ctypes.byref(batch.c), items.ctypes.data, int(n))
         assert m == n
     return items
+
+
+def efim_plan_info(batch, fp8=False, workspace_bytes=0):
+    info = EfimPlanInfo()
+    _check(_lib.efim_plan_info(ctypes.byref(batch.c), int(bool(fp8)), int(workspace_bytes), ctypes.byref(info)),
+           "efim_plan_info")
+    return {name: int(getattr(info, name)) for name, _ in EfimPlanInfo._fields_}
 
 
 def efim_set_tuning(key, value):

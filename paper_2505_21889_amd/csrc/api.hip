@@ -1,5 +1,4 @@
 // C ABI entry points of libefim: argument checks, planning, staging of the work list.
-#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -354,15 +353,13 @@ const Plan& cached_plan(const efim_batch_t* b, bool fp8 = false) {
   return cache.plan;
 }
 
-// The plan of a call over 8-bit caches, where the workspace (whose size comes from a query that does not know the
-// format) is large enough for it; else the other one.
+// The plan of a call over 8-bit caches: the one that the size query made, unless the format asks for another row tile
+// and the workspace (the query does not know the format) is large enough.
 const Plan& fp8_plan(const efim_batch_t* b, size_t workspace_bytes) {
-  const int g = b->num_q_heads / b->num_kv_heads;
-  int64_t rows = 0;
-  for (int r = 0; r < b->batch; ++r) rows = std::max(rows, (int64_t)g * b->new_len[r]);
-  if (rows <= 128) return cached_plan(b);  // (they are the same)
-  const Plan& plan = cached_plan(b, true);
-  return plan.total_bytes <= workspace_bytes ? plan : cached_plan(b);
+  const Plan& plan = cached_plan(b);
+  if (plan.rows_per_item == plan.fp8_rows_per_item) return plan;
+  const Plan& own = cached_plan(b, true);
+  return own.total_bytes <= workspace_bytes ? own : plan;
 }
 
 }  // namespace
@@ -867,6 +864,23 @@ int64_t efim_extend_plan_items(const efim_batch_t* batch, efim_work_item_t* item
   const int64_t n = (int64_t)plan.items.size();
   for (int64_t i = 0; i < n && i < capacity; ++i) items[i] = plan.items[i];
   return n;
+}
+
+int efim_plan_info(const efim_batch_t* batch, int fp8, size_t workspace_bytes, efim_plan_info_t* info) {
+  int64_t total = 0;
+  int rc = validate_batch(batch, &total);
+  if (rc != EFIM_OK) return rc;
+  if (!info || (fp8 != 0 && fp8 != 1)) return EFIM_ERR_INVALID_ARG;
+  std::lock_guard<std::mutex> lock(g_plan_mutex);
+  const Plan& plan = fp8 ? fp8_plan(batch, workspace_bytes) : cached_plan(batch);
+  const bool draws = plan_draws(plan, fp8 != 0);
+  info->row_tile = plan.rows_per_item;
+  info->merges = (int64_t)plan.merges.size();
+  info->queued_items = draws ? plan.queued_items : 0;
+  info->draws = draws ? plan.draws : 0;
+  info->workspace_bytes = (int64_t)plan.total_bytes;
+  info->plans_built = (int64_t)g_next_plan_id;
+  return EFIM_OK;
 }
 
 int efim_set_tuning(int key, int value) {

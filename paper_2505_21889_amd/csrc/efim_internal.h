@@ -25,7 +25,7 @@ constexpr int kStageSlots = 64;       // launch tokens in turn: a token comes ro
 constexpr int kTicketSlots = kStageSlots;
 constexpr int kTicketsPerSlot = 8192; // split query tiles one launch can combine in-kernel, and (the last one) its queue
 
-// Key tiles that the items of a launch have in the mean for its later ones to be drawn (reason at the launch).
+// Key tiles that the items of a launch have in the mean for its later ones to be drawn (reason at plan_draws).
 constexpr int kLongItems = 28;
 
 // Fixed device memory of efim_extend_attention_static: for the work list and for the partial results of split key ranges.
@@ -81,6 +81,7 @@ Tuning& tuning();
 struct Plan {
   uint64_t id = 0;          // distinct for every plan the cache has built
   int rows_per_item = 128;  // query rows per workgroup tile (32 per wave)
+  int fp8_rows_per_item = 128;  // the same in the plan for 8-bit caches: all else equal, plans of one tile are
   int max_item_rows = 0;    // largest row_count of a work item
   int partial_rows = 128;   // rows per partial-result slot of a split key range
   bool once = false;        // few work items of few rows, each short enough for the kernel that gathers a whole range at once
@@ -109,6 +110,17 @@ struct CacheFormat {
 
 // Validates the host-visible part of a batch. total_new receives T.
 int validate_batch(const efim_batch_t* b, int64_t* total_new);
+
+// Whether a launch with a counter draws the plan's queued items.  A draw costs a workgroup 1 to 1.5 us before it can
+// start: 16..24 tiles per item 0.8-4.5 % slower drawn (17 requests of 714..1181 +
+// 69..230 tokens, 32/32 heads 110 / 115 us), 28 and more 1-7.5 % faster (57 requests of 5319..16384 keys, one new
+// token, 32/32 heads 1804 / 1669).  A tile of codes takes half the time, and so the line lies at twice the length there
+// (45 requests of 3767..14730 + 8..16 in one call 633 / 617); with at most 16
+// rows per item two workgroups share a unit over codes, start at once and gain nothing (27 requests of
+// 1649..5713 keys, one new token, 175.2 / 179.0).
+inline bool plan_draws(const Plan& plan, bool fp8) {
+  return plan.queued_items > 0 && plan.mean_tiles >= (fp8 ? 2 : 1) * kLongItems && !(fp8 && plan.rows16);
+}
 
 // Builds the work list. num_slots = number of 4-wave workgroups the device runs concurrently; fp8: for 8-bit caches.
 void build_plan(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8 = false);

@@ -1773,18 +1773,11 @@ bool use_tickets(const Plan& plan) {
   return want && !plan.merges.empty() && plan.merges.size() < (size_t)kTicketsPerSlot;
 }
 
-// Workgroups of a launch; with a launch token, whose block of counters is this launch's alone, and long items, the
-// plan's queued ones are drawn.  (A plan object's launches have none: a counter in the workspace would be
-// shared by launches of one plan that run at the same time, which where no range is cut only read it.)  A draw costs
-// a workgroup 1 to 1.5 us before it can start: 16..24 tiles per item 0.8-4.5 % slower drawn (17 requests of 714..1181 +
-// 69..230 tokens, 32/32 heads 110 / 115 us), 28 and more 1-7.5 % faster (57 requests of 5319..16384 keys, one new
-// token, 32/32 heads 1804 / 1669).  A tile of codes takes half the time, and so the line lies at twice the length there
-// (45 requests of 3767..14730 + 8..16 in one call 633 / 617); with at most 16
-// rows per item two workgroups share a unit over codes, start at once and gain nothing (27 requests of
-// 1649..5713 keys, one new token, 175.2 / 179.0).
+// Workgroups of a launch; with a launch token, whose block of counters is this launch's alone, the plan's queued items
+// may be drawn.  (A plan object's launches have none: a counter in the workspace would be
+// shared by launches of one plan that run at the same time, which where no range is cut only read it.)
 unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, AttnParams* p) {
-  if (plan.queued_items == 0 || plan.mean_tiles < (fp8 ? 2 : 1) * kLongItems || (fp8 && plan.rows16) || stage_slot < 0)
-    return (unsigned)plan.items.size();
+  if (stage_slot < 0 || !plan_draws(plan, fp8)) return (unsigned)plan.items.size();
   p->queue_at = (stage_slot + 1) * kTicketsPerSlot - 1;
   p->static_items = plan.static_items;
   p->queued_items = plan.queued_items;

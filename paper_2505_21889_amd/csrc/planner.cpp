@@ -486,12 +486,14 @@ void build(const efim_batch_t* b, int num_slots, int M, Plan* plan) {
 
 void build_plan(const efim_batch_t* b, int num_slots, Plan* plan, bool fp8) {
   const RowTile tile = choose_row_tile(b, num_slots);
+  plan->fp8_rows_per_item = tile.fp8;
   build(b, num_slots, fp8 ? tile.fp8 : tile.bf16, plan);
   // 128 rows make up to twice the items and other cuts.  Where those outgrow what efim_extend_attention_static (bf16
   // only) holds and 256 rows do not, the step stays at 256: nothing that call takes there is refused.
   auto fits = [](const Plan& p) { return p.header_bytes <= kStaticListBytes && p.total_bytes <= kStaticPartialBytes; };
   if (fp8 || !tile.narrowed || fits(*plan) || tile.wide_tiles * sizeof(DevItem) > kStaticListBytes) return;
   Plan wide;
+  wide.fp8_rows_per_item = tile.fp8;
   build(b, num_slots, 256, &wide);
   if (fits(wide)) *plan = std::move(wide);
 }
