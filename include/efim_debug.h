@@ -38,8 +38,8 @@ typedef struct efim_work_item {
 int64_t efim_extend_plan_items(const efim_batch_t* batch, efim_work_item_t* items, int64_t capacity);
 
 /*
- * What a batch call (attention or decode step) over bf16 (fp8 = 0) or 8-bit caches (1) launches for this batch when it
- * is given a workspace of that size: row tile, split query tiles to merge, items that workgroups draw from a counter
+ * What a batch call (attention or decode step) over bf16 (fp8 = 0) or 8-bit caches (1) launches for this batch:
+ * row tile, split query tiles to merge, items that workgroups draw from a counter
  * and workgroups that draw, workspace it uses; and the plans the process has built so far for batch calls and size
  * queries.  (efim_extend_plan_items lists the items of a call over bf16 caches.)
  */
@@ -52,7 +52,7 @@ typedef struct efim_plan_info {
   int64_t plans_built;
 } efim_plan_info_t;
 
-int efim_plan_info(const efim_batch_t* batch, int fp8, size_t workspace_bytes, efim_plan_info_t* info);
+int efim_plan_info(const efim_batch_t* batch, int fp8, efim_plan_info_t* info);
 
 /*
  * Process-wide tuning knobs for tests and benchmarks (not needed in normal use).

@@ -134,7 +134,7 @@ def _load():
     lib.efim_decode_step_fp8_table.restype = i32
     lib.efim_extend_plan_items.argtypes = [bp, vp, i64]
     lib.efim_extend_plan_items.restype = i64
-    lib.efim_plan_info.argtypes = [bp, i32, ctypes.c_size_t, ctypes.POINTER(EfimPlanInfo)]
+    lib.efim_plan_info.argtypes = [bp, i32, ctypes.POINTER(EfimPlanInfo)]
     lib.efim_plan_info.restype = i32
     lib.efim_set_tuning.argtypes = [i32, i32]
     lib.efim_set_tuning.restype = i32
@@ -400,9 +400,9 @@ def efim_extend_plan_items(batch):
     return items
 
 
-def efim_plan_info(batch, fp8=False, workspace_bytes=0):
+def efim_plan_info(batch, fp8=False):
     info = EfimPlanInfo()
-    _check(_lib.efim_plan_info(ctypes.byref(batch.c), int(bool(fp8)), int(workspace_bytes), ctypes.byref(info)),
+    _check(_lib.efim_plan_info(ctypes.byref(batch.c), int(bool(fp8)), ctypes.byref(info)),
            "efim_plan_info")
     return {name: int(getattr(info, name)) for name, _ in EfimPlanInfo._fields_}
 

@@ -354,12 +354,13 @@ const Plan& cached_plan(const efim_batch_t* b, bool fp8 = false) {
 }
 
 // The plan of a call over 8-bit caches: the one that the size query made, unless the format asks for another row tile
-// and the workspace (the query does not know the format) is large enough.
-const Plan& fp8_plan(const efim_batch_t* b, size_t workspace_bytes) {
+// and that plan needs no more workspace than the query said (it does not know the format).  So the batch
+// alone decides, not the size of the buffer that the caller has.
+const Plan& fp8_plan(const efim_batch_t* b) {
   const Plan& plan = cached_plan(b);
   if (plan.rows_per_item == plan.fp8_rows_per_item) return plan;
   const Plan& own = cached_plan(b, true);
-  return own.total_bytes <= workspace_bytes ? own : plan;
+  return own.total_bytes <= plan.total_bytes ? own : plan;
 }
 
 }  // namespace
@@ -483,7 +484,7 @@ int extend_attention_base(const efim_batch_t* batch, const void* q, const void* 
       (reinterpret_cast<uintptr_t>(batch->block_table) & 3u))
     return EFIM_ERR_INVALID_ARG;
   std::lock_guard<std::mutex> lock(g_plan_mutex);
-  const Plan& plan = fmt.fp8 ? fp8_plan(batch, workspace_bytes) : cached_plan(batch);
+  const Plan& plan = fmt.fp8 ? fp8_plan(batch) : cached_plan(batch);
   if (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) || workspace_bytes < plan.total_bytes)
     return EFIM_ERR_WORKSPACE;
   if (sm_scale == 0.f) sm_scale = 1.0f / sqrtf((float)batch->head_dim);
@@ -866,13 +867,13 @@ int64_t efim_extend_plan_items(const efim_batch_t* batch, efim_work_item_t* item
   return n;
 }
 
-int efim_plan_info(const efim_batch_t* batch, int fp8, size_t workspace_bytes, efim_plan_info_t* info) {
+int efim_plan_info(const efim_batch_t* batch, int fp8, efim_plan_info_t* info) {
   int64_t total = 0;
   int rc = validate_batch(batch, &total);
   if (rc != EFIM_OK) return rc;
   if (!info || (fp8 != 0 && fp8 != 1)) return EFIM_ERR_INVALID_ARG;
   std::lock_guard<std::mutex> lock(g_plan_mutex);
-  const Plan& plan = fp8 ? fp8_plan(batch, workspace_bytes) : cached_plan(batch);
+  const Plan& plan = fp8 ? fp8_plan(batch) : cached_plan(batch);
   const bool draws = plan_draws(plan, fp8 != 0);
   info->row_tile = plan.rows_per_item;
   info->merges = (int64_t)plan.merges.size();

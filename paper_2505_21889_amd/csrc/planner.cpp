@@ -65,8 +65,8 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // 1.83), so what surrounds them decides.  Two workgroups on a unit cover each other's start and end, and half
 // the tile leaves less of a last tile empty and packs better; with long ranges the gathers count and little else
 // does.  A compute-heavy step ("compute-heavy": more than the machine balance of about 315 flop per byte, 2.5
-// PFLOP/s over 8 TB/s) takes 128 rows up to 32 key tiles in the mean, 64 with head dim 64, and always over 8-bit
-// caches.  256 / 128 rows, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim
+// PFLOP/s over 8 TB/s) takes 128 rows up to 32 key tiles in the mean, 64 with head dim 64, and over 8-bit caches
+// whenever the workspace that the size query names holds that plan (fp8_plan).  256 / 128 rows, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim
 // 128, up to 32 tiles 0.95 (0.77 .. 1.02), 32 to 100 tiles 0.99 (0.95 .. 1.02), above 1.01 (0.94 .. 1.06); head dim 64,
 // up to 64 tiles 0.96 (0.87 .. 1.01); 8-bit caches, 9 to 214 tiles, 0.92 (0.80 .. 0.98).
 // A step bound by HBM takes 256 rows when it has at least two such tiles per compute unit, which then balance

@@ -446,3 +446,41 @@ def test_fp8_one_very_long_context(E):
     max_abs, rel = U.assert_close(got, ref, "long context decode step")
     print("fp8 long context: max_abs %.3e rel_l2 %.3e" % (max_abs, rel))
     U.assert_close(gpu_attention8(E, b, q_ref, kc_ref, vc_ref, scale, scale), ref, "long context attention")
+
+
+@pytest.mark.parametrize("cached,new,tile", [([5860, 5800, 5911], [178, 170, 181], 128), ([8200, 9000], [100, 260], 256)])
+def test_fp8_output_does_not_depend_on_spare_workspace(E, cached, new, tile):
+    """Compute-heavy steps whose plan over bf16 caches takes 256 rows: over codes 128, unless that needs more workspace
+    than the size query says.  An exact buffer and a larger one give the same bits, near the fp32 result."""
+    hq, hkv, d, page = 32, 8, 128, 16
+    keys = [c + n for c, n in zip(cached, new)]
+    per = [-(-k // page) for k in keys]
+    gen = torch.Generator(device="cuda").manual_seed(sum(cached))
+    q = torch.randn(sum(new), hq, d, dtype=torch.bfloat16, device="cuda", generator=gen)
+    kf, vf = (torch.randn(sum(per), hkv, page, d, device="cuda", generator=gen).to(torch.float8_e4m3fn) for _ in range(2))
+    kc, vc = kf.view(torch.uint8), vf.view(torch.uint8)
+    table = torch.zeros(len(new), max(per), dtype=torch.int32)
+    for r, n in enumerate(per):
+        table[r, :n] = torch.arange(n) + sum(per[:r])
+    table = table.cuda()
+    desc = E.BatchDesc(cached, new, table, hq, hkv, d, page, sum(per))
+    need = E.efim_extend_workspace_bytes(desc)
+    assert E.efim_plan_info(desc)["row_tile"] == 256 and E.efim_plan_info(desc, fp8=True)["row_tile"] == tile
+    outs = []
+    for nbytes in (need, need + (64 << 20), need):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+        E.efim_extend_attention_fp8(desc, q, kc, vc, out, 0.0, 1.0, 1.0, ws, nbytes)
+        outs.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    row = 0
+    for r, n in enumerate(new):
+        pages = table[r, :per[r]].long()
+        seen = torch.arange(keys[r], device="cuda")[None] <= cached[r] + torch.arange(n, device="cuda")[:, None]
+        for h in (0, 13, 31):
+            k, v = (x[pages, h // (hq // hkv)].float().reshape(-1, d)[:keys[r]] for x in (kf, vf))
+            s = (q[row:row + n, h].float() @ k.T / d ** 0.5).masked_fill(~seen, float("-inf"))
+            ref = torch.softmax(s, 1) @ v
+            assert float((outs[0][row:row + n, h].float() - ref).abs().max()) <= U.MAX_ABS_TOL
+        row += n

@@ -31,9 +31,26 @@ def test_one_plan_where_the_format_does_not_change_the_tile(step):
     d = desc(*STEPS[step])
     need = E.efim_extend_workspace_bytes(d)
     before = E.efim_plan_info(d)
-    after = E.efim_plan_info(d, fp8=True, workspace_bytes=need)
+    after = E.efim_plan_info(d, fp8=True)
     assert (after["plans_built"] == before["plans_built"]) == (step != "compute-heavy, long ranges")
     assert after["row_tile"] == 128 and before["row_tile"] == (256 if step == "compute-heavy, long ranges" else 128)
     for _ in range(3):
-        assert E.efim_plan_info(d, fp8=True, workspace_bytes=need) == after
+        assert E.efim_plan_info(d, fp8=True) == after
         assert E.efim_extend_workspace_bytes(d) == need
+
+
+def test_the_plan_fits_what_the_query_said():
+    """Over drawn compute-heavy steps whose tiles differ: 128 rows unless they need more workspace than the query says,
+    which a buffer of exactly that size has to do."""
+    rng = np.random.default_rng(17)
+    own = other = 0
+    for _ in range(150):
+        batch = int(rng.integers(1, 9))
+        d = desc(rng.integers(2000, 16000, batch).tolist(), rng.integers(40, 400, batch).tolist(),
+                 [(32, 8), (28, 4)][int(rng.integers(0, 2))])
+        need, plain, info = E.efim_extend_workspace_bytes(d), E.efim_plan_info(d), E.efim_plan_info(d, fp8=True)
+        assert info["workspace_bytes"] <= need and plain["workspace_bytes"] == need
+        if plain["row_tile"] == 256:
+            own += info["row_tile"] == 128
+            other += info["row_tile"] == 256
+    assert own >= 20 and other >= 3
