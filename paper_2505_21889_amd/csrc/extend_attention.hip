@@ -23,6 +23,7 @@
 // one head-dim element per lane) -- and converted to bf16 operands in registers.  The codes'
 // values are exact in bf16; the key scale is folded into the softmax scale and the value
 // scale into the final normalisation.
+#include <cstddef>
 #include <type_traits>
 
 #include "efim_internal.h"
@@ -94,8 +95,19 @@ struct AttnParams {
 };
 
 
-// Bytes of the kernel's arguments in front of its struct (EFIM_ARGS): five pointers and four integers.
-constexpr int kArgsInFront = 5 * 8 + 4 * 4;
+// The kernel's arguments as they lie in its argument block: each where a struct of them would have it.  The launch
+// checks that the kernel's parameters are these.
+struct KernelArgs {
+  const DevItem* items;
+  const int32_t* block_table;
+  const uint16_t* q_rows;
+  const uint16_t* k_pages;
+  const uint16_t* v_pages;
+  int32_t max_pages, kv_heads, shape, static_items;
+  AttnParams p;
+};
+constexpr int kFreqAt = offsetof(KernelArgs, p) + offsetof(AttnParams, inv_freq);
+static_assert(std::is_standard_layout<KernelArgs>::value && kFreqAt % 4 == 0, "read with 16-byte loads of aligned words");
 
 constexpr float kSlack = 8.f;  // log2 units by which a row max may outgrow its reference
 
@@ -490,7 +502,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   char* const s_freq = s_table + (threadIdx.x >> 6) * 1024;
   if constexpr (FUSED) {
     typedef const __attribute__((address_space(4))) char* ArgPtr;
-    const ArgPtr freq = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr() + kArgsInFront + offsetof(AttnParams, inv_freq);
+    const ArgPtr freq = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr() + kFreqAt;
     load_to_lds_16((const void*)(uintptr_t)freq, (threadIdx.x & 31u) * 16u, (uint32_t)(uintptr_t)(LDS_PTR(char))s_freq);
   }
 
@@ -1794,6 +1806,12 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 // for that), so that the work item is the first thing it waits for.  With them, the rest of the arguments asked for
 // beside the work item and the frequencies copied to LDS instead of loaded behind it: one request of 2344 keys, 32
 // layers 354 -> 346 us; 32 requests of 2048..8192 keys, 28/4 heads 69.9 -> 69.3 us per layer.
+static_assert(std::is_same<decltype(&extend_attention_kernel<128, 4, 2, true, false, true>),
+                           void (*)(decltype(KernelArgs::items), decltype(KernelArgs::block_table), decltype(KernelArgs::q_rows),
+                                    decltype(KernelArgs::k_pages), decltype(KernelArgs::v_pages), decltype(KernelArgs::max_pages),
+                                    decltype(KernelArgs::kv_heads), decltype(KernelArgs::shape),
+                                    decltype(KernelArgs::static_items), decltype(KernelArgs::p))>::value,
+              "KernelArgs describes the kernel's parameters");
 #define EFIM_ARGS(p) \
   p.items, p.block_table, p.q, p.k_cache, p.v_cache, p.max_pages, p.num_kv_heads, p.group | p.page_shift << 8, p.static_items, p
 
