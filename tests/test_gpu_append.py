@@ -9,7 +9,9 @@ from oracle import efim_oracle as O
 from paper_2505_21889_amd import workloads as W
 
 import gpu_util as U
-from test_gpu_fp8 import gpu_append8, oracle_cache8, oracle_step8
+from oracle import fp8_oracle as F
+from test_gpu_decode import run_decode
+from test_gpu_fp8 import gpu_append8, oracle_cache8, oracle_step8, run_decode8
 
 pytestmark = pytest.mark.gpu
 
@@ -149,3 +151,42 @@ def test_midpoints_round_once(E):
                                  b.rope_base, interleaved=bool(interleaved))
         for x, y in zip(got, (q_ref, kc, vc)):
             assert np.array_equal(x, y)
+
+
+SPECIAL = np.array([0x7F80, 0xFF80, 0x7FC0, 0xFFC0, 0x7F81, 0xFFFF, 0x0000, 0x8000, 0x0001, 0x8001, 0x007F, 0x0080, 0x8080,
+                    0x00FF, 0x7F7F, 0xFF7F, 0x3F80, 0xBF80], np.uint16)   # inf, NaN, zero, subnormal, least normal, largest, one
+
+
+@pytest.mark.parametrize("interleaved", [0, 1])
+@pytest.mark.parametrize("heads,d", [((8, 2), 128), ((4, 4), 64)])
+def test_special_values_are_rotated_as_in_fp64(E, heads, d, interleaved):
+    """Infinities, NaN, zeros, subnormals and the largest numbers beside bit patterns drawn at random, as queries, keys
+    and values: each number as the oracle has it, NaN (whose bits are not defined) where it has NaN."""
+    rng = np.random.default_rng(d + interleaved)
+    c, n = np.array([0, 5, 900], np.int32), np.array([8, 5, 8], np.int32)   # (position 0: cosine 1, sine 0)
+    b = W.make_batch("c1", seed=d, lengths=(c, n), heads=heads, head_dim=d)
+    for x in (b.q_new, b.k_new, b.v_new):
+        x[:] = np.where(rng.random(x.shape) < 0.5, rng.choice(SPECIAL, x.shape), rng.integers(0, 1 << 16, x.shape))
+
+    def same(got, want):
+        nan = np.isnan(O.bf16_to_f64(want))
+        assert np.array_equal(np.isnan(O.bf16_to_f64(got)), nan) and np.array_equal(got[~nan], want[~nan])
+
+    with np.errstate(all="ignore"):
+        kc, vc = U.oracle_cache(b)
+        got = U.gpu_rope_append(E, b, kc, vc, interleaved)
+        step = run_decode(E, b, kc, vc, interleaved)[1:3]
+        q_ref, _ = O.rope_append(b.cached_len, b.new_len, b.block_table, b.page_size, b.q_new, b.k_new, b.v_new, kc, vc,
+                                 b.rope_base, interleaved=bool(interleaved))
+        assert np.isnan(O.bf16_to_f64(q_ref)).any() and np.isinf(O.bf16_to_f64(q_ref)).any()
+        for x, y in zip(got + step, (q_ref, kc, vc, kc, vc)):
+            same(x, y)
+        for scale in (0.0123, 300.0, 2.0 ** -126, 3.0e38):
+            kc8, vc8 = oracle_cache8(b, scale, scale)
+            got = gpu_append8(E, b, kc8, vc8, scale, scale, interleaved)
+            step = run_decode8(E, b, kc8, vc8, scale, scale, interleaved)[1:3]
+            F.rope_append_fp8(b.cached_len, b.new_len, b.block_table, b.page_size, None, b.k_new, b.v_new, kc8, vc8,
+                              b.rope_base, scale, scale, bool(interleaved))
+            same(got[0], q_ref)
+            for x, y in zip(got[1:] + step, (kc8, vc8, kc8, vc8)):   # (one code stands for every NaN)
+                assert np.array_equal(x, y)
