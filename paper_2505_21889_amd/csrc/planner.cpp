@@ -66,9 +66,11 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // the tile leaves less of a last tile empty and packs better; with long ranges the gathers count and little else
 // does.  A compute-heavy step ("compute-heavy": more than the machine balance of about 315 flop per byte, 2.5
 // PFLOP/s over 8 TB/s) takes 128 rows up to 32 key tiles in the mean, 64 with head dim 64, and over 8-bit caches
-// whenever the workspace that the size query names holds that plan (fp8_plan).  256 / 128 rows, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim
-// 128, up to 32 tiles 0.95 (0.77 .. 1.02), 32 to 100 tiles 0.99 (0.95 .. 1.02), above 1.01 (0.94 .. 1.06); head dim 64,
-// up to 64 tiles 0.96 (0.87 .. 1.01); 8-bit caches, 9 to 214 tiles, 0.92 (0.80 .. 0.98).
+// whenever the workspace that the size query names holds that plan (fp8_plan).  Time with 128 rows over time
+// with 256, drawn steps with more than 128 rows per kv head, geometric mean (range): bf16, head dim 128, up to 32
+// tiles 0.954 (0.77 .. 1.02, 23 steps), 32 to 40 0.991 (0.95 .. 1.01, 6), 40 to 100 0.997 (0.95 .. 1.11, 9), above 1.009
+// (0.94 .. 1.06, 13): past 32 nothing is gained in the mean, and the 256 rows that gather half as often
+// stay.  Head dim 64, up to 64 tiles 0.96 (0.87 .. 1.01); 8-bit caches, 9 to 214 tiles, 0.92 (0.80 .. 0.98).
 // A step bound by HBM takes 256 rows when it has at least two such tiles per compute unit, which then balance
 // over the units without cutting key ranges (no merge pass), and few of its key ranges are read by more
 // than one tile (34 requests of 824..1782 + 203..512 tokens, 32/32 heads: 416 / 396 us).
@@ -424,7 +426,7 @@ void build(const efim_batch_t* b, int num_slots, int M, Plan* plan) {
     while (!plan->items.empty() && plan->items.back().row_count == 0) plan->items.pop_back();
   }
 
-  // Items past the ones that start at once can be drawn from a counter by the workgroups that start later,
+  // Items past the ones that start at once can be drawn from a counter by the workgroups that start later (batch calls),
   // longest first, where no two read the same keys.  The dispatcher deals workgroups to the eight XCDs in turn,
   // the same number to each, but an XCD streams up to 10 % faster or slower than another (which ones
   // differs from one set of buffers to the next): bound by HBM, with the second half of the items dealt out, the

@@ -126,7 +126,7 @@ __device__ __forceinline__ void rotate_units(u32x4& a, u32x4& b, const double (&
 // step, evaluated the cosines with one of its four waves and read the rows behind a barrier.  us, before / now,
 // passes over the same buffers: 2176 tokens of 16 requests, 32/8 heads 18.6 / 15.0 (other buffers every
 // pass); 1113 tokens, 32/32 heads 11.2 / 9.1; 1014 tokens, 28/4 heads 6.7 / 5.5 (5 us of it the host's), 8-bit
-// cache 8.7 / 5.8; 87286 tokens, 32/8 heads 384 / 365 = 5.9 TB/s.  One pass per wave is 6-10 % slower
+// cache 8.7 / 5.8; 87286 tokens, 32/8 heads 419 / 394 = 5.4 TB/s.  One pass per wave is 6-10 % slower
 // at 1000 to 2000 tokens, three 0-5 % either way.
 template <int D, bool INTERLEAVED, bool KV8, int MAXREQ>
 __global__ __launch_bounds__(kThreads) void rope_append_kernel(
