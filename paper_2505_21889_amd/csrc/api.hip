@@ -782,7 +782,7 @@ efim_plan_t* efim_plan_create(const efim_batch_t* batch, int decode) {
   if (!plan.merges.empty())
     std::memcpy(pl->image.data() + plan.off_merges, plan.merges.data(), plan.merges.size() * sizeof(MergeItem));
   pl->off_tickets = align256(plan.header_bytes);
-  pl->off_partials = pl->off_tickets + align256(plan.merges.size() * sizeof(int32_t));
+  pl->off_partials = pl->off_tickets + align256((plan.merges.size() << ticket_shift(plan.merges.size())) * sizeof(int32_t));
   pl->total_bytes = pl->off_partials + plan.total_bytes;
   return pl;
 }
@@ -799,7 +799,8 @@ int efim_plan_upload(efim_plan_t* plan, void* workspace, size_t workspace_bytes,
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* ws = static_cast<char*>(workspace);
   EFIM_HIP(hipMemcpyAsync(ws, plan->image.data(), plan->image.size(), hipMemcpyHostToDevice, s));
-  return launch_zero_words(reinterpret_cast<int32_t*>(ws + plan->off_tickets), plan->plan.merges.size(), s);
+  const size_t merges = plan->plan.merges.size();
+  return launch_zero_words(reinterpret_cast<int32_t*>(ws + plan->off_tickets), merges << ticket_shift(merges), s);
 }
 
 int efim_extend_attention_planned(const efim_plan_t* plan, const int32_t* block_table, const void* q,

@@ -25,6 +25,17 @@ constexpr int kStageSlots = 64;       // launch tokens in turn: a token comes ro
 constexpr int kTicketSlots = kStageSlots;
 constexpr int kTicketsPerSlot = 8192; // split query tiles one launch can combine in-kernel, and (the last one) its queue
 
+// log2 of the distance of a launch's arrival counters, in counters: 64 bytes while its block then holds them all in
+// front of the queue's, else as far as it does.  Counters of one line are counted up one after another, from whatever
+// XCD.  us, all counters of a launch in one line / in lines of their own: one new token, one request of 2344 keys,
+// 32 layers 356.5 / 349.9, two of 4290 and 10819 keys, 28/4 heads 14.5 / 13.6, four of 4000..5000 over codes
+// 15.7 / 14.6; as a plan object the first 345.0 / 337.5.  128 and 256 bytes are the same as 64.
+inline int ticket_shift(size_t merges) {
+  int shift = 4;
+  while (shift > 0 && (merges << shift) >= (size_t)kTicketsPerSlot) --shift;
+  return shift;
+}
+
 // Key tiles that the items of a launch have in the mean for its later ones to be drawn (reason at plan_draws).
 constexpr int kLongItems = 28;
 
@@ -165,8 +176,8 @@ int launch_rope_append(const efim_batch_t* b, int64_t total_new, void* q, const 
 // `stage_slot` is the index of the call's launch token (0 .. kStageSlots-1): it selects the
 // launch's block of arrival counters.  Negative: no token, split key ranges are combined by the
 // second launch.
-// `tickets` (optional): DEVICE arrival counters owned by the caller (one per split query tile, zero between launches);
-// given, the split key ranges are combined inside the main kernel with these counters and no launch token is needed.
+// `tickets` (optional): DEVICE arrival counters owned by the caller (one per split query tile, ticket_shift apart,
+// zero between launches); given, the split key ranges are combined inside the main kernel with these counters and no launch token is needed.
 // Without a token items follow the workgroup ids.  `quiet`: the timing hook is not served (a launch that may be
 // under graph capture records no events).
 int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char* header, int stage_slot,

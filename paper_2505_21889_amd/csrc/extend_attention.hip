@@ -37,7 +37,8 @@ namespace {
 // combines the parts.  One block of counters per work-list staging slot, so that launches in
 // flight at the same time never share a counter; all zero whenever no launch is running
 // (zero-initialised with the module, and the merging workgroup puts its counter back).
-__device__ int32_t g_tickets[kTicketSlots * kTicketsPerSlot];
+// (Aligned, so that which counters share a line does not follow from the size of the code in front of them.)
+__device__ __align__(256) int32_t g_tickets[kTicketSlots * kTicketsPerSlot];
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -50,9 +51,6 @@ typedef __attribute__((ext_vector_type(2))) int i32x2;
 
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
-// (The order and size of the fields were kept after measuring: with the same instructions in the kernel, one request of
-// 2344 keys through 32 layers takes 345 us with them as they are and 352 with 24 bytes more, with the frequencies
-// split off, or with duplicates of the leading arguments left out.  The cause was not found.)
 struct AttnParams {
   const DevItem* items;
   const uint16_t* q;
@@ -83,6 +81,7 @@ struct AttnParams {
   const MergeItem* merges;
   int32_t ticket_base;    // first arrival counter of this launch in g_tickets (or in `tickets`),
                           // or -1: the split key ranges are combined by merge_kernel in a second launch
+  int32_t ticket_shift;   // counter of merge i: 2^ticket_shift * i behind the first
   int32_t* tickets;       // the caller's arrival counters, or nullptr: the library's own
   int32_t page_shift;     // log2 of the page size (tokens per page)
   int32_t interleaved;    // rotary pairing
@@ -1691,7 +1690,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   // is drawn.
   if (it.partial_slot >= 0 && p.ticket_base >= 0) {
     const MergeItem mi = p.merges[it.merge_id];
-    int32_t* ticket = (p.tickets ? p.tickets : g_tickets) + p.ticket_base + it.merge_id;
+    int32_t* ticket = (p.tickets ? p.tickets : g_tickets) + p.ticket_base + (it.merge_id << p.ticket_shift);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     if (tid == 0)
@@ -1753,6 +1752,7 @@ void fill_params(AttnParams* p, const efim_batch_t* b, const Plan& plan, const c
   p->k_cache_w = nullptr;
   p->v_cache_w = nullptr;
   p->ticket_base = -1;
+  p->ticket_shift = ticket_shift(plan.merges.size());
   p->tickets = nullptr;
   p->queue_at = 0;
   p->static_items = (int32_t)plan.items.size();

@@ -183,6 +183,13 @@ int main() {
     return 1;
   }
   if (static_limits(rng)) return 1;
+  for (size_t merges = 1; merges < (size_t)kTicketsPerSlot; ++merges) {
+    const int shift = ticket_shift(merges);   // counters apart, all in front of the block's last word
+    if (((merges - 1) << shift) >= (size_t)kTicketsPerSlot - 1 || (shift < 4 && (merges << (shift + 1)) < (size_t)kTicketsPerSlot)) {
+      printf("%zu counters: shift %d\n", merges, shift);
+      return 1;
+    }
+  }
   printf("planner ok, %ld items, %ld plans for the whole-range kernel, %ld with queued items\n", items_total, once_plans, queued_plans);
   return 0;
 }

@@ -369,6 +369,40 @@ def test_decode_step_with_the_merge_in_a_second_launch(E):
     assert np.array_equal(in_kernel, second_launch)
 
 
+@pytest.mark.parametrize("merges", [511, 512, 1024, 4095, 4096, 8191, 8192])
+def test_as_many_split_ranges_as_there_are_counters(E, merges):
+    """Arrival counters lie further apart the fewer a launch needs; 8192 split ranges are one more than a launch has
+    counters.  Batch call and plan object, each twice, against the oracle, and bit for bit against the second launch."""
+    c = np.full(merges, 100, dtype=np.int32)
+    b = W.make_batch("c1", seed=merges, lengths=(c, np.ones_like(c)), heads=(1, 1), head_dim=64)
+    kc, vc = U.oracle_cache(b)
+    _, kc_ref, vc_ref, ref = oracle_step(b, kc, vc)
+    E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, 64)
+    try:
+        table = torch.from_numpy(b.block_table).cuda()
+        desc = U.make_desc(E, b, table)
+        assert E.efim_plan_info(desc)["merges"] == merges
+        E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, 0)
+        want = run_decode(E, b, kc, vc)[0]
+        U.assert_close(want, ref)
+        E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, 1)
+        for _ in range(2):
+            got, kc_got, vc_got, _ = run_decode(E, b, kc, vc)
+            assert np.array_equal(got, want) and np.array_equal(kc_got, kc_ref) and np.array_equal(vc_got, vc_ref)
+        plan = E.Plan(desc, decode=True)
+        nbytes = E.efim_plan_workspace_bytes(plan)
+        ws = torch.full((nbytes,), 0x5A, dtype=torch.uint8, device="cuda")
+        E.efim_plan_upload(plan, ws, nbytes)
+        q, kn, vn, kcd, vcd = (U.dev_bits(x) for x in (b.q_new, b.k_new, b.v_new, kc, vc))
+        for _ in range(2):
+            out = torch.zeros_like(q)
+            E.efim_decode_step_planned(plan, table, q, kn, vn, kcd, vcd, out, b.rope_base, 0, 0.0, ws)
+            assert np.array_equal(U.host_bits(out), want)
+    finally:
+        E.efim_set_tuning(E.EFIM_TUNE_SPLIT_KV, -1)
+        E.efim_set_tuning(E.EFIM_TUNE_FUSED_MERGE, -1)
+
+
 def test_decode_sequence_grows_the_cache_token_by_token(E):
     """Eight consecutive decode steps of three requests: the caches after the last step and
     every step's output equal the oracle's, which appends token by token too."""
