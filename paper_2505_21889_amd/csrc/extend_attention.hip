@@ -494,12 +494,17 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   // the "this workgroup merges" flag is only used once the tile buffers are dead
   int* const s_last = reinterpret_cast<int*>(lds);
 
-  // Fused step: the rotation frequencies go straight from the kernel's arguments to LDS, a copy for each
-  // wave, ahead of everything (a load into registers would be moved behind the work item's, and waited
-  // for there).  The copy lies where this wave will put its first tokens' cosines and sines.
+  // Fused step: the rotation frequency of this thread's pair (thread = (token, pair)), read in the shadow of the work
+  // item's load -- behind the gathers it would wait for them.  ONCE: the frequencies go straight from the kernel's
+  // arguments to LDS, a copy for each wave, where this wave will put its first tokens' cosines and sines: with one
+  // item per compute unit nothing covers the wait for the register, which the compiler puts behind the item.  With
+  // many items per unit it is the copies that cost: one new token, 300 requests of 200..400 keys, 32/8 heads 96.8 us
+  // with them and 95.3 without, head dim 64 47.2 / 46.3, 298 such over codes 41.1 / 39.4.
   char* const s_table = ONCE ? lds + kTileBufBytes + kFusedBytes : lds + (STAGES - 1) * kStageBytes;
   char* const s_freq = s_table + (threadIdx.x >> 6) * 1024;
-  if constexpr (FUSED) {
+  double inv_freq = 0.0;
+  if constexpr (FUSED && !ONCE) inv_freq = p.inv_freq[threadIdx.x % (D / 2)];
+  if constexpr (FUSED && ONCE) {
     typedef const __attribute__((address_space(4))) char* ArgPtr;
     const ArgPtr freq = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr() + kFreqAt;
     load_to_lds_16((const void*)(uintptr_t)freq, (threadIdx.x & 31u) * 16u, (uint32_t)(uintptr_t)(LDS_PTR(char))s_freq);
@@ -511,10 +516,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   if constexpr (!ONCE) {
     if (__builtin_expect(index >= static_items, 0)) {
       index = draw_item(p, static_items, reinterpret_cast<int*>(lds));
-      if (index < 0) {
-        if constexpr (FUSED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
-        return;
-      }
+      if (index < 0) return;
     }
   }
   const DevItem staged = items[index];
@@ -523,7 +525,7 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   if constexpr (FUSED) asm volatile("" ::"s"(p.k_new), "s"(p.v_new), "s"(p.rotary_dim), "s"(p.interleaved));
   asm volatile("" ::"s"(p.num_q_heads), "s"(p.out), "s"(p.part_o), "s"(p.scale_log2), "s"(it.row_count), "s"(staged.cached));
   if (it.row_count == 0) {
-    if constexpr (FUSED) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
+    if constexpr (FUSED && ONCE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load into LDS outlives the workgroup
     return;
   }
   struct { int32_t cached, row_start; } rq;
@@ -1215,8 +1217,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   // 32 requests of 2048..8192 keys, 28/4 heads 74.9 -> 72.3 us, 8-bit cache 43.7 -> 41.6 us; 16
   // requests of 1024..4096 keys, 32/32 heads 124.9 -> 118.9 us.
   const int n_tok = it.row_count / g;  // fused: all rows of the (request, kv head) pair are in this tile
-  double inv_freq = 0.0;  // of this thread's pair (thread = (token, pair))
   if constexpr (FUSED) {
+    if constexpr (!ONCE) asm volatile("" ::"v"(inv_freq) : "memory");
     constexpr int kRawChunks = D / 8;            // 16-byte chunks of a bf16 row
     constexpr int kRowsPerLoad = 64 / kRawChunks;
     static_assert(kFusedRows % kRowsPerLoad == 0 && kFusedMaxTokens * 2 % kRowsPerLoad == 0, "loads fill whole areas");
@@ -1239,16 +1241,18 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
       }
       load_to_lds_16(src, dst);
     }
-    // the frequencies have landed: all but this wave's raw rows
-    static_assert((kFusedRows + 2 * kFusedMaxTokens) / kRowsPerLoad <= 4 * WAVES, "the wait counts that many loads");
-    switch ((q_loads + kv_loads - wave + WAVES - 1) / WAVES) {
-      case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
-      case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
-      case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
-      case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
-      default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if constexpr (ONCE) {
+      // the frequencies have landed: all but this wave's raw rows
+      static_assert((kFusedRows + 2 * kFusedMaxTokens) / kRowsPerLoad <= 4 * WAVES, "the wait counts that many loads");
+      switch ((q_loads + kv_loads - wave + WAVES - 1) / WAVES) {
+        case 1: asm volatile("s_waitcnt vmcnt(1)" ::: "memory"); break;
+        case 2: asm volatile("s_waitcnt vmcnt(2)" ::: "memory"); break;
+        case 3: asm volatile("s_waitcnt vmcnt(3)" ::: "memory"); break;
+        case 4: asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); break;
+        default: asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      }
+      inv_freq = reinterpret_cast<const double*>(s_freq)[tid % (D / 2)];
     }
-    inv_freq = reinterpret_cast<const double*>(s_freq)[tid % (D / 2)];
   }
   if constexpr (ONCE) {
     // (page ids of all tiles together, one latency, where a page holds the four loads of a wave: bf16 rows of head
