@@ -52,10 +52,6 @@ typedef __attribute__((ext_vector_type(2))) int i32x2;
 #define LDS_PTR(T) __attribute__((address_space(3))) T*
 
 struct AttnParams {
-  const DevItem* items;
-  const uint16_t* q;
-  const uint16_t* k_cache;
-  const uint16_t* v_cache;
   uint16_t* out;
   // Partial result of one part of a split key range, per query row: the unnormalised output
   // row O as binary16 values O / a with a = max |O| over the row (half the bytes of fp32, on a
@@ -63,10 +59,7 @@ struct AttnParams {
   // relative error at 2^-11 of the row's largest element), and three fp32 values.
   uint16_t* part_o;  // [slot][rows_per_item][D] binary16 bits
   float* part_ml;    // [slot][rows_per_item][4] = (running max in log2 units, running sum, a, unused)
-  const int32_t* block_table;
-  int32_t max_pages;
   int32_t num_q_heads;
-  int32_t num_kv_heads;
   int32_t group;          // Hq / Hkv
   int32_t rows_per_item;  // rows of one partial-result slot
   float scale_log2;       // sm_scale * log2(e) (times the key scale of an 8-bit cache)
@@ -83,16 +76,13 @@ struct AttnParams {
                           // or -1: the split key ranges are combined by merge_kernel in a second launch
   int32_t ticket_shift;   // counter of merge i: 2^ticket_shift * i behind the first
   int32_t* tickets;       // the caller's arrival counters, or nullptr: the library's own
-  int32_t page_shift;     // log2 of the page size (tokens per page)
   int32_t interleaved;    // rotary pairing
   int32_t rotary_dim;     // leading elements of a head row that are rotated
   double inv_freq[64];    // rotation frequency of pair j (rotary_dim / 2 entries)
   int32_t queue_at;       // the counter of drawn items, in g_tickets
   int32_t queued_items;   // items from static_items on are drawn from the queue
   int32_t draws;          // workgroups that draw
-  int32_t static_items;   // the workgroup's item is its id below this
 };
-
 
 // The kernel's arguments as they lie in its argument block: each where a struct of them would have it.  The launch
 // checks that the kernel's parameters are these.
@@ -102,7 +92,10 @@ struct KernelArgs {
   const uint16_t* q_rows;
   const uint16_t* k_pages;
   const uint16_t* v_pages;
-  int32_t max_pages, kv_heads, shape, static_items;
+  int32_t max_pages;     // columns of the block table
+  int32_t kv_heads;
+  int32_t shape;         // heads per group, from bit 8 on the log2 of the page size (tokens per page)
+  int32_t static_items;  // the workgroup's item is its id below this
   AttnParams p;
 };
 constexpr int kFreqAt = offsetof(KernelArgs, p) + offsetof(AttnParams, inv_freq);
@@ -1727,20 +1720,25 @@ __global__ __launch_bounds__(256) void merge_kernel(const AttnParams p, const Me
 
 namespace {
 
-void fill_params(AttnParams* p, const efim_batch_t* b, const Plan& plan, const char* header, const void* q,
+void fill_params(KernelArgs* args, const efim_batch_t* b, const Plan& plan, const char* header, const void* q,
                  const void* k_cache, const void* v_cache, void* out, float sm_scale, const CacheFormat& fmt,
                  char* partials) {
-  p->items = reinterpret_cast<const DevItem*>(header + plan.off_items);
-  p->q = static_cast<const uint16_t*>(q);
-  p->k_cache = static_cast<const uint16_t*>(k_cache);
-  p->v_cache = static_cast<const uint16_t*>(v_cache);
+  args->items = reinterpret_cast<const DevItem*>(header + plan.off_items);
+  args->block_table = b->block_table;
+  args->q_rows = static_cast<const uint16_t*>(q);
+  args->k_pages = static_cast<const uint16_t*>(k_cache);
+  args->v_pages = static_cast<const uint16_t*>(v_cache);
+  args->max_pages = b->max_pages_per_req;
+  args->kv_heads = b->num_kv_heads;
+  int page_shift = 0;
+  while ((1 << page_shift) < b->page_size) ++page_shift;
+  args->shape = b->num_q_heads / b->num_kv_heads | page_shift << 8;
+  args->static_items = (int32_t)plan.items.size();
+  AttnParams* const p = &args->p;
   p->out = static_cast<uint16_t*>(out);
   p->part_o = reinterpret_cast<uint16_t*>(partials + plan.off_part_o);
   p->part_ml = reinterpret_cast<float*>(partials + plan.off_part_ml);
-  p->block_table = b->block_table;
-  p->max_pages = b->max_pages_per_req;
   p->num_q_heads = b->num_q_heads;
-  p->num_kv_heads = b->num_kv_heads;
   p->group = b->num_q_heads / b->num_kv_heads;
   p->rows_per_item = plan.partial_rows;
   p->scale_log2 = sm_scale * 1.4426950408889634f;
@@ -1759,11 +1757,8 @@ void fill_params(AttnParams* p, const efim_batch_t* b, const Plan& plan, const c
   p->ticket_shift = ticket_shift(plan.merges.size());
   p->tickets = nullptr;
   p->queue_at = 0;
-  p->static_items = (int32_t)plan.items.size();
   p->queued_items = p->draws = 0;
   p->merges = reinterpret_cast<const MergeItem*>(header + plan.off_merges);
-  p->page_shift = 0;
-  while ((1 << p->page_shift) < b->page_size) ++p->page_shift;
   p->interleaved = 0;
   p->rotary_dim = b->head_dim;
   for (double& f : p->inv_freq) f = 0.0;
@@ -1793,12 +1788,12 @@ bool use_tickets(const Plan& plan) {
 // may be drawn.  (A plan object's launches have none: a counter in the workspace would be
 // shared by launches of one plan that run at the same time, which where no range is cut only read it.  16 requests of
 // 1024..4096 keys, one new token, 32/32 heads: 118.0 us as a plan object, 116.2 when it could draw.)
-unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, AttnParams* p) {
+unsigned workgroups(const Plan& plan, bool fp8, int stage_slot, KernelArgs* args) {
   if (stage_slot < 0 || !plan_draws(plan, fp8)) return (unsigned)plan.items.size();
-  p->queue_at = (stage_slot + 1) * kTicketsPerSlot - 1;
-  p->static_items = plan.static_items;
-  p->queued_items = plan.queued_items;
-  p->draws = plan.draws;
+  args->static_items = plan.static_items;
+  args->p.queue_at = (stage_slot + 1) * kTicketsPerSlot - 1;
+  args->p.queued_items = plan.queued_items;
+  args->p.draws = plan.draws;
   return (unsigned)(plan.static_items + plan.draws);
 }
 
@@ -1808,17 +1803,16 @@ __global__ void zero_words_kernel(int32_t* words, size_t count) {
 }
 
 // The kernel's arguments.  Those in front of the struct are in scalar registers when a wave starts (the build asks
-// for that), so that the work item is the first thing it waits for.  With them, the rest of the arguments asked for
-// beside the work item and the frequencies copied to LDS instead of loaded behind it: one request of 2344 keys, 32
-// layers 354 -> 346 us; steps of more work the same as without.
+// for that), so that the work item is the first thing it waits for; the rest is asked for beside the work item.  One
+// request of 2344 keys, 32 layers 347 us, without the first 357, without the second 361; 298 requests of 199..408
+// keys, head dim 64, over codes 39.4 / 39.6 / 40.6; 32 of 2048..8192, 28/4 heads, 16 layers 1131 / 1135 / 1134.
 static_assert(std::is_same<decltype(&extend_attention_kernel<128, 4, 2, true, false, true>),
                            void (*)(decltype(KernelArgs::items), decltype(KernelArgs::block_table), decltype(KernelArgs::q_rows),
                                     decltype(KernelArgs::k_pages), decltype(KernelArgs::v_pages), decltype(KernelArgs::max_pages),
                                     decltype(KernelArgs::kv_heads), decltype(KernelArgs::shape),
                                     decltype(KernelArgs::static_items), decltype(KernelArgs::p))>::value,
               "KernelArgs describes the kernel's parameters");
-#define EFIM_ARGS(p) \
-  p.items, p.block_table, p.q, p.k_cache, p.v_cache, p.max_pages, p.num_kv_heads, p.group | p.page_shift << 8, p.static_items, p
+#define EFIM_ARGS(a) a.items, a.block_table, a.q_rows, a.k_pages, a.v_pages, a.max_pages, a.kv_heads, a.shape, a.static_items, a.p
 
 // Key-parallel kernels: no work item has more than 32 query rows (R16, Plan::rows16: 16), always so for the decode step.
 // Four-wave kernels take two stages over bf16 rows and three over 8-bit rows, where a tile is half
@@ -1829,16 +1823,16 @@ static_assert(std::is_same<decltype(&extend_attention_kernel<128, 4, 2, true, fa
 // are better, 512 of 10 tiles 25.1 / 32.0, 520 of 8 tiles (four layers) 68.7 / 82.8, 320 of 4
 // tiles 15.3 / 16.1.  The plain call over the same rows is not faster with three.
 template <bool FUSED, bool R16>
-void launch_key_parallel(int head_dim, bool wide, bool fp8, bool crowded, bool once, dim3 grid, const AttnParams& p,
+void launch_key_parallel(int head_dim, bool wide, bool fp8, bool crowded, bool once, dim3 grid, const KernelArgs& args,
                          hipStream_t stream) {
 #define EFIM_KP(DD, WAVES, STAGES, F8, P8, ONCE) \
-  extend_attention_kernel<DD, WAVES, STAGES, FUSED, F8, true, false, P8, ONCE, R16><<<grid, 64 * (WAVES), 0, stream>>>(EFIM_ARGS(p))
+  extend_attention_kernel<DD, WAVES, STAGES, FUSED, F8, true, false, P8, ONCE, R16><<<grid, 64 * (WAVES), 0, stream>>>(EFIM_ARGS(args))
 #define EFIM_KP_FORMS(DD, F8, P8)                            \
   do {                                                       \
     if (wide) EFIM_KP(DD, 8, 3, F8, P8, false);              \
     else EFIM_KP(DD, 4, F8 ? 3 : 2, F8, P8, false);          \
   } while (0)
-  const bool two_pages = fp8 && head_dim == 64 && p.page_shift == 3;  // a load spans two pages
+  const bool two_pages = fp8 && head_dim == 64 && args.shape >> 8 == 3;  // a load spans two pages
   if (two_pages) {
     EFIM_KP_FORMS(64, true, true);
   } else if (once) {
@@ -1861,22 +1855,22 @@ void launch_key_parallel(int head_dim, bool wide, bool fp8, bool crowded, bool o
 }
 
 template <bool FUSED>
-void launch_kernel(int head_dim, const Plan& plan, bool fp8, dim3 grid, const AttnParams& p, hipStream_t stream) {
+void launch_kernel(int head_dim, const Plan& plan, bool fp8, dim3 grid, const KernelArgs& args, hipStream_t stream) {
   const bool wide = plan.rows_per_item == 256, crowded = plan.crowded;
   if (FUSED || plan.max_item_rows <= 32) {
-    if (plan.rows16) launch_key_parallel<FUSED, true>(head_dim, wide, fp8, crowded, plan.once, grid, p, stream);
-    else launch_key_parallel<FUSED, false>(head_dim, wide, fp8, crowded, plan.once, grid, p, stream);
+    if (plan.rows16) launch_key_parallel<FUSED, true>(head_dim, wide, fp8, crowded, plan.once, grid, args, stream);
+    else launch_key_parallel<FUSED, false>(head_dim, wide, fp8, crowded, plan.once, grid, args, stream);
     return;
   }
 #define EFIM_PIPE(DD, F8, PACK, P8)                                                                            \
   do {                                                                                                        \
-    if (wide) extend_attention_kernel<DD, 8, 3, false, F8, false, PACK, P8><<<grid, 512, 0, stream>>>(EFIM_ARGS(p));       \
-    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, false, F8, false, PACK, P8><<<grid, 256, 0, stream>>>(EFIM_ARGS(p));  \
+    if (wide) extend_attention_kernel<DD, 8, 3, false, F8, false, PACK, P8><<<grid, 512, 0, stream>>>(EFIM_ARGS(args));       \
+    else extend_attention_kernel<DD, 4, F8 ? 3 : 2, false, F8, false, PACK, P8><<<grid, 256, 0, stream>>>(EFIM_ARGS(args));  \
   } while (0)
   if (head_dim == 128) {
     if (fp8) EFIM_PIPE(128, true, false, false); else EFIM_PIPE(128, false, false, false);
   } else if (fp8) {
-    if (p.page_shift == 3) EFIM_PIPE(64, true, false, true); else EFIM_PIPE(64, true, false, false);
+    if (args.shape >> 8 == 3) EFIM_PIPE(64, true, false, true); else EFIM_PIPE(64, true, false, false);
   } else {
     if (crowded) EFIM_PIPE(64, false, true, false); else EFIM_PIPE(64, false, false, false);
   }
@@ -1908,8 +1902,9 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
                             const void* q, const void* k_cache, const void* v_cache, void* out,
                             float sm_scale, const CacheFormat& fmt, void* workspace, hipStream_t stream,
                             int32_t* tickets, bool quiet) {
-  AttnParams p;
-  fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
+  KernelArgs args;
+  AttnParams& p = args.p;
+  fill_params(&args, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
   if (tickets) {
     p.tickets = tickets;
     p.ticket_base = 0;
@@ -1917,11 +1912,11 @@ int launch_extend_attention(const efim_batch_t* b, const Plan& plan, const char*
     p.ticket_base = stage_slot * kTicketsPerSlot;
   }
 
-  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, &p));
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, &args));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
-  launch_kernel<false>(b->head_dim, plan, fmt.fp8, grid, p, stream);
+  launch_kernel<false>(b->head_dim, plan, fmt.fp8, grid, args, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
@@ -1933,8 +1928,9 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
                        const void* q, const void* k_new, const void* v_new, void* k_cache, void* v_cache,
                        void* out, const double* inv_freq, int rotary_dim, int interleaved, float sm_scale,
                        const CacheFormat& fmt, void* workspace, hipStream_t stream, int32_t* tickets, bool quiet) {
-  AttnParams p;
-  fill_params(&p, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
+  KernelArgs args;
+  AttnParams& p = args.p;
+  fill_params(&args, b, plan, header, q, k_cache, v_cache, out, sm_scale, fmt, static_cast<char*>(workspace));
   if (tickets) {
     p.tickets = tickets;
     p.ticket_base = 0;
@@ -1950,11 +1946,11 @@ int launch_decode_step(const efim_batch_t* b, const Plan& plan, const char* head
   const int D = b->head_dim;
   for (int j = 0; j < rotary_dim / 2; ++j) p.inv_freq[j] = inv_freq[j];
 
-  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, &p));
+  const dim3 grid(workgroups(plan, fmt.fp8, stage_slot, &args));
   Tuning tn = tuning();
   if (quiet) tn.ev_start = tn.ev_stop = nullptr;
   if (tn.ev_start) (void)hipEventRecord(tn.ev_start, stream);
-  launch_kernel<true>(D, plan, fmt.fp8, grid, p, stream);
+  launch_kernel<true>(D, plan, fmt.fp8, grid, args, stream);
   hipError_t e = hipGetLastError();
   if (tn.ev_stop) (void)hipEventRecord(tn.ev_stop, stream);
   if (e != hipSuccess) { set_last_hip_error(e); return EFIM_ERR_LAUNCH; }
