@@ -504,10 +504,8 @@ __global__ __launch_bounds__(64 * WAVES, ONCE ? 2 : waves_per_simd(D, WAVES, FUS
   }
 
   int index = blockIdx.x;
-  // (ONCE: all items start at once.  Out of the way elsewhere, too: with the draw in the straight line of the code one
-  // request of 2344 keys through 32 layers took 353 us instead of 346, two of 4290 and 10819 18.3 instead of 17.5.)
-  if constexpr (!ONCE) {
-    if (__builtin_expect(index >= static_items, 0)) {
+  if constexpr (!ONCE) {  // (there all items start at once)
+    if (index >= static_items) {
       index = draw_item(p, static_items, reinterpret_cast<int*>(lds));
       if (index < 0) return;
     }
