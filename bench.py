@@ -32,7 +32,7 @@ if ROOT not in sys.path:
 # on: the digest of extend_attention.hip is recorded with it and checked at run time.
 MEASURED_TRAFFIC = {
     # workload: (bytes per launch, sha256 of csrc/extend_attention.hip when measured)
-    "c5": (2527453699, "3afde38e239aa7a4716a4235065619d4285507c929c65d8563a89c573867b25a"),
+    "c5": (2533009369, "cea31e96d587b5ec6c75ce5fb0016f7c1f00468e94f9bc377cf9411690604e93"),
 }
 
 PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA peak

@@ -1771,10 +1771,11 @@ namespace {
 // that pays when every tile has very few rows (decode steps of the usual head groupings),
 // where it saves a launch, and costs more than the launch as the rows grow, so by default it is used
 // when no work item has more than 8 query rows.  4 layers, second launch / in the kernel, us: 16 requests of
-// 3000 keys 4 rows 160.8 / 158.3, 8 rows 162.2 / 161.0, 14 rows 100.8 / 100.9 (28/4 heads), 16 rows 170.2 / 171.7, 32
-// rows 183.9 / 190.9; two calls 4 rows 185.3 / 183.8, 8 rows 186.6 / 187.4, 16 rows 190.7 / 195.8.  Many parts per
-// range cost the kernel a round of reads for every eight: two requests of 2344 keys, ten parts, 4 rows 43.1 /
-// 45.8; head dim 64 gains up to 16 rows with few parts (107.6 / 107.3) and loses as much with ten (40.1 / 44.0).
+// 3000 keys 4 rows 158.4 / 157.0, 8 rows 161.2 / 159.7, 14 rows 99.4 / 99.4 (28/4 heads), 16 rows 167.8 / 169.8, 32
+// rows 183.0 / 188.4; two calls 4 rows 173.9 / 172.9, 8 rows 175.0 / 176.2, 16 rows 178.6 / 184.1; four of 4000..5000
+// over codes, 4 rows 61.9 / 58.7.  Many parts per range cost the kernel a round of reads for every eight: two requests
+// of 2344 keys, ten parts, 4 rows 43.0 / 43.2; head dim 64 gains up to 16 rows with few parts (99.9 / 98.1) and loses
+// as much with ten (37.7 / 38.6).
 constexpr int kTicketMergeMaxRows = 8;
 bool use_tickets(const Plan& plan) {
   const int knob = tuning().fused_merge;
